@@ -42,7 +42,7 @@ HBM_PEAK_GBS = 8000.0
 def kernel_source_hash():
     import hashlib
     h = hashlib.sha256()
-    for f in ("fftgal_kernels.hip", "fftgal_internal.h"):
+    for f in ("fftgal_kernels.hip", "fftgal_fast.hip", "fftgal_device.h", "fftgal_internal.h"):
         with open(os.path.join(ROOT, "paper_1412_2033_amd", "csrc", f), "rb") as fh:
             h.update(fh.read())
     return h.hexdigest()[:16]

@@ -110,14 +110,14 @@ enum fftgal_precision {
 /* Flag or-ed into `precision` of fftgal_workspace_bytes* and fftgal_plan /
  * fftgal_plan_static.  By default a Ga plan takes per axis the smallest
  * 3,5,7-smooth double grid M >= 2N - 1.  With the flag it takes instead the
- * smallest length with specialised kernels (81, 125, 225, 245, 729 or 2025
- * points) at least 2N - 1 on each axis whose default length is at least 9,
- * when the grid then holds at most four times the points of the default grid
- * or at most 2^21 points (else the default grid).  The double-grid
+ * smallest of the lengths 81, 125, 225, 245, 729 and 2025 that is at least
+ * 2N - 1 on each axis whose default length is at least 9, when the grid then
+ * holds at most four times the points of the default grid or at most 2^21
+ * points (else the default grid).  The double-grid
  * quadrature is exact for every M >= 2N - 1 (Lemma integ_eval_VM, eq. MBA_GA),
- * so the bounds are those of the default grid up to rounding.  The specialised
- * transforms run several times faster per point than the generic ones, and the
- * workspace grows with the grid.  fftgal_grid_size reports the grid taken.
+ * so the bounds are those of the default grid up to rounding.  The kernels of
+ * these lengths are the most tuned ones; the workspace grows with the grid.
+ * fftgal_grid_size reports the grid taken.
  * EINVAL with GaNi and reduced plans, whose grids the scheme fixes. */
 #define FFTGAL_FAST_GRID 0x1000
 
@@ -372,11 +372,11 @@ int fftgal_bounds_of(struct fftgal_plan *plan, struct fftgal_plan *src, double *
  * (the series on Z_{2N-1} folded onto Z_N with the phase of s, then one
  * inverse DFT of size N), and every operator application runs the transform
  * passes once per shift with the phases S(s), S*(s) of the lemma, summing the
- * projected results.  Every N_a must be odd; 81, 125, 225, 245, 729 and 2025
- * run the specialised kernels, other 3,5,7-smooth lengths the generic ones,
- * and the other lengths (the primes 41, 113, 1013 among them) Bluestein's chirp
- * convolution of the smooth length L >= 2 N_a - 1 in the generic kernels.  Solves, bounds, history and
- * the bound tolerance work as for fftgal_plan; warm starts, a-posteriori
+ * projected results.  Every N_a must be odd; 3,5,7-smooth lengths from 9 to
+ * 2025 (3D: to 405, and 729 and 2025) run the specialised kernels, other smooth
+ * lengths the generic ones, and the other lengths (the primes 41, 113, 1013
+ * among them) Bluestein's chirp convolution of the smooth length L >= 2 N_a - 1
+ * in the generic kernels.  Solves, bounds, history and the bound tolerance work as for fftgal_plan; warm starts, a-posteriori
  * bounds and batches are not available (EINVAL).  The workspace holds 2^d
  * material fields of |N| values and transform intermediates of the N-grid:
  * fftgal_workspace_bytes_reduced (P as in fftgal_workspace_bytes_p).  With the

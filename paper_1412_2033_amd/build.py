@@ -8,6 +8,7 @@ Produces ``paper_1412_2033_amd/_lib/libfftgal.so`` from ``csrc/*.hip`` and
 
 from __future__ import annotations
 
+import concurrent.futures
 import os
 import shutil
 import subprocess
@@ -19,7 +20,10 @@ CSRC = os.path.join(HERE, "csrc")
 LIBDIR = os.path.join(HERE, "_lib")
 LIB = os.path.join(LIBDIR, "libfftgal.so")
 
-SOURCES = ["fftgal_kernels.hip", "fftgal.cpp"]
+FAST_PARTS = 8  # kFastParts: the specialised kernels are compiled in parts, side by side
+# (source, object, extra flags)
+UNITS = [("fftgal_fast.hip", "fftgal_fast%d.o" % p, ["-DFFTGAL_PART=%d" % p]) for p in range(FAST_PARTS)] + [
+    ("fftgal_kernels.hip", "fftgal_kernels.o", []), ("fftgal.cpp", "fftgal.o", [])]
 HIPCC_FLAGS = [
     "--offload-arch=gfx950",
     "-O3",
@@ -39,16 +43,20 @@ def hipcc():
 
 def build(verbose=True):
     os.makedirs(LIBDIR, exist_ok=True)
-    objs = []
-    for src in SOURCES:
-        obj = os.path.join(LIBDIR, os.path.splitext(src)[0] + ".o")
-        lang = ["-x", "hip"]
-        cmd = [hipcc()] + HIPCC_FLAGS + lang + ["-I", os.path.join(ROOT, "include"), "-I", CSRC,
-                                               "-c", os.path.join(CSRC, src), "-o", obj]
+
+    def compile_unit(unit):
+        src, obj, extra = unit
+        obj = os.path.join(LIBDIR, obj)
+        cmd = [hipcc()] + HIPCC_FLAGS + extra + ["-x", "hip", "-I", os.path.join(ROOT, "include"), "-I", CSRC,
+                                                 "-c", os.path.join(CSRC, src), "-o", obj]
         if verbose:
             print(" ".join(cmd), flush=True)
         subprocess.run(cmd, check=True)
-        objs.append(obj)
+        return obj
+
+    jobs = int(os.environ.get("MAX_JOBS", min(8, os.cpu_count() or 1)))
+    with concurrent.futures.ThreadPoolExecutor(max_workers=max(1, jobs)) as pool:
+        objs = list(pool.map(compile_unit, UNITS))
     tmp = LIB + ".tmp"
     cmd = [hipcc(), "--offload-arch=gfx950", "-shared", "-fPIC", "-o", tmp] + objs + \
         ["-Wl,-rpath,/opt/rocm/lib"]

@@ -113,10 +113,10 @@ enum Scheme { kSchemeGa = 0, kSchemeGani = 1, kSchemeReduced = 2 };
 // (Def. GaNi, Algorithm 1).  Reduced Ga: the material series keeps its support
 // Z_{2N-1}, the transforms run on the N-grid (2^d shifted copies).  Lengths
 // that are not 3,5,7-smooth are transformed by Bluestein's algorithm.
-// Smallest length with specialised kernels that is at least m, or 0.
+// Smallest length FFTGAL_FAST_GRID takes that is at least m, or 0.
 int fast_length_at_least(int m) {
     int best = 0;
-    for (int i = 0; i < kNumFast; ++i)
+    for (int i = 0; i < kNumGridLengths; ++i)
         if (kFastSched[i].n >= m && (best == 0 || kFastSched[i].n < best)) best = kFastSched[i].n;
     return best;
 }

@@ -33,27 +33,48 @@ struct FftDesc {
     int hoff;
 };
 
-// Grid sizes with compile-time specialised kernels, and their radix
-// schedules (composite radices are done in registers).  The host builds the
-// twiddle tables of these lengths with the same schedule.  Schedules read the
-// same forwards and backwards where the length allows: then the last stage of
-// an inverse transform leaves each thread holding exactly the points that the
-// first stage of a forward transform consumes.
+// Transform lengths with compile-time specialised kernels, and their radix
+// schedules (composite radices are done in registers): every odd 3,5,7-smooth
+// length from 9 to 2025.  The host builds the twiddle tables of these lengths
+// with the same schedule, and the generic kernels run it too (radices 3, 5, 7,
+// 9, 15, 25).  The schedules of the first six read the same forwards and
+// backwards where the length allows: then the last stage of an inverse
+// transform leaves each thread holding exactly the points that the first stage
+// of a forward transform consumes.  The others get that from running the
+// forward transform as the transpose of the inverse one (row_iso_pairs).
 struct FastSched {
     int n;
     int nst;
     int r[4];
 };
 constexpr FastSched kFastSched[] = {
-    {81, 2, {9, 9, 0, 0}},      {125, 2, {25, 5, 0, 0}},  {225, 2, {15, 15, 0, 0}},
-    {245, 3, {7, 5, 7, 0}},     {729, 3, {9, 9, 9, 0}},   {2025, 3, {15, 9, 15, 0}},
+    {81, 2, {9, 9, 0, 0}},      {125, 2, {25, 5, 0, 0}},   {225, 2, {15, 15, 0, 0}},
+    {245, 3, {7, 5, 7, 0}},     {729, 3, {9, 9, 9, 0}},    {2025, 3, {15, 9, 15, 0}},
+    {9, 2, {3, 3, 0, 0}},       {15, 2, {5, 3, 0, 0}},     {21, 2, {3, 7, 0, 0}},
+    {25, 2, {5, 5, 0, 0}},      {27, 2, {9, 3, 0, 0}},     {35, 2, {5, 7, 0, 0}},
+    {45, 2, {5, 9, 0, 0}},      {49, 2, {7, 7, 0, 0}},     {63, 2, {9, 7, 0, 0}},
+    {75, 2, {5, 15, 0, 0}},     {105, 2, {7, 15, 0, 0}},   {135, 2, {15, 9, 0, 0}},
+    {147, 3, {7, 3, 7, 0}},     {175, 3, {5, 7, 5, 0}},    {189, 3, {9, 3, 7, 0}},
+    {243, 3, {9, 3, 9, 0}},     {315, 3, {9, 5, 7, 0}},    {343, 3, {7, 7, 7, 0}},
+    {375, 3, {5, 15, 5, 0}},    {405, 3, {9, 5, 9, 0}},    {441, 3, {7, 9, 7, 0}},
+    {525, 3, {7, 5, 15, 0}},    {567, 3, {9, 7, 9, 0}},    {625, 3, {5, 25, 5, 0}},
+    {675, 3, {9, 5, 15, 0}},    {735, 3, {7, 15, 7, 0}},   {875, 3, {5, 25, 7, 0}},
+    {945, 3, {7, 9, 15, 0}},    {1029, 4, {7, 7, 3, 7}},   {1125, 3, {15, 5, 15, 0}},
+    {1215, 3, {9, 15, 9, 0}},   {1225, 4, {7, 5, 5, 7}},   {1323, 4, {7, 9, 3, 7}},
+    {1575, 3, {15, 7, 15, 0}},  {1701, 4, {9, 7, 3, 9}},   {1715, 4, {7, 5, 7, 7}},
+    {1875, 4, {5, 15, 5, 5}},
 };
+// The lengths FFTGAL_FAST_GRID chooses from (the first entries of kFastSched).
+constexpr int kNumGridLengths = 6;
+// 3D passes are compiled for lengths up to kMaxFast3 and for the first six.
+constexpr int kMaxFast3 = 405;
 constexpr int kNumFast = sizeof(kFastSched) / sizeof(kFastSched[0]);
 constexpr int fast_index(int n) {
     for (int i = 0; i < kNumFast; ++i)
         if (kFastSched[i].n == n) return i;
     return -1;
 }
+constexpr bool fast_dim(int fi, int d) { return d == 2 || fi < kNumGridLengths || kFastSched[fi].n <= kMaxFast3; }
 
 // Device-resident state of one CG solve (Remark CG), advanced by the scalar
 // kernels; every kernel of an iteration returns at once when `done` is set.
@@ -308,6 +329,30 @@ struct LaunchEv {
     hipEvent_t start = nullptr;
     hipEvent_t stop = nullptr;
 };
+// The specialised kernels of one length: launchers, pencils (row pairs,
+// transforms) per work-group and LDS bytes, by precision (1: FP64) and
+// dimension (d - 2); a null launcher means there is none.
+struct FastKernels {
+    struct Pencil {
+        void (*fn)(const PencilArgs *, const int *, int np, int total, hipStream_t, LaunchEv) = nullptr;
+        int B = 0;
+        size_t lds = 0;
+    };
+    struct Row {
+        void (*fn)(const RowArgs *, const int *, int np, int total, hipStream_t, LaunchEv) = nullptr;
+        int RP = 0;
+        int nh_max = 0;  // longest half-spectrum row it takes
+        size_t lds = 0;
+    };
+    Pencil pencil[2][2];
+    Row row[2][2];    // any material: RP row pairs
+    Row iso[2][2];    // isotropic: RP transforms (row pair, component)
+    Row pairs[2][2];  // isotropic: RP transforms of whole row pairs
+    Row gram[2];      // FP64 energy Gram: RP row pairs
+};
+constexpr int kFastParts = 8;
+template <int PART> void fill_fast(FastKernels *table);  // entries fi with fi % kFastParts == PART
+const FastKernels &fast_kernels(int fi);
 hipError_t launch_pencil_multi(const PencilArgs &proto, const PencilArgs *args, const int *woff, int np,
                                int total, bool fp64, hipStream_t s, LaunchEv ev = LaunchEv{});
 hipError_t launch_row_multi(const RowArgs &proto, const RowArgs *args, const int *woff, int np, int total,

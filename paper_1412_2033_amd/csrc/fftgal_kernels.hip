@@ -5,248 +5,15 @@
 // Transforms are mixed-radix (3, 5, 7) self-sorting Stockham DFTs staged in
 // LDS; every grid size is odd (M >= 2N-1 odd and 3,5,7-smooth), so no radix 2
 // and no Nyquist frequency ever occurs.
-#include "fftgal_internal.h"
+#include "fftgal_device.h"
 
-#include <type_traits>
-
-#include <hip/hip_ext.h>
-#include <hip/hip_runtime.h>
+#include <utility>
 
 #include <algorithm>
 #include <cmath>
 
 namespace fftgal {
 namespace {
-
-template <typename T> struct VecOf;
-template <> struct VecOf<float> { using type = float2; };
-template <> struct VecOf<double> { using type = double2; };
-
-template <typename T> using Vt = typename VecOf<T>::type;
-
-// The argument tables hold generic pointers; operands known to live in device
-// global memory are cast to that address space so that the compiler emits
-// global (not flat) accesses and may move them past LDS accesses.
-template <typename T> __device__ __forceinline__ __attribute__((address_space(1))) T *gbl(T *p) {
-    return (__attribute__((address_space(1))) T *)(p);
-}
-
-template <typename T>
-__device__ __forceinline__ Vt<T> mk(T a, T b) {
-    Vt<T> v;
-    v.x = a;
-    v.y = b;
-    return v;
-}
-// complex loads and stores through global-address-space pointers, as one
-// 8- or 16-byte access of a native two-element vector
-template <typename V> struct ScalarOf;
-template <> struct ScalarOf<float2> { using type = float; };
-template <> struct ScalarOf<double2> { using type = double; };
-template <typename S> using NVec2 = S __attribute__((ext_vector_type(2)));
-template <typename V> __device__ __forceinline__ V gld(const __attribute__((address_space(1))) V *p) {
-    using S = typename ScalarOf<V>::type;
-    const NVec2<S> w = *reinterpret_cast<const __attribute__((address_space(1))) NVec2<S> *>(p);
-    V v;
-    v.x = w.x;
-    v.y = w.y;
-    return v;
-}
-template <typename V> __device__ __forceinline__ void gst(__attribute__((address_space(1))) V *p, V v) {
-    using S = typename ScalarOf<V>::type;
-    NVec2<S> w;
-    w.x = v.x;
-    w.y = v.y;
-    *reinterpret_cast<__attribute__((address_space(1))) NVec2<S> *>(p) = w;
-}
-template <typename V> __device__ __forceinline__ V cadd(V a, V b) {
-    a.x += b.x;
-    a.y += b.y;
-    return a;
-}
-template <typename V> __device__ __forceinline__ V csub(V a, V b) {
-    a.x -= b.x;
-    a.y -= b.y;
-    return a;
-}
-template <typename V> __device__ __forceinline__ V cmul(V a, V b) {
-    V r;
-    r.x = a.x * b.x - a.y * b.y;
-    r.y = a.x * b.y + a.y * b.x;
-    return r;
-}
-
-// cos(2 pi j / R) and sin(2 pi j / R), 0 <= j <= (R - 1) / 2.
-template <int R> __device__ constexpr double ccos(int j);
-template <int R> __device__ constexpr double csin(int j);
-template <> __device__ constexpr double ccos<3>(int j) { return j == 0 ? 1.0 : -0.5; }
-template <> __device__ constexpr double csin<3>(int j) {
-    return j == 0 ? 0.0 : 0.86602540378443864676372317075294;
-}
-template <> __device__ constexpr double ccos<5>(int j) {
-    return j == 0 ? 1.0 : j == 1 ? 0.30901699437494742410229341718282 : -0.80901699437494742410229341718282;
-}
-template <> __device__ constexpr double csin<5>(int j) {
-    return j == 0 ? 0.0 : j == 1 ? 0.95105651629515357211643933337938 : 0.58778525229247312916870595463907;
-}
-template <> __device__ constexpr double ccos<7>(int j) {
-    return j == 0 ? 1.0
-         : j == 1 ? 0.62348980185873353052500488400424
-         : j == 2 ? -0.22252093395631440428890256449680
-                  : -0.90096886790241912623610231950745;
-}
-template <> __device__ constexpr double csin<7>(int j) {
-    return j == 0 ? 0.0
-         : j == 1 ? 0.78183148246802980870844452667406
-         : j == 2 ? 0.97492791218182360701813168299393
-                  : 0.43388373911755812047576833284836;
-}
-
-// In-register DFT of odd length R: U[m] = sum_q u[q] exp(sg 2 pi i q m / R),
-// computed from the symmetric and antisymmetric pair sums u[q] +- u[R-q].
-template <typename T, int R>
-__device__ __forceinline__ void dft(Vt<T> *u, T sg) {
-    constexpr int H = (R - 1) / 2;
-    Vt<T> sp[H], sm[H];
-#pragma unroll
-    for (int q = 1; q <= H; ++q) {
-        sp[q - 1] = cadd(u[q], u[R - q]);
-        sm[q - 1] = csub(u[q], u[R - q]);
-    }
-    const Vt<T> u0 = u[0];
-    Vt<T> tot = u0;
-#pragma unroll
-    for (int q = 0; q < H; ++q) tot = cadd(tot, sp[q]);
-#pragma unroll
-    for (int m = 1; m <= H; ++m) {
-        Vt<T> a = u0;
-        Vt<T> b = mk<T>(T(0), T(0));
-#pragma unroll
-        for (int q = 1; q <= H; ++q) {
-            const int j = (q * m) % R;
-            const T cv = T(j <= H ? ccos<R>(j) : ccos<R>(R - j));
-            const T sv = T(j <= H ? csin<R>(j) : -csin<R>(R - j));
-            a.x += cv * sp[q - 1].x;
-            a.y += cv * sp[q - 1].y;
-            b.x += sv * sm[q - 1].x;
-            b.y += sv * sm[q - 1].y;
-        }
-        b.x *= sg;
-        b.y *= sg;
-        u[m] = mk<T>(a.x - b.y, a.y + b.x);
-        u[R - m] = mk<T>(a.x + b.y, a.y - b.x);
-    }
-    u[0] = tot;
-}
-
-constexpr double kPiD = 3.14159265358979323846;
-constexpr double cx_sin_small(double x) {
-    double x2 = x * x, t = x, s = x;
-    for (int k = 1; k < 14; ++k) {
-        t *= -x2 / ((2.0 * k) * (2.0 * k + 1.0));
-        s += t;
-    }
-    return s;
-}
-constexpr double cx_cos_small(double x) {
-    double x2 = x * x, t = 1.0, s = 1.0;
-    for (int k = 1; k < 14; ++k) {
-        t *= -x2 / ((2.0 * k - 1.0) * (2.0 * k));
-        s += t;
-    }
-    return s;
-}
-// cos and sin of 2 pi j / R by exact quadrant reduction of the rational j/R
-// and Taylor series on [0, pi/4] (evaluated at compile time).
-template <int R> struct TrigTab {
-    double c[R], s[R];
-    constexpr TrigTab() : c(), s() {
-        for (int j = 0; j < R; ++j) {
-            const int q = (4 * j) / R, r = 4 * j - q * R;
-            double cc = 0.0, ss = 0.0;
-            if (2 * r <= R) {
-                const double t = (kPiD / 2) * r / R;
-                cc = cx_cos_small(t);
-                ss = cx_sin_small(t);
-            } else {
-                const double u = (kPiD / 2) * (R - r) / R;
-                cc = cx_sin_small(u);
-                ss = cx_cos_small(u);
-            }
-            c[j] = q == 0 ? cc : q == 1 ? -ss : q == 2 ? -cc : ss;
-            s[j] = q == 0 ? ss : q == 1 ? cc : q == 2 ? -ss : -cc;
-        }
-    }
-};
-template <int R> struct Trig { static constexpr TrigTab<R> v{}; };
-
-constexpr int smallest_prime_factor(int n) {
-    for (int p = 2; p * p <= n; ++p)
-        if (n % p == 0) return p;
-    return n;
-}
-
-// In-register DFT of length R (any product of 3, 5, 7): prime lengths use the
-// symmetric butterflies above, composite ones R = R1 R2 a Cooley-Tukey split
-// (R2 DFTs of length R1, twiddles exp(sg 2 pi i n2 k1 / R), R1 DFTs of length
-// R2, output index k1 + R1 k2).
-template <typename T, int R>
-__device__ __forceinline__ void dftn(Vt<T> *u, T sg) {
-    if constexpr (R == 3 || R == 5 || R == 7) {
-        dft<T, R>(u, sg);
-    } else if constexpr (R == 15) {
-        // Good-Thomas split 15 = 3 * 5 (coprime, no twiddles): input index
-        // (5 n1 + 3 n2) mod 15, output index (10 k1 + 6 k2) mod 15
-        Vt<T> y[3][5];
-#pragma unroll
-        for (int n2 = 0; n2 < 5; ++n2) {
-            Vt<T> col[3];
-#pragma unroll
-            for (int n1 = 0; n1 < 3; ++n1) col[n1] = u[(5 * n1 + 3 * n2) % 15];
-            dft<T, 3>(col, sg);
-#pragma unroll
-            for (int k1 = 0; k1 < 3; ++k1) y[k1][n2] = col[k1];
-        }
-#pragma unroll
-        for (int k1 = 0; k1 < 3; ++k1) {
-            dft<T, 5>(y[k1], sg);
-#pragma unroll
-            for (int k2 = 0; k2 < 5; ++k2) u[(10 * k1 + 6 * k2) % 15] = y[k1][k2];
-        }
-    } else {
-        constexpr int R1 = smallest_prime_factor(R);
-        constexpr int R2 = R / R1;
-        Vt<T> y[R];
-#pragma unroll
-        for (int n2 = 0; n2 < R2; ++n2) {
-            Vt<T> col[R1];
-#pragma unroll
-            for (int n1 = 0; n1 < R1; ++n1) col[n1] = u[n1 * R2 + n2];
-            dftn<T, R1>(col, sg);
-#pragma unroll
-            for (int k1 = 0; k1 < R1; ++k1) {
-                const int j = (n2 * k1) % R;
-                if (j == 0) {
-                    y[k1 * R2 + n2] = col[k1];
-                } else {
-                    const T c = T(Trig<R>::v.c[j]);
-                    const T sn = sg * T(Trig<R>::v.s[j]);
-                    y[k1 * R2 + n2] = mk<T>(col[k1].x * c - col[k1].y * sn, col[k1].x * sn + col[k1].y * c);
-                }
-            }
-        }
-#pragma unroll
-        for (int k1 = 0; k1 < R1; ++k1) {
-            Vt<T> row[R2];
-#pragma unroll
-            for (int n2 = 0; n2 < R2; ++n2) row[n2] = y[k1 * R2 + n2];
-            dftn<T, R2>(row, sg);
-#pragma unroll
-            for (int k2 = 0; k2 < R2; ++k2) u[k1 + R1 * k2] = row[k2];
-        }
-    }
-}
-
 // One Stockham stage of radix R over nb independent transforms of length n.
 // Butterfly i (k = i mod p) reads positions i + q n/R, applies the twiddles
 // exp(sg 2 pi i q k / (p R)), a length-R DFT, and writes positions
@@ -363,109 +130,6 @@ __device__ __forceinline__ Vt<T> *fft_lds(Vt<T> *A, Vt<T> *Bf, const FftDesc &f,
     }
     __syncthreads();
     return Y;
-}
-
-// Deterministic work-group sum (fixed shuffle tree, then waves in order) over
-// a work-group of at most NT threads; the result is valid in thread 0.
-template <int NT>
-__device__ double block_sum_t(double v) {
-    __shared__ double red[NT / 64];
-    for (int off = 32; off > 0; off >>= 1) v += __shfl_down(v, off, 64);
-    const int lane = threadIdx.x & 63;
-    const int wave = threadIdx.x >> 6;
-    __syncthreads();
-    if (lane == 0) red[wave] = v;
-    __syncthreads();
-    double s = 0.0;
-    if (threadIdx.x == 0) {
-        for (int w = 0; w < (int)(blockDim.x >> 6); ++w) s += red[w];
-    }
-    __syncthreads();
-    return s;
-}
-__device__ double block_sum(double v) { return block_sum_t<kThreads>(v); }
-
-// K work-group sums at once, each in the order of block_sum (a shuffle tree
-// per wave, then the waves in turn), written to out[0 .. K-1] by the first K
-// threads: one barrier for all K instead of three per sum.
-template <int K>
-__device__ void block_sum_many(const double (&v)[K], double *out) {
-    __shared__ double red[K][kThreads / 64];
-    const int lane = threadIdx.x & 63;
-    const int wave = threadIdx.x >> 6;
-#pragma unroll
-    for (int k = 0; k < K; ++k) {
-        double x = v[k];
-        for (int off = 32; off > 0; off >>= 1) x += __shfl_down(x, off, 64);
-        if (lane == 0) red[k][wave] = x;
-    }
-    __syncthreads();
-    if (threadIdx.x < K) {
-        double s = 0.0;
-        for (int w = 0; w < (int)(blockDim.x >> 6); ++w) s += red[threadIdx.x][w];
-        out[threadIdx.x] = s;
-    }
-}
-
-__device__ __forceinline__ int wrapi(int i, int L) { return i < (L + 1) / 2 ? i : i - L; }
-__device__ __forceinline__ int posmod(int k, int n) {
-    int r = k % n;
-    return r < 0 ? r + n : r;
-}
-
-// Orthonormal basis t_a(k) (a < nc) of the admissible directions at frequency k:
-// primal (E_N): k/|k|; dual (J_N), d = 2: R k/|k| with R the rotation by +90
-// degrees; d = 3: t1 = k x e_j / |k x e_j| with j the axis of smallest |k_j|
-// (lowest index on ties) and t2 = s(k) k/|k| x t1 with s(k) the sign of the
-// first non-zero k_j.  Every t_a is odd in k, so a field i sum_a t_a(k) c_a(k)
-// is real exactly when each c_a is Hermitian.  Returns 0 at k = 0.
-template <typename T>
-__device__ __forceinline__ int basis(int d, int kind, int k1, int k2, int k3, T t[2][3]) {
-    // straight-line code (selects, no branches): written per branch, the
-    // compiler keeps the partially written rows of t on the stack
-    // |k|^2 and |k x e_j|^2 are exact integers; rsqrt (reciprocal square
-    // root, within a few ulp) replaces a square root and a division, and the
-    // second one is only formed for the 3D dual (kind is uniform per launch)
-    const T a = T(k1), b = T(k2), c = T(d == 3 ? k3 : 0);
-    const T nn = a * a + b * b + c * c;
-    const T inv = nn == T(0) ? T(0) : rsqrt(nn);
-    const T h1 = a * inv, h2 = b * inv, h3 = c * inv;
-    const int ab1 = k1 < 0 ? -k1 : k1, ab2 = k2 < 0 ? -k2 : k2, ab3 = k3 < 0 ? -k3 : k3;
-    const bool x1 = ab1 <= ab2 && ab1 <= ab3;  // k x e_1
-    const bool x2 = !x1 && ab2 <= ab3;         // k x e_2, else k x e_3
-    T u1 = x1 ? T(0) : x2 ? -c : b;
-    T u2 = x1 ? c : x2 ? T(0) : -a;
-    T u3 = x1 ? -b : x2 ? a : T(0);
-    const bool primal = kind == KIND_E, two = d == 2;
-    T un = T(0);
-    if (!primal && !two) {
-        const T uu = u1 * u1 + u2 * u2 + u3 * u3;
-        un = uu == T(0) ? T(0) : rsqrt(uu);
-    }
-    u1 *= un;
-    u2 *= un;
-    u3 *= un;
-    const T s = (k1 != 0) ? (k1 > 0 ? T(1) : T(-1)) : (k2 != 0) ? (k2 > 0 ? T(1) : T(-1)) : (k3 > 0 ? T(1) : T(-1));
-    t[0][0] = primal ? h1 : two ? -h2 : u1;
-    t[0][1] = primal ? h2 : two ? h1 : u2;
-    t[0][2] = primal ? h3 : two ? T(0) : u3;
-    t[1][0] = s * (h2 * u3 - h3 * u2);
-    t[1][1] = s * (h3 * u1 - h1 * u3);
-    t[1][2] = s * (h1 * u2 - h2 * u1);
-    return nn == T(0) ? 0 : (primal || two) ? 1 : 2;
-}
-
-// exp(-i pi sum_a s_a k_a / N_a) of the shift s (S(s) of Lemma reduce_grid);
-// 1 when no shift is set.
-__device__ __forceinline__ void shift_phase(const PencilArgs &a, int k1, int k2, int k3, double *c, double *s) {
-    const double x = (a.shift[0] ? (double)k1 / a.Nfull[0] : 0.0) + (a.shift[1] ? (double)k2 / a.Nfull[1] : 0.0) +
-                     (a.shift[2] ? (double)k3 / a.Nfull[2] : 0.0);
-    sincospi(-x, s, c);
-}
-__device__ __forceinline__ bool has_shift(const PencilArgs &a) { return (a.shift[0] | a.shift[1] | a.shift[2]) != 0; }
-
-__device__ __forceinline__ double sinc_pi(double x) {
-    return x == 0.0 ? 1.0 : sinpi(x) / (M_PI * x);
 }
 
 // ---------------------------------------------------------------------------
@@ -868,20 +532,6 @@ __global__ __launch_bounds__(kThreads) void fold_series_kernel(double2 *out, con
                 }
         out[idx] = make_double2(re, im);
     }
-}
-
-// Symmetric material matrix at linear grid point pt from d (d + 1) / 2 fields
-// (entries 11, 12, [13,] 22, [23,] 33; field f at g + f * stride).
-template <typename T>
-__device__ __forceinline__ void sym_load(const T *g, long stride, long pt, int d, T *m) {
-    int f = 0;
-    for (int i = 0; i < d; ++i)
-        for (int j = i; j < d; ++j) {
-            const T v = g[(long)f * stride + pt];
-            m[i * d + j] = v;
-            m[j * d + i] = v;
-            ++f;
-        }
 }
 
 // ---------------------------------------------------------------------------
@@ -1489,1583 +1139,6 @@ __global__ __launch_bounds__(kThreads) void incl_coeff_kernel(double2 *out, int 
     }
 }
 
-
-// ---------------------------------------------------------------------------
-// Specialised transforms for the grid sizes in kFastSched: compile-time
-// schedules with composite radices done in registers (Cooley-Tukey with
-// constant internal twiddles), in-place stages staged through registers (one
-// LDS buffer), and all d components of a batch transformed together.
-// ---------------------------------------------------------------------------
-// One in-place Stockham stage over NB transforms of length N: every thread
-// first loads all inputs of its butterflies into registers, then (after a
-// barrier) twiddles, transforms and stores them.  Column layout (ROWL false)
-// with NA < NB: only the NA transforms 0 .. (NA - 1) / 2 and NB - NA / 2 ..
-// NB - 1 (the non-zero frequencies of a zero-padded axis) are done.
-template <typename T, int R, int N, int P, int NB, bool ROWL, int NT = kThreads, int NA = NB>
-__device__ __forceinline__ void stage_ip(Vt<T> *X, const Vt<T> *__restrict__ tw, T sg) {
-    constexpr int TQ = N / R;
-    constexpr int NT_ = ROWL ? NB : NA;  // transforms done
-    constexpr int TOT = TQ * NT_;
-    constexpr int PER = (TOT + NT - 1) / NT;
-    auto colmap = [](int c) { return c < (NA + 1) / 2 ? c : c + (NB - NA); };
-    Vt<T> u[PER][R];
-#pragma unroll
-    for (int t = 0; t < PER; ++t) {
-        const int idx = threadIdx.x + t * NT;
-        if (PER * NT == TOT || idx < TOT) {
-            const int b = ROWL ? idx / TQ : colmap(idx % NA);
-            const int i = ROWL ? idx % TQ : idx / NA;
-#pragma unroll
-            for (int q = 0; q < R; ++q) {
-                const int pos = i + q * TQ;
-                u[t][q] = ROWL ? X[b * N + pos] : X[pos * NB + b];
-            }
-        }
-    }
-    __syncthreads();
-#pragma unroll
-    for (int t = 0; t < PER; ++t) {
-        const int idx = threadIdx.x + t * NT;
-        if (PER * NT == TOT || idx < TOT) {
-            const int b = ROWL ? idx / TQ : colmap(idx % NA);
-            const int i = ROWL ? idx % TQ : idx / NA;
-            const int k = i % P;
-            if constexpr (P > 1) {
-#pragma unroll
-                for (int q = 1; q < R; ++q) {
-                    Vt<T> w = tw[(q - 1) * P + k];
-                    w.y *= -sg;
-                    u[t][q] = cmul(u[t][q], w);
-                }
-            }
-            dftn<T, R>(u[t], sg);
-            const int j = (i - k) * R + k;
-#pragma unroll
-            for (int q = 0; q < R; ++q) {
-                const int pos = j + q * P;
-                if (ROWL)
-                    X[b * N + pos] = u[t][q];
-                else
-                    X[pos * NB + b] = u[t][q];
-            }
-        }
-    }
-    __syncthreads();
-}
-
-template <typename T, int FI, int S, int P, int OFF, int NB, bool ROWL, int NT = kThreads, int NA = NB>
-__device__ __forceinline__ void fft_ip(Vt<T> *X, const Vt<T> *tw, T sg) {
-    if constexpr (S < kFastSched[FI].nst) {
-        constexpr int R = kFastSched[FI].r[S];
-        stage_ip<T, R, kFastSched[FI].n, P, NB, ROWL, NT, NA>(X, tw + OFF, sg);
-        fft_ip<T, FI, S + 1, P * R, OFF + (R - 1) * P, NB, ROWL, NT, NA>(X, tw, sg);
-    }
-}
-
-
-// Copy the n - 1 twiddles of a specialised transform into LDS (read by every
-// stage; a global read per butterfly twiddle would stall each stage).
-// Only short tables are staged: for n = 2025 the table (32 KB in FP64) would
-// cost more occupancy than its reads cost latency.
-constexpr bool tw_in_lds(int n, int es) { return n * es <= 12 * 1024; }
-constexpr size_t tw_lds_entries(int n, int es) { return tw_in_lds(n, es) ? (size_t)n : 0; }
-template <typename T, int N, int NTH = kThreads>
-__device__ __forceinline__ const Vt<T> *twiddles_to_lds(Vt<T> *dst, const Vt<T> *__restrict__ src) {
-    if constexpr (!tw_in_lds(N, sizeof(Vt<T>))) {
-        return src;
-    } else {
-        for (int i = threadIdx.x; i < N - 1; i += NTH) dst[i] = src[i];
-        return dst;
-    }
-}
-
-// row pairs per work-group of the specialised anisotropic row pass so that
-// one batch of all d components stays within 24 KB of LDS (the passes are
-// latency-bound: smaller work-groups put more of them on a CU)
-constexpr int fast_batch(int n, int es, int d) {
-    const int cap = 24 * 1024;
-    int b = 16;
-    while (b > 1 && d * b * n * es > cap) b /= 2;
-    return b;
-}
-
-// pencils per work-group of the specialised strided-axis pass: one batch of
-// all d components within 24 KB of LDS, or 48 KB for 3D FP64 transforms of
-// more than 225 points, where the larger batch keeps more of the work-group
-// busy in the butterfly stages; elsewhere (2D, shorter 3D transforms) the
-// smaller work-groups, more of them per CU, measured faster.  The 3D
-// transforms of 225 points (order 113) take tiles sized to the rounds of
-// resident work-groups, set by the axis-1 passes and their 113 x 57 pencils:
-// in FP32, 9 pencils (50 KB of LDS, three work-groups per CU) make 716
-// tiles, one round of the 768 work-groups that fit at once; in FP64 (twice
-// the bytes, more than all LDS of the chip holds) 7 pencils (79 KB, two per
-// CU) make 921 tiles, under two rounds of 512.  The 2D FP32 transforms of 729
-// points (order 365) take 3 pencils with 512 threads (486 of the 2 x 3 x 81
-// radix-9 butterflies busy in one round, against two rounds for 2 pencils and
-// 256 threads): a batch of 16 such solves 7 % faster.
-constexpr int pencil_batch(int n, int es, int d) {
-    if (d == 3 && n == 225) return es >= 16 ? 7 : 9;
-    if (es < 16 && d == 2 && n == 729) return 3;
-    const int cap = (es >= 16 && d == 3 && n > 225) ? 48 * 1024 : 24 * 1024;
-    int b = 16;
-    while (b > 1 && d * b * n * es > cap) b /= 2;
-    return b;
-}
-
-// Problem owning this work-group in a multi-problem launch (binary search of
-// the work-group offsets); *lb receives the problem-local work-group index.
-// Work-groups are dispatched to the 8 XCDs round-robin (physical index mod 8);
-// each XCD has its own L2.  Map the physical index to a logical one so that
-// every XCD receives a contiguous range of logical tiles: neighbouring tiles
-// (which share 128-byte lines of the strided operands) then meet in one L2.
-constexpr int kXcds = 8;
-__device__ __forceinline__ int xcd_logical(int b, int total) {
-    const int q = total / kXcds, r = total % kXcds;
-    const int x = b % kXcds, k = b / kXcds;
-    return x < r ? x * (q + 1) + k : r * (q + 1) + (x - r) * q + k;
-}
-
-__device__ __forceinline__ int find_problem(const int *__restrict__ woff, int np, int *lb) {
-    int lo = 0, hi = np - 1;
-    const int bx = xcd_logical(blockIdx.x, gridDim.x);
-    while (lo < hi) {
-        const int mid = (lo + hi + 1) >> 1;
-        if (woff[mid] <= bx)
-            lo = mid;
-        else
-            hi = mid - 1;
-    }
-    *lb = bx - woff[lo];
-    return lo;
-}
-
-// threads of the specialised strided-axis pass: 512 for the 2D FP64 pencils
-// of 2025 points (one pencil of both components per work-group), the 2D FP32
-// tiles of 729 points and the 3D tiles of 225 points (315 or 405 transforms of
-// 15 points per stage), so that every stage of the transform takes one round
-// of the threads; else 256
-constexpr int pencil_nt(int n, int es, int d) {
-    return ((es >= 16 && d == 2 && n >= 2025) || (es < 16 && d == 2 && n == 729) || (d == 3 && n == 225))
-               ? 512
-               : kThreads;
-}
-
-template <typename T, int FI, int D>
-__global__ __launch_bounds__(pencil_nt(kFastSched[FI].n, sizeof(Vt<T>), D))
-void pencil_fast(const PencilArgs *__restrict__ pa, const int *__restrict__ woff, int np) {
-    using V = Vt<T>;
-    constexpr int N = kFastSched[FI].n;
-    constexpr int NT = pencil_nt(N, sizeof(V), D);
-    constexpr int B = pencil_batch(N, sizeof(V), D);
-    constexpr int NB = D * B;  // LDS layout [pos][component][batch]
-    constexpr int LPI = NT / NB;  // positions per step of the plain prologue / epilogue
-    int lb;
-    const PencilArgs &a = pa[find_problem(woff, np, &lb)];
-    if (a.status != nullptr && a.status->done) return;
-    // loads of a starting work-group before the stages of running ones (the
-    // priority drops again once the batch is in LDS)
-    __builtin_amdgcn_s_setprio(3);
-    extern __shared__ __align__(16) unsigned char smem_raw[];  // 16-byte complex doubles
-    V *X = reinterpret_cast<V *>(smem_raw);
-    const int gx = (a.nb + B - 1) / B;
-    const int o = lb / gx;
-    const int b0 = (lb - o * gx) * B;
-    const int nbw = min(B, a.nb - b0);
-    const V *tw = twiddles_to_lds<T, N, NT>(X + N * NB, reinterpret_cast<const V *>(a.tw) + a.f.twoff[0]);
-    const T sg = T(a.sgn);
-    const T scale = T(a.scale);
-    const V zero = mk<T>(T(0), T(0));
-    // pencil b0 + bb sits at (b0 + bb) / Nh, (b0 + bb) % Nh: one division per
-    // work-group, then at most one carry per pencil (B <= Nh is not assumed)
-    const int q0 = b0 / a.Nh, r0 = b0 - q0 * a.Nh;
-    auto split = [&](int bb, int *qb, int *rb) {
-        int r = r0 + bb, q = q0;
-        while (r >= a.Nh) {
-            r -= a.Nh;
-            ++q;
-        }
-        *qb = q;
-        *rb = r;
-    };
-    auto freq = [&](int l, int L, int bb, int *k1, int *k2, int *k3) {
-        *k1 = wrapi(l, L);
-        int qb, rb;
-        split(bb, &qb, &rb);
-        if (D == 3) {
-            *k2 = wrapi(qb, a.Nmid);
-            *k3 = rb;
-        } else {
-            *k2 = rb;
-            *k3 = 0;
-        }
-    };
-    // Global loads of a phase are issued together (branch-free, with idle
-    // slots reading an in-range address) into scalar register arrays, then
-    // written to LDS.  The input frequencies k in [-(L_in / 2), khi) sit at
-    // positions 0 .. khi - 1 and N - L_in / 2 .. N - 1, so the positions
-    // khi .. khi + N - L_in - 1 form one contiguous zero band of the LDS batch,
-    // written by a loop of its own; slots of idle pencils in the input range
-    // are written as zeros by the loading threads.  The trip counts are
-    // compile-time bounds: inputs of at most (N + 1) / 2 points (zero-padded
-    // transforms) or of N points.
-    const int khi = (a.L_in + 1) / 2;
-    if (a.pro == PRO_EXPAND) {
-      // the CG vectors hold at most (N + 1) / 2 frequencies per axis (Ga), or N
-      // (GaNi, transforms on the grid of the approximation order itself)
-      auto expand = [&](auto cap) {
-        constexpr int PE = (decltype(cap)::value * B + NT - 1) / NT;
-        const auto *sr = gbl(reinterpret_cast<const V *>(a.st_r));
-        auto *sp = gbl(reinterpret_cast<V *>(a.st_p));
-        const auto *sx = gbl(reinterpret_cast<const V *>(a.st_x));
-        const T beta = (a.update_p && a.status) ? T(a.status->beta) : T(0);
-        T ax[PE][2], ay[PE][2], bx[PE][2], by[PE][2];
-#pragma unroll
-        for (int t = 0; t < PE; ++t) {
-            const int idx = threadIdx.x + t * NT;
-            const int bb = idx % B;
-            const int l = idx / B;
-            const bool ok = idx < a.L_in * B && bb < nbw;
-            const long off = ok ? (long)l * a.in_ls + b0 + bb : (long)b0;
-#pragma unroll
-            for (int c = 0; c < 2; ++c) {
-                const long o2 = (c < a.nc ? c : 0) * a.st_cs + off;
-                const V va = a.update_p ? gld(sr + o2) : gld(sx + o2);
-                const V vb = a.update_p ? gld(sp + o2) : zero;
-                ax[t][c] = va.x;
-                ay[t][c] = va.y;
-                bx[t][c] = vb.x;
-                by[t][c] = vb.y;
-            }
-        }
-        for (int idx = threadIdx.x; idx < (N - a.L_in) * NB; idx += NT) X[khi * NB + idx] = zero;
-#pragma unroll
-        for (int t = 0; t < PE; ++t) {
-            const int idx = threadIdx.x + t * NT;
-            const int bb = idx % B;
-            const int l = idx / B;
-            if (idx >= a.L_in * B) continue;
-            if (bb >= nbw) {  // idle pencil of a ragged tile
-                const int pos = posmod(wrapi(l, a.L_in), N);
-#pragma unroll
-                for (int al = 0; al < D; ++al) X[pos * NB + al * B + bb] = zero;
-                continue;
-            }
-            int k1, k2, k3;
-            freq(l, a.L_in, bb, &k1, &k2, &k3);
-            T tb[2][3];
-            const int nt = basis<T>(D, a.kind, k1, k2, k3, tb);
-            V v[2];
-#pragma unroll
-            for (int c = 0; c < 2; ++c) {
-                v[c] = zero;
-                if (c < a.nc) {
-                    if (a.update_p) {
-                        v[c] = mk<T>(ax[t][c] + beta * bx[t][c], ay[t][c] + beta * by[t][c]);
-                        gst(sp + c * a.st_cs + (long)l * a.in_ls + b0 + bb, v[c]);
-                    } else {
-                        v[c] = mk<T>(ax[t][c], ay[t][c]);
-                    }
-                }
-            }
-            const int pos = posmod(k1, N);
-            double pc = 1.0, ps = 0.0;
-            if (has_shift(a)) shift_phase(a, k1, k2, k3, &pc, &ps);
-#pragma unroll
-            for (int al = 0; al < D; ++al) {
-                T ex = T(0), ey = T(0);
-#pragma unroll
-                for (int c = 0; c < 2; ++c) {
-                    if (c < nt) {
-                        ex -= tb[c][al] * v[c].y;
-                        ey += tb[c][al] * v[c].x;
-                    }
-                }
-                if (has_shift(a)) {
-                    const T nx = ex * T(pc) - ey * T(ps);
-                    ey = ex * T(ps) + ey * T(pc);
-                    ex = nx;
-                }
-                X[pos * NB + al * B + bb] = mk<T>(ex, ey);
-            }
-        }
-      };
-      if (2 * a.L_in <= N + 1)
-          expand(std::integral_constant<int, (N + 1) / 2>{});
-      else
-          expand(std::integral_constant<int, N>{});
-    } else {
-        // every thread owns one LDS slot rr (component c, pencil bb) of LPI
-        // positions per step, so its addresses advance by a constant stride;
-        // slots of idle pencils in the input range are written as zeros, the
-        // zero band outside it by a loop over the band alone
-        const int rr = threadIdx.x % NB;
-        const int l0 = threadIdx.x / NB;
-        const bool act = threadIdx.x < LPI * NB;
-        const int c = rr / B;
-        const int bb = rr - c * B;
-        const auto *in = gbl(reinterpret_cast<const V *>(a.in) + (long)o * a.in_os + b0 + (long)c * a.in_cs + bb);
-        auto load = [&](auto cap) {
-            constexpr int P = (decltype(cap)::value + LPI - 1) / LPI;
-            T vx[P], vy[P];
-#pragma unroll
-            for (int t = 0; t < P; ++t) {
-                const int l = l0 + t * LPI;
-                const bool ok = act && l < a.L_in && bb < nbw;
-                const V v = gld(in + (ok ? (long)l * a.in_ls : 0L));
-                vx[t] = ok ? v.x : T(0);
-                vy[t] = ok ? v.y : T(0);
-            }
-            const int nz = N - a.L_in;  // zero band: positions khi .. khi + nz - 1
-            for (int l = l0; act && l < nz; l += LPI) X[(khi + l) * NB + rr] = zero;
-#pragma unroll
-            for (int t = 0; t < P; ++t) {
-                const int l = l0 + t * LPI;
-                if (act && l < a.L_in) X[posmod(wrapi(l, a.L_in), N) * NB + rr] = mk<T>(vx[t], vy[t]);
-            }
-        };
-        if (2 * a.L_in <= N + 1)
-            load(std::integral_constant<int, (N + 1) / 2>{});
-        else
-            load(std::integral_constant<int, N>{});
-    }
-    __syncthreads();
-    __builtin_amdgcn_s_setprio(0);
-    fft_ip<T, FI, 0, 1, 0, NB, false, NT>(X, tw, sg);
-    auto *out = gbl(reinterpret_cast<V *>(a.out));
-    if (a.epi == EPI_PROJECT) {
-      // the projected vector holds at most (N + 1) / 2 frequencies per axis (Ga) or N (GaNi)
-      auto project = [&](auto cap) -> double {
-        constexpr int PE = (decltype(cap)::value * B + NT - 1) / NT;
-        const auto *dv = gbl(reinterpret_cast<const V *>(a.st_dot));
-        T dx[PE][2], dy[PE][2];
-        if (a.st_dot != nullptr) {
-#pragma unroll
-            for (int t = 0; t < PE; ++t) {
-                const int idx = threadIdx.x + t * NT;
-                const int bb = idx % B;
-                const int l = idx / B;
-                const bool ok = idx < a.L_out * B && bb < nbw;
-                const long off = ok ? (long)l * a.out_ls + b0 + bb : (long)b0;
-#pragma unroll
-                for (int c = 0; c < 2; ++c) {
-                    const V v = gld(dv + (c < a.nc ? c : 0) * a.out_cs + off);
-                    dx[t][c] = v.x;
-                    dy[t][c] = v.y;
-                }
-            }
-        }
-        double part = 0.0;
-#pragma unroll
-        for (int t = 0; t < PE; ++t) {
-            const int idx = threadIdx.x + t * NT;
-            const int bb = idx % B;
-            const int l = idx / B;
-            if (idx >= a.L_out * B || bb >= nbw) continue;
-            int k1, k2, k3;
-            freq(l, a.L_out, bb, &k1, &k2, &k3);
-            T tb[2][3];
-            const int nt = basis<T>(D, a.kind, k1, k2, k3, tb);
-            const int pos = posmod(k1, N);
-            V y[D];
-#pragma unroll
-            for (int al = 0; al < D; ++al) y[al] = X[pos * NB + al * B + bb];
-            const double w = (D == 3 ? k3 : k2) == 0 ? 1.0 : 2.0;  // half spectrum: k_d > 0 counts twice
-            double pc = 1.0, ps = 0.0;
-            if (has_shift(a)) shift_phase(a, k1, k2, k3, &pc, &ps);
-#pragma unroll
-            for (int c = 0; c < 2; ++c) {
-                if (c < a.nc) {
-                    T qx = T(0), qy = T(0);
-                    if (c < nt) {
-#pragma unroll
-                        for (int al = 0; al < D; ++al) {
-                            const T tt = tb[c][al] * scale;
-                            qx += tt * y[al].y;
-                            qy -= tt * y[al].x;
-                        }
-                    }
-                    const long off = c * a.out_cs + (long)l * a.out_ls + b0 + bb;
-                    if (has_shift(a)) {  // S*(s): the conjugate phase
-                        const T nx = qx * T(pc) + qy * T(ps);
-                        qy = qy * T(pc) - qx * T(ps);
-                        qx = nx;
-                    }
-                    if (a.accumulate) {
-                        const V old = gld(out + off);
-                        qx += old.x;
-                        qy += old.y;
-                    }
-                    gst(out + off, mk<T>(qx, qy));
-                    if (a.st_dot != nullptr) {
-                        part += w * ((double)dx[t][c] * (double)qx + (double)dy[t][c] * (double)qy);
-                    } else {
-                        part += w * ((double)qx * (double)qx + (double)qy * (double)qy);
-                    }
-                }
-            }
-        }
-        return part;
-      };
-      const double part = (2 * a.L_out <= N + 1) ? project(std::integral_constant<int, (N + 1) / 2>{})
-                                                 : project(std::integral_constant<int, N>{});
-        const double s = block_sum_t<NT>(part);
-        if (threadIdx.x == 0) a.partial[lb] = s;
-    } else {
-        const int rr = threadIdx.x % NB;
-        const int c = rr / B;
-        const int bb = rr - c * B;
-        if (threadIdx.x < LPI * NB && bb < nbw) {
-            auto *ob = out + (long)c * a.out_cs + (long)o * a.out_os + b0 + bb;
-            for (int l = threadIdx.x / NB; l < a.L_out; l += LPI) {
-                V v = X[posmod(wrapi(l, a.L_out), N) * NB + rr];
-                v.x *= scale;
-                v.y *= scale;
-                gst(ob + (long)l * a.out_ls, v);
-            }
-        }
-    }
-}
-
-template <typename T, int FI, int D>
-__global__ __launch_bounds__(kThreads) void row_fast(const RowArgs *__restrict__ ra, const int *__restrict__ woff,
-                                                     int np) {
-    using V = Vt<T>;
-    constexpr int N = kFastSched[FI].n;
-    constexpr int RP = fast_batch(N, sizeof(V), D);
-    constexpr int NB = D * RP;  // LDS layout [component][row pair][pos]
-    int lb;
-    const RowArgs &a = ra[find_problem(woff, np, &lb)];
-    if (a.status != nullptr && a.status->done) return;
-    extern __shared__ __align__(16) unsigned char smem_raw[];  // 16-byte complex doubles
-    V *X = reinterpret_cast<V *>(smem_raw);
-    const int nh = a.Nh_row;
-    const V *tw = twiddles_to_lds<T, N>(X + N * NB, reinterpret_cast<const V *>(a.tw) + a.f.twoff[0]);
-    V *data = reinterpret_cast<V *>(a.data);
-    const T *g = reinterpret_cast<const T *>(a.g);
-    const int pair0 = lb * RP;
-    const int nvp = min(RP, (a.nrows + 1) / 2 - pair0);
-    const V zero = mk<T>(T(0), T(0));
-    T A0[D * D], Dm[D * D];
-#pragma unroll
-    for (int i = 0; i < D * D; ++i) {
-        A0[i] = T(a.A0[i]);
-        Dm[i] = T(a.D[i]);
-    }
-    // material values of this thread's grid points, loaded before the
-    // transforms so that their latency overlaps them
-    constexpr int MP = (RP * N + kThreads - 1) / kThreads;
-    T gv1[MP], gv2[MP];
-#pragma unroll
-    for (int t = 0; t < MP; ++t) {
-        const int idx = threadIdx.x + t * kThreads;
-        const int j = idx / N;
-        const int x = idx - j * N;
-        gv1[t] = T(0);
-        gv2[t] = T(0);
-        if (idx < RP * N && j < nvp && a.nfield <= 1) {
-            const int r1 = 2 * (pair0 + j);
-            gv1[t] = g[(long)r1 * N + x];
-            if (r1 + 1 < a.nrows) gv2[t] = g[(long)(r1 + 1) * N + x];
-        }
-    }
-    if (a.mode == ROW_OPER) {
-        // both rows of every pair, all loads in flight together (nh <= (N + 1) / 2),
-        // then the packed Hermitian extension; the zero band nh <= x <= N - nh
-        // is written by a disjoint loop
-        constexpr int PLR = (NB * ((N + 1) / 2) + kThreads - 1) / kThreads;
-        const auto *dg = gbl(reinterpret_cast<const V *>(a.data));
-        T p1x[PLR], p1y[PLR], p2x[PLR], p2y[PLR];
-#pragma unroll
-        for (int t = 0; t < PLR; ++t) {
-            const int idx = threadIdx.x + t * kThreads;
-            const int pc = idx / nh;
-            const int kx = idx - pc * nh;
-            const int c = pc / RP;
-            const int j = pc - c * RP;
-            const int r1 = 2 * (pair0 + j);
-            const bool ok = idx < NB * nh && j < nvp;
-            const bool ok2 = ok && r1 + 1 < a.nrows;
-            const long off = ok ? (long)c * a.cs + (long)r1 * nh + kx : 0L;
-            const V u1 = gld(dg + off);
-            const V u2 = gld(dg + (ok2 ? off + nh : off));
-            p1x[t] = u1.x;
-            p1y[t] = u1.y;
-            p2x[t] = ok2 ? u2.x : T(0);
-            p2y[t] = ok2 ? u2.y : T(0);
-        }
-        for (int idx = threadIdx.x; idx < NB * (N - 2 * nh + 1); idx += kThreads) {
-            const int pc = idx / (N - 2 * nh + 1);
-            X[pc * N + nh + (idx - pc * (N - 2 * nh + 1))] = zero;
-        }
-#pragma unroll
-        for (int t = 0; t < PLR; ++t) {
-            const int idx = threadIdx.x + t * kThreads;
-            const int pc = idx / nh;
-            const int kx = idx - pc * nh;
-            if (idx >= NB * nh) continue;
-            const V u1 = mk<T>(p1x[t], p1y[t]);
-            const V u2 = mk<T>(p2x[t], p2y[t]);
-            if (kx == 0) {
-                X[pc * N] = mk<T>(u1.x, u2.x);
-            } else {
-                X[pc * N + kx] = mk<T>(u1.x - u2.y, u1.y + u2.x);
-                X[pc * N + N - kx] = mk<T>(u1.x + u2.y, u2.x - u1.y);
-            }
-        }
-        __syncthreads();
-        fft_ip<T, FI, 0, 1, 0, NB, true>(X, tw, T(1));
-#pragma unroll
-        for (int t = 0; t < MP; ++t) {
-            const int idx = threadIdx.x + t * kThreads;
-            const int j = idx / N;
-            const int x = idx - j * N;
-            if (idx >= RP * N || j >= nvp) continue;
-            V e[D];
-#pragma unroll
-            for (int b = 0; b < D; ++b) e[b] = X[(b * RP + j) * N + x];
-            T m1[D * D], m2[D * D];
-            if (a.nfield > 1) {
-                const int r1 = 2 * (pair0 + j);
-                sym_load<T>(g, a.gstride, (long)r1 * N + x, D, m1);
-                if (r1 + 1 < a.nrows)
-                    sym_load<T>(g, a.gstride, (long)(r1 + 1) * N + x, D, m2);
-                else
-#pragma unroll
-                    for (int i = 0; i < D * D; ++i) m2[i] = T(0);
-            } else {
-                const T g1 = gv1[t];
-                const T g2 = gv2[t];
-#pragma unroll
-                for (int i = 0; i < D * D; ++i) {
-                    m1[i] = A0[i] + g1 * Dm[i];
-                    m2[i] = A0[i] + g2 * Dm[i];
-                }
-            }
-#pragma unroll
-            for (int al = 0; al < D; ++al) {
-                T y1 = T(0), y2 = T(0);
-#pragma unroll
-                for (int b = 0; b < D; ++b) {
-                    y1 += m1[al * D + b] * e[b].x;
-                    y2 += m2[al * D + b] * e[b].y;
-                }
-                X[(al * RP + j) * N + x] = mk<T>(y1, y2);
-            }
-        }
-    } else {  // ROW_RHS: y = A(x) E on both rows, |y|^2 and y.E partial sums
-        double load = 0.0, work = 0.0;
-#pragma unroll
-        for (int t = 0; t < MP; ++t) {
-            const int idx = threadIdx.x + t * kThreads;
-            if (idx >= RP * N) continue;
-            const int j = idx / N;
-            const int x = idx - j * N;
-            V y[D];
-#pragma unroll
-            for (int al = 0; al < D; ++al) y[al] = zero;
-            if (j < nvp) {
-                const int r1 = 2 * (pair0 + j);
-                const int r2 = r1 + 1;
-                const bool v2 = r2 < a.nrows;
-                T m1[D * D], m2[D * D];
-                if (a.nfield > 1) {
-                    sym_load<T>(g, a.gstride, (long)r1 * N + x, D, m1);
-                    if (v2)
-                        sym_load<T>(g, a.gstride, (long)r2 * N + x, D, m2);
-                    else
-#pragma unroll
-                        for (int i = 0; i < D * D; ++i) m2[i] = T(0);
-                } else {
-                    const T g1 = gv1[t];
-                    const T g2 = gv2[t];
-#pragma unroll
-                    for (int i = 0; i < D * D; ++i) {
-                        m1[i] = A0[i] + g1 * Dm[i];
-                        m2[i] = A0[i] + g2 * Dm[i];
-                    }
-                }
-#pragma unroll
-                for (int al = 0; al < D; ++al) {
-                    T y1 = T(0), y2 = T(0);
-#pragma unroll
-                    for (int b = 0; b < D; ++b) {
-                        y1 += m1[al * D + b] * T(a.E[b]);
-                        if (v2) y2 += m2[al * D + b] * T(a.E[b]);
-                    }
-                    y[al] = mk<T>(y1, y2);
-                    load += (double)y1 * y1 + (double)y2 * y2;
-                    work += ((double)y1 + (double)y2) * a.E[al];
-                }
-            }
-#pragma unroll
-            for (int al = 0; al < D; ++al) X[(al * RP + j) * N + x] = y[al];
-        }
-        const double s = block_sum(load);
-        const double s2 = block_sum(work);
-        if (threadIdx.x == 0) {
-            a.partial[lb] = s;
-            if (a.partial2 != nullptr) a.partial2[lb] = s2;
-        }
-    }
-    __syncthreads();
-    fft_ip<T, FI, 0, 1, 0, NB, true>(X, tw, T(-1));
-    const T half = T(a.scale) * T(0.5);
-    for (int idx = threadIdx.x; idx < NB * nh; idx += kThreads) {
-        const int pc = idx / nh;
-        const int kx = idx - pc * nh;
-        const int c = pc / RP;
-        const int j = pc - c * RP;
-        if (j >= nvp) continue;
-        const int r1 = 2 * (pair0 + j);
-        const int r2 = r1 + 1;
-        const V w = X[pc * N + kx];
-        const V wm = X[pc * N + (kx == 0 ? 0 : N - kx)];
-        data[(long)c * a.cs + (long)r1 * nh + kx] = mk<T>((w.x + wm.x) * half, (w.y - wm.y) * half);
-        if (r2 < a.nrows)
-            data[(long)c * a.cs + (long)r2 * nh + kx] = mk<T>((w.y + wm.y) * half, (wm.x - w.x) * half);
-    }
-}
-
-
-// ---------------------------------------------------------------------------
-// Operator row pass for isotropic materials, A(x) = (a0 + g(x) dA) I.  Every
-// component row is multiplied by the same scalar field, so each packed row
-// pair (two real rows as one complex transform) is independent of the others.
-// The first inverse stage reads its points straight from the half-spectrum
-// rows (Hermitian extension and zero padding on the fly); the last inverse
-// stage leaves each thread holding the points x = i + q N/R, where the
-// material multiply is applied and the first forward stage (same radix, same
-// points) follows in registers.  Only the middle stages, the exchanges
-// between stages and the final Hermitian unpacking go through LDS.
-constexpr bool palindromic(int fi) {
-    const int s = kFastSched[fi].nst;
-    for (int i = 0; i < s; ++i)
-        if (kFastSched[fi].r[i] != kFastSched[fi].r[s - 1 - i]) return false;
-    return true;
-}
-constexpr int sched_p(int fi, int st) {
-    int p = 1;
-    for (int i = 0; i < st; ++i) p *= kFastSched[fi].r[i];
-    return p;
-}
-constexpr int sched_off(int fi, int st) {
-    int off = 0, p = 1;
-    for (int i = 0; i < st; ++i) {
-        off += (kFastSched[fi].r[i] - 1) * p;
-        p *= kFastSched[fi].r[i];
-    }
-    return off;
-}
-// transforms per work-group and work-group size: every thread of the first
-// and last stages owns one butterfly of radix r[0]
-constexpr int iso_tb(int fi) {
-    const int tq = kFastSched[fi].n / kFastSched[fi].r[0];
-    // transforms of more than 128 butterflies per stage (n = 2025): one per
-    // work-group, so that several share a CU
-    return tq <= 64 ? 128 / tq : (tq <= 128 ? 256 / tq : 1);
-}
-constexpr int iso_nt(int fi) {
-    const int tq = kFastSched[fi].n / kFastSched[fi].r[0];
-    return (iso_tb(fi) * tq + 63) / 64 * 64;
-}
-
-template <typename T, int FI, int S, int SEND, int NB, int NT>
-__device__ __forceinline__ void fft_mid(Vt<T> *X, const Vt<T> *tw, T sg) {
-    if constexpr (S < SEND) {
-        stage_ip<T, kFastSched[FI].r[S], kFastSched[FI].n, sched_p(FI, S), NB, true, NT>(X, tw + sched_off(FI, S),
-                                                                                          sg);
-        fft_mid<T, FI, S + 1, SEND, NB, NT>(X, tw, sg);
-    }
-}
-
-template <typename T, int FI>
-__global__ __launch_bounds__(iso_nt(FI)) __attribute__((amdgpu_waves_per_eu(sizeof(T) == 8 ? 3 : 1)))
-void row_iso_fast(const RowArgs *__restrict__ ra,
-                                                           const int *__restrict__ woff, int np) {
-    using V = Vt<T>;
-    constexpr int N = kFastSched[FI].n;
-    constexpr int S = kFastSched[FI].nst;
-    constexpr int R = kFastSched[FI].r[0];
-    constexpr int TQ = N / R;  // butterflies per transform in the first and last stages
-    constexpr int TB = iso_tb(FI);
-    constexpr int NT = iso_nt(FI);
-    constexpr int OFFL = sched_off(FI, S - 1);  // twiddles of the last stage (P = TQ)
-    static_assert(palindromic(FI) && S >= 2 && sched_p(FI, S - 1) == TQ, "schedule must be palindromic");
-    int lb;
-    const RowArgs &a = ra[find_problem(woff, np, &lb)];
-    if (a.status != nullptr && a.status->done) return;
-    extern __shared__ __align__(16) unsigned char smem_raw[];  // 16-byte complex doubles
-    V *X = reinterpret_cast<V *>(smem_raw);  // [transform][pos]
-    // stage twiddles staged in LDS when short; for the longest rows (2025
-    // points, 32 KB in FP64) the LDS goes to the transforms and the twiddles
-    // are read through the cache
-    const V *twg = reinterpret_cast<const V *>(a.tw) + a.f.twoff[0];
-    const V *tws = twiddles_to_lds<T, N, NT>(X + TB * N, twg);
-    const V zero = mk<T>(T(0), T(0));
-    const int nh = a.Nh_row;
-    const int npairs = (a.nrows + 1) / 2;
-    const int ntr = a.d * npairs;
-    const int tl = threadIdx.x / TQ;
-    const int i = threadIdx.x - tl * TQ;
-    const int tb = lb * TB + tl;
-    const bool act = tl < TB && tb < ntr;
-    // transforms ordered pair-major (components fastest), so that the d
-    // transforms reading one row pair's material values share a work-group
-    int c = 0, r1 = 0;
-    if (act) {
-        const int pr = tb / a.d;
-        c = tb - pr * a.d;
-        r1 = 2 * pr;
-    }
-    const bool v2 = act && r1 + 1 < a.nrows;
-    const V *data = reinterpret_cast<const V *>(a.data);
-    const V *row1 = data + (long)c * a.cs + (long)r1 * nh;
-    const T *g = reinterpret_cast<const T *>(a.g);
-    const T a0 = T(a.A0[0]);
-    const T da = T(a.D[0]);
-    V u[R];
-    {
-        // all loads first (idle points read entry 0 of the pair), then the
-        // Hermitian packing by selects
-        T l1x[R], l1y[R], l2x[R], l2y[R];
-        const auto *rg = gbl(row1);
-#pragma unroll
-        for (int q = 0; q < R; ++q) {
-            const int pos = i + q * TQ;
-            const int kx = pos < nh ? pos : (pos > N - nh ? N - pos : 0);
-            const V a1 = gld(rg + kx);
-            const V a2 = gld(rg + (v2 ? nh + kx : kx));
-            l1x[q] = a1.x;
-            l1y[q] = a1.y;
-            l2x[q] = a2.x;
-            l2y[q] = a2.y;
-        }
-#pragma unroll
-        for (int q = 0; q < R; ++q) {
-            const int pos = i + q * TQ;
-            const V u1 = mk<T>(l1x[q], l1y[q]);
-            const V u2 = v2 ? mk<T>(l2x[q], l2y[q]) : zero;
-            const V lo = pos == 0 ? mk<T>(u1.x, u2.x) : mk<T>(u1.x - u2.y, u1.y + u2.x);
-            const V hi = mk<T>(u1.x + u2.y, u2.x - u1.y);
-            u[q] = !act ? zero : (pos < nh ? lo : (pos > N - nh ? hi : zero));
-        }
-    }
-    // first inverse stage (P = 1): outputs at i R + q
-    dftn<T, R>(u, T(1));
-    if (act) {
-#pragma unroll
-        for (int q = 0; q < R; ++q) X[tl * N + i * R + q] = u[q];
-    }
-    __syncthreads();
-    fft_mid<T, FI, 1, S - 1, TB, NT>(X, tws, T(1));
-    // last inverse stage: inputs and outputs at i + q TQ (own points only)
-    if (act) {
-#pragma unroll
-        for (int q = 0; q < R; ++q) u[q] = X[tl * N + i + q * TQ];
-    }
-    __syncthreads();
-#pragma unroll
-    for (int q = 1; q < R; ++q) {
-        V w = tws[OFFL + (q - 1) * TQ + i];
-        w.y = -w.y;
-        u[q] = cmul(u[q], w);
-    }
-    dftn<T, R>(u, T(1));
-    // the two real rows at x = i + q TQ: multiply by a0 + g da (the material
-    // values are loaded here, not held through the inverse stages; idle lanes
-    // read row r1, in range, and their products are never stored)
-    {
-        const T *gr1 = g + (long)r1 * N + i;
-        const T *gr2 = v2 ? gr1 + N : gr1;
-        T g1[R], g2[R];
-#pragma unroll
-        for (int q = 0; q < R; ++q) {
-            g1[q] = gr1[q * TQ];
-            g2[q] = gr2[q * TQ];
-        }
-#pragma unroll
-        for (int q = 0; q < R; ++q) {
-            u[q].x *= a0 + g1[q] * da;
-            u[q].y *= a0 + g2[q] * da;
-        }
-    }
-    // first forward stage on the same points
-    dftn<T, R>(u, T(-1));
-    if (act) {
-#pragma unroll
-        for (int q = 0; q < R; ++q) X[tl * N + i * R + q] = u[q];
-    }
-    __syncthreads();
-    fft_mid<T, FI, 1, S - 1, TB, NT>(X, tws, T(-1));
-    if (act) {
-#pragma unroll
-        for (int q = 0; q < R; ++q) u[q] = X[tl * N + i + q * TQ];
-#pragma unroll
-        for (int q = 1; q < R; ++q) u[q] = cmul(u[q], tws[OFFL + (q - 1) * TQ + i]);
-        dftn<T, R>(u, T(-1));
-#pragma unroll
-        for (int q = 0; q < R; ++q) X[tl * N + i + q * TQ] = u[q];
-    }
-    __syncthreads();
-    // unpack the two rows of each transform and keep the first nh frequencies
-    V *out = reinterpret_cast<V *>(a.data);
-    const T half = T(a.scale) * T(0.5);
-    for (int o = threadIdx.x; o < TB * nh; o += NT) {
-        const int t = o / nh;
-        const int kx = o - t * nh;
-        const int tbo = lb * TB + t;
-        if (tbo >= ntr) continue;
-        const int po = tbo / a.d;
-        const int co = tbo - po * a.d;
-        const int ro = 2 * po;
-        const V w = X[t * N + kx];
-        const V wm = X[t * N + (kx == 0 ? 0 : N - kx)];
-        V *orow = out + (long)co * a.cs + (long)ro * nh;
-        orow[kx] = mk<T>((w.x + wm.x) * half, (w.y - wm.y) * half);
-        if (ro + 1 < a.nrows) orow[nh + kx] = mk<T>((w.y + wm.y) * half, (wm.x - w.x) * half);
-    }
-}
-
-// Variant for two-stage schedules: every exchange between stages moves the
-// real parts through LDS first and the imaginary parts second, so a transform
-// needs n reals of LDS instead of n complex values; with the material values
-// loaded at the multiply (not held in registers) this raises the resident
-// waves, which hides the latencies of the stages, and each thread unpacks its
-// own points (no index division).
-constexpr int split_tb(int fi) { return iso_tb(fi); }
-constexpr int split_nt(int fi) { return iso_nt(fi); }
-
-template <typename T, int FI>
-__global__ __launch_bounds__(split_nt(FI)) void row_iso_split(const RowArgs *__restrict__ ra,
-                                                             const int *__restrict__ woff, int np) {
-    using V = Vt<T>;
-    constexpr int N = kFastSched[FI].n;
-    constexpr int R = kFastSched[FI].r[0];
-    constexpr int TQ = N / R;
-    constexpr int TB = split_tb(FI);
-    constexpr int NT = split_nt(FI);
-    constexpr int OFFL = sched_off(FI, 1);
-    static_assert(kFastSched[FI].nst == 2 && kFastSched[FI].r[1] == R, "two-stage palindromic schedule");
-    int lb;
-    const RowArgs &a = ra[find_problem(woff, np, &lb)];
-    if (a.status != nullptr && a.status->done) return;
-    extern __shared__ __align__(16) unsigned char smem_raw[];  // 16-byte complex doubles
-    T *Bf = reinterpret_cast<T *>(smem_raw);            // [transform][pos], one part at a time
-    V *tws = reinterpret_cast<V *>(Bf + TB * N);        // last-stage twiddles
-    const V *twg = reinterpret_cast<const V *>(a.tw) + a.f.twoff[0];
-    for (int i = threadIdx.x; i < N - 1; i += NT) tws[i] = twg[i];
-    const V zero = mk<T>(T(0), T(0));
-    const int nh = a.Nh_row;
-    const int npairs = (a.nrows + 1) / 2;
-    const int ntr = a.d * npairs;
-    const int tl = threadIdx.x / TQ;
-    const int i = threadIdx.x - tl * TQ;
-    const int tb = lb * TB + tl;
-    const bool act = tl < TB && tb < ntr;
-    int c = 0, r1 = 0;
-    if (act) {
-        const int pr = tb / a.d;
-        c = tb - pr * a.d;
-        r1 = 2 * pr;
-    }
-    const bool v2 = act && r1 + 1 < a.nrows;
-    V *data = reinterpret_cast<V *>(a.data);
-    V *row1 = data + (long)c * a.cs + (long)r1 * nh;
-    V *row2 = row1 + nh;
-    const T *g = reinterpret_cast<const T *>(a.g);
-    T *Bt = Bf + (act ? tl : 0) * N;
-    // exchange: write own values at positions wp(q), read positions rp(q)
-    auto xchg = [&](V *u, auto wp, auto rp) {
-#pragma unroll
-        for (int q = 0; q < R; ++q)
-            if (act) Bt[wp(q)] = u[q].x;
-        __syncthreads();
-#pragma unroll
-        for (int q = 0; q < R; ++q)
-            if (act) u[q].x = Bt[rp(q)];
-        __syncthreads();
-#pragma unroll
-        for (int q = 0; q < R; ++q)
-            if (act) Bt[wp(q)] = u[q].y;
-        __syncthreads();
-#pragma unroll
-        for (int q = 0; q < R; ++q)
-            if (act) u[q].y = Bt[rp(q)];
-        __syncthreads();
-    };
-    auto stage_out = [&](int q) { return i * R + q; };
-    auto own = [&](int q) { return i + q * TQ; };
-    V u[R];
-    {
-        // loads in two groups (idle points read entry 0 of the pair), each
-        // followed by the Hermitian packing by selects; the empty asm
-        // statements keep the second group from being hoisted, which bounds
-        // the registers the staged values need
-        const auto *rg = gbl(row1);
-        constexpr int LG = (R + 1) / 2;
-#pragma unroll
-        for (int q0 = 0; q0 < R; q0 += LG) {
-            asm volatile("" ::: "memory");
-            T l1x[LG], l1y[LG], l2x[LG], l2y[LG];
-#pragma unroll
-            for (int q = q0; q < q0 + LG && q < R; ++q) {
-                const int pos = i + q * TQ;
-                const int kx = pos < nh ? pos : (pos > N - nh ? N - pos : 0);
-                const V a1 = gld(rg + kx);
-                const V a2 = gld(rg + (v2 ? nh + kx : kx));
-                l1x[q - q0] = a1.x;
-                l1y[q - q0] = a1.y;
-                l2x[q - q0] = a2.x;
-                l2y[q - q0] = a2.y;
-            }
-#pragma unroll
-            for (int q = q0; q < q0 + LG && q < R; ++q) {
-                const int pos = i + q * TQ;
-                const V u1 = mk<T>(l1x[q - q0], l1y[q - q0]);
-                const V u2 = v2 ? mk<T>(l2x[q - q0], l2y[q - q0]) : zero;
-                const V lo = pos == 0 ? mk<T>(u1.x, u2.x) : mk<T>(u1.x - u2.y, u1.y + u2.x);
-                const V hi = mk<T>(u1.x + u2.y, u2.x - u1.y);
-                u[q] = !act ? zero : (pos < nh ? lo : (pos > N - nh ? hi : zero));
-            }
-        }
-        asm volatile("" ::: "memory");
-    }
-    dftn<T, R>(u, T(1));
-    xchg(u, stage_out, own);
-#pragma unroll
-    for (int q = 1; q < R; ++q) {
-        V w = tws[OFFL + (q - 1) * TQ + i];
-        w.y = -w.y;
-        u[q] = cmul(u[q], w);
-    }
-    dftn<T, R>(u, T(1));
-    {
-        // material values in groups of five loads, issued only here (the
-        // empty asm statements keep the compiler from hoisting them over
-        // the transform, where they would hold registers)
-        const T a0 = T(a.A0[0]);
-        const T da = T(a.D[0]);
-        const T *g1 = g + (long)r1 * N + i;
-        const T *g2 = v2 ? g1 + N : g1;
-        constexpr int GQ = 5;
-#pragma unroll
-        for (int q0 = 0; q0 < R; q0 += GQ) {
-            asm volatile("" ::: "memory");
-#pragma unroll
-            for (int q = q0; q < q0 + GQ && q < R; ++q) {
-                const T ga = g1[q * TQ];
-                const T gb = g2[q * TQ];
-                u[q].x *= a0 + ga * da;
-                u[q].y *= a0 + gb * da;
-            }
-        }
-        asm volatile("" ::: "memory");
-    }
-    dftn<T, R>(u, T(-1));
-    xchg(u, stage_out, own);
-#pragma unroll
-    for (int q = 1; q < R; ++q) u[q] = cmul(u[q], tws[OFFL + (q - 1) * TQ + i]);
-    dftn<T, R>(u, T(-1));
-    // Hermitian unpacking: each thread pairs its points p < nh with N - p
-    // (nh <= (N + 1) / 2, so only the first QH of its points are kept)
-    constexpr int QH = ((N + 1) / 2 + TQ - 1) / TQ;
-    V m[QH];
-    auto partner = [&](int q) {
-        const int p = i + q * TQ;
-        return p == 0 ? 0 : N - p;
-    };
-#pragma unroll
-    for (int q = 0; q < R; ++q)
-        if (act) Bt[own(q)] = u[q].x;
-    __syncthreads();
-#pragma unroll
-    for (int q = 0; q < QH; ++q)
-        if (act) m[q].x = Bt[partner(q)];
-    __syncthreads();
-#pragma unroll
-    for (int q = 0; q < R; ++q)
-        if (act) Bt[own(q)] = u[q].y;
-    __syncthreads();
-#pragma unroll
-    for (int q = 0; q < QH; ++q)
-        if (act) m[q].y = Bt[partner(q)];
-    const T half = T(a.scale) * T(0.5);
-#pragma unroll
-    for (int q = 0; q < QH; ++q) {
-        const int p = i + q * TQ;
-        if (act && p < nh) {
-            const V w = u[q];
-            const V wm = m[q];
-            row1[p] = mk<T>((w.x + wm.x) * half, (w.y - wm.y) * half);
-            if (v2) row2[p] = mk<T>((w.y + wm.y) * half, (wm.x - w.x) * half);
-        }
-    }
-}
-
-// Variant for the row lengths of Ga plans (half-spectrum rows of at most
-// (N + 3) / 4 points: order (N + 1) / 2 on the grid N).  Every global load of
-// a work-group -- its half-spectrum rows, the material rows of its pairs and
-// the last-stage twiddles -- is issued at once and parked in LDS, so a
-// work-group waits for memory once.  Work-groups own whole row pairs (all D
-// components of each, pair-major), so each material row is fetched once.
-// Lanes beyond the last transform repeat the work of the last one, and the
-// spare lane of a 16-lane group that of the group's 15th (same inputs, same
-// instructions, so their LDS writes store the values already there) instead
-// of branching around every LDS access; only the final stores are guarded.
-// The transform is that of row_iso_split; per-transform LDS rows are padded
-// so that the stride exchanges of neighbouring transforms fall into
-// different banks.
-constexpr int staged_nhc(int n) { return (n + 3) / 4; }
-// lanes per transform: 15 butterflies get an aligned group of 16 lanes (the
-// last lane repeats the 15th), so that the lanes of one LDS access pass belong
-// to whole transforms
-constexpr int staged_lg(int fi) {
-    const int tq = kFastSched[fi].n / kFastSched[fi].r[0];
-    return tq == 15 ? 16 : tq;
-}
-// threads per work-group: the best lane utilisation of 128, 192 or 256, except
-// for the 3D FP64 rows of 225 points (es: bytes of a complex value), which
-// take 256 (five row pairs, three work-groups per CU): 2 % faster than the
-// 192 of the best utilisation, while in FP32 the two were alike
-constexpr int staged_nt(int fi, int d, int es) {
-    if (es >= 16 && d == 3 && kFastSched[fi].n == 225) return 256;
-    const int tq = kFastSched[fi].n / kFastSched[fi].r[0];
-    int best = 128, bu = 0;  // utilisation in 1/1024
-    for (int nt = 128; nt <= 256; nt += 64) {
-        const int tb = (nt / staged_lg(fi)) / d * d;
-        const int u = tb * tq * 1024 / nt;
-        if (u > bu) {
-            bu = u;
-            best = nt;
-        }
-    }
-    return best;
-}
-constexpr int staged_tb(int fi, int d, int es) { return (staged_nt(fi, d, es) / staged_lg(fi)) / d * d; }
-// LDS row stride of one transform (in reals): 240 = 16 (mod 32) for n = 225
-constexpr int staged_stride(int fi) { return kFastSched[fi].n == 225 ? 240 : kFastSched[fi].n; }
-// twiddles of the second stage: w_n^(q i) at (q - 1) n / r + i (1 <= q < r,
-// 0 <= i < n / r), so that the lanes of a transform read consecutive entries
-constexpr int staged_ntp(int fi) { return (kFastSched[fi].r[0] - 1) * (kFastSched[fi].n / kFastSched[fi].r[0]); }
-template <typename T>
-constexpr size_t staged_lds(int fi, int d) {
-    const int n = kFastSched[fi].n, tb = staged_tb(fi, d, (int)sizeof(Vt<T>));
-    const size_t work = std::max(sizeof(Vt<T>) * tb * 2 * (staged_nhc(n) + 1), sizeof(T) * tb * staged_stride(fi));
-    const size_t gm = sizeof(T) * (tb / d) * 2 * n;
-    return (gm + 15) / 16 * 16 + sizeof(Vt<T>) * staged_ntp(fi) + work;
-}
-
-// three waves per SIMD: what the LDS of four 192-thread or three 256-thread
-// work-groups per CU allows in FP64
-template <typename T, int FI, int D>
-__global__ __launch_bounds__(staged_nt(FI, D, sizeof(Vt<T>))) __attribute__((amdgpu_waves_per_eu(sizeof(T) == 8 ? 3 : 1)))
-void row_iso_staged(const RowArgs *__restrict__ ra,
-                                                                  const int *__restrict__ woff, int np) {
-    using V = Vt<T>;
-    constexpr int N = kFastSched[FI].n;
-    constexpr int R = kFastSched[FI].r[0];
-    constexpr int TQ = N / R;
-    constexpr int TB = staged_tb(FI, D, sizeof(Vt<T>));
-    constexpr int PW = TB / D;  // row pairs per work-group
-    constexpr int NT = staged_nt(FI, D, sizeof(Vt<T>));
-    constexpr int NHC = staged_nhc(N);
-    constexpr int SR = NHC + 1;  // staged row: NHC points and a zero slot
-    constexpr int S = staged_stride(FI);
-    constexpr int NTP = staged_ntp(FI);
-    constexpr int OFFL = sched_off(FI, 1);
-    constexpr int LG = staged_lg(FI);
-    static_assert(kFastSched[FI].nst == 2 && kFastSched[FI].r[1] == R, "two-stage palindromic schedule");
-    static_assert(TB * LG <= NT && TB % D == 0 && NT - TB * LG <= LG && LG >= TQ, "work-group shape");
-    int lb;
-    const RowArgs &a = ra[find_problem(woff, np, &lb)];
-    if (a.status != nullptr && a.status->done) return;
-    extern __shared__ __align__(16) unsigned char smem_raw[];  // 16-byte complex doubles
-    T *Gs = reinterpret_cast<T *>(smem_raw);                                           // [2 PW][N] material
-    V *tp = reinterpret_cast<V *>(smem_raw + (sizeof(T) * PW * 2 * N + 15) / 16 * 16);  // [NTP] stage twiddles
-    V *St = tp + NTP;                      // [D][2 PW][SR] staged half-spectrum rows ...
-    T *Bf = reinterpret_cast<T *>(St);     // ... later [TB][S], one part at a time
-    const int nh = a.Nh_row;
-    const int npairs = (a.nrows + 1) / 2;
-    const int pr0 = lb * PW;
-    const int npr = min(PW, npairs - pr0);
-    const int nrow_wg = min(2 * npr, a.nrows - 2 * pr0);  // rows of this work-group
-    // ---- all global loads in flight together, then parked in LDS; the waves
-    // of a work-group issuing its loads take priority over those already in
-    // the transform arithmetic, so that a new work-group's loads leave early
-    __builtin_amdgcn_s_setprio(3);
-    constexpr int GP = (PW * 2 * N + NT - 1) / NT;
-    constexpr int RS = 2 * PW * SR;  // staged slots of one component: its 2 PW rows
-    constexpr int SPC = (RS + NT - 1) / NT;
-    constexpr int NW = (R - 1) * TQ;  // stage-1 twiddles
-    constexpr int WP = (NW + NT - 1) / NT;
-    const auto *gsrc = gbl(reinterpret_cast<const T *>(a.g) + (long)2 * pr0 * N);
-    const auto *dsrc = gbl(reinterpret_cast<const V *>(a.data));
-    const auto *twg = gbl(reinterpret_cast<const V *>(a.tw) + a.f.twoff[0] + OFFL);
-    const int gcnt = nrow_wg * N;
-    T gv[GP];
-    T sx[D][SPC], sy[D][SPC];
-    T wx[WP], wy[WP];
-#pragma unroll
-    for (int t = 0; t < GP; ++t) {
-        const int idx = threadIdx.x + t * NT;
-        gv[t] = gsrc[idx < gcnt ? idx : 0];
-    }
-    // the rows of a work-group are contiguous in each component: one flat
-    // copy per component into slots [c][row][SR] (slot k >= nh and rows past
-    // the last are zero), with the offsets of a component in 32 bits
-#pragma unroll
-    for (int c = 0; c < D; ++c) {
-        const auto *dc = dsrc + (long)c * a.cs + (long)2 * pr0 * nh;
-#pragma unroll
-        for (int t = 0; t < SPC; ++t) {
-            const int f = threadIdx.x + t * NT;
-            const int row = f / SR;
-            const int k = f - row * SR;
-            const bool ok = f < RS && k < nh && row < nrow_wg;
-            const V v = gld(dc + (ok ? row * nh + k : 0));
-            sx[c][t] = ok ? v.x : T(0);
-            sy[c][t] = ok ? v.y : T(0);
-        }
-    }
-#pragma unroll
-    for (int t = 0; t < WP; ++t) {
-        const int idx = threadIdx.x + t * NT;
-        const V v = gld(twg + (idx < NW ? idx : 0));
-        wx[t] = v.x;
-        wy[t] = v.y;
-    }
-#pragma unroll
-    for (int t = 0; t < GP; ++t) {
-        const int idx = threadIdx.x + t * NT;
-        if (idx < PW * 2 * N) Gs[idx] = idx < gcnt ? gv[t] : T(0);
-    }
-#pragma unroll
-    for (int c = 0; c < D; ++c) {
-#pragma unroll
-        for (int t = 0; t < SPC; ++t) {
-            const int f = threadIdx.x + t * NT;
-            if (f < RS) St[c * RS + f] = mk<T>(sx[c][t], sy[c][t]);
-        }
-    }
-#pragma unroll
-    for (int t = 0; t < WP; ++t) {
-        const int idx = threadIdx.x + t * NT;
-        if (idx < NW) tp[idx] = mk<T>(wx[t], wy[t]);
-    }
-    __syncthreads();
-    __builtin_amdgcn_s_setprio(0);
-    // ---- packed Hermitian extension of the two rows of this thread's transform
-    const int tr = threadIdx.x / LG;
-    const int lane = threadIdx.x - tr * LG;
-    const int tl = tr < TB ? tr : TB - 1;  // lanes past the last transform repeat it
-    const int i = lane < TQ ? lane : TQ - 1;  // and spare lanes of a group repeat its last
-    const int lp = tl / D;                 // pair within the work-group
-    const int c = tl - lp * D;             // component
-    const bool owner = tr < TB && lane < TQ && lp < npr;
-    // Points i + q TQ of this thread that lie in the zero band for every
-    // thread (NHC <= q TQ and q TQ + TQ - 1 <= N - NHC) are zero on input and
-    // not needed on output: with the band known at compile time the compiler
-    // drops their arithmetic from the first inverse and the last forward stage.
-    auto zband = [](int q) { return q * TQ >= NHC && q * TQ + TQ - 1 <= N - NHC; };
-    V u[R];
-    {
-        const V *s1 = St + c * RS + 2 * lp * SR;
-#pragma unroll
-        for (int q = 0; q < R; ++q) {
-            if (zband(q)) {
-                u[q] = mk<T>(T(0), T(0));
-                continue;
-            }
-            // z = u1 + i u2 at p < nh, conj(u1) + i conj(u2) at p > N - nh,
-            // (u1.x, u2.x) at p = 0, zero between (the zero slot)
-            const int pos = i + q * TQ;
-            const bool low = pos < nh;
-            const int kx = low ? pos : (pos > N - nh ? N - pos : NHC);
-            const V u1 = s1[kx];
-            const V u2 = s1[SR + kx];
-            const T sg = low ? (pos == 0 ? T(0) : T(1)) : T(-1);
-            u[q] = mk<T>(u1.x - sg * u2.y, u2.x + sg * u1.y);
-        }
-    }
-    __syncthreads();  // St is reused as Bf
-    T *Bt = Bf + tl * S;
-    auto xchg = [&](V *w, auto wp, auto rp) {
-#pragma unroll
-        for (int q = 0; q < R; ++q) Bt[wp(q)] = w[q].x;
-        __syncthreads();
-#pragma unroll
-        for (int q = 0; q < R; ++q) w[q].x = Bt[rp(q)];
-        __syncthreads();
-#pragma unroll
-        for (int q = 0; q < R; ++q) Bt[wp(q)] = w[q].y;
-        __syncthreads();
-#pragma unroll
-        for (int q = 0; q < R; ++q) w[q].y = Bt[rp(q)];
-        __syncthreads();
-    };
-    auto stage_out = [&](int q) { return i * R + q; };
-    auto own = [&](int q) { return i + q * TQ; };
-    dftn<T, R>(u, T(1));
-    xchg(u, stage_out, own);
-#pragma unroll
-    for (int q = 1; q < R; ++q) {
-        V w = tp[(q - 1) * TQ + i];
-        w.y = -w.y;
-        u[q] = cmul(u[q], w);
-    }
-    dftn<T, R>(u, T(1));
-    {
-        const T a0 = T(a.A0[0]);
-        const T da = T(a.D[0]);
-        const T *g1 = Gs + 2 * lp * N + i;
-#pragma unroll
-        for (int q = 0; q < R; ++q) {
-            u[q].x *= a0 + g1[q * TQ] * da;
-            u[q].y *= a0 + g1[N + q * TQ] * da;
-        }
-    }
-    dftn<T, R>(u, T(-1));
-    xchg(u, stage_out, own);
-#pragma unroll
-    for (int q = 1; q < R; ++q) u[q] = cmul(u[q], tp[(q - 1) * TQ + i]);
-    dftn<T, R>(u, T(-1));
-    // Hermitian unpacking: outputs p < nh <= NHC pair with N - p > N - NHC,
-    // so only the points that can lie there go through LDS
-    constexpr int QH = (NHC + TQ - 1) / TQ;
-    V m[QH];
-    auto partner = [&](int q) {
-        const int p = i + q * TQ;
-        return p == 0 ? 0 : N - p;
-    };
-    auto high = [](int q) { return q * TQ + TQ - 1 > N - NHC; };
-#pragma unroll
-    for (int q = 0; q < R; ++q)
-        if (high(q)) Bt[own(q)] = u[q].x;
-    Bt[own(0)] = u[0].x;  // p = 0 pairs with itself
-    __syncthreads();
-#pragma unroll
-    for (int q = 0; q < QH; ++q) m[q].x = Bt[partner(q)];
-    __syncthreads();
-#pragma unroll
-    for (int q = 0; q < R; ++q)
-        if (high(q)) Bt[own(q)] = u[q].y;
-    Bt[own(0)] = u[0].y;
-    __syncthreads();
-#pragma unroll
-    for (int q = 0; q < QH; ++q) m[q].y = Bt[partner(q)];
-    if (!owner) return;
-    const int r1 = 2 * (pr0 + lp);
-    const bool v2 = 2 * lp + 1 < nrow_wg;
-    auto *row1 = gbl(reinterpret_cast<V *>(a.data) + (long)c * a.cs + (long)r1 * nh);
-    const T half = T(a.scale) * T(0.5);
-#pragma unroll
-    for (int q = 0; q < QH; ++q) {
-        const int p = i + q * TQ;
-        if (p < nh) {
-            const V w = u[q];
-            const V wm = m[q];
-            gst(row1 + p, mk<T>((w.x + wm.x) * half, (w.y - wm.y) * half));
-            if (v2) gst(row1 + nh + p, mk<T>((w.y + wm.y) * half, (wm.x - w.x) * half));
-        }
-    }
-}
-
-// Launch target of the specialised kernels: the stream and, for timing, the
-// events the dispatch records at its own start and end.
-struct Disp {
-    hipStream_t s;
-    LaunchEv ev;
-    Disp(hipStream_t st, LaunchEv e = LaunchEv{}) : s(st), ev(e) {}
-};
-template <typename... KArgs, typename... Args>
-void dispatch(void (*kernel)(KArgs...), dim3 grid, dim3 block, size_t lds, const Disp &d, Args... args) {
-    if (d.ev.start != nullptr)
-        hipExtLaunchKernelGGL(kernel, grid, block, (std::uint32_t)lds, d.s, d.ev.start, d.ev.stop, 0u, args...);
-    else
-        hipLaunchKernelGGL(kernel, grid, block, lds, d.s, args...);
-}
-
-template <typename T, int FI, int D>
-void launch_pencil_fast_t(const PencilArgs *args, const int *woff, int np, int total, const Disp &s) {
-    constexpr int N = kFastSched[FI].n;
-    constexpr int B = pencil_batch(N, sizeof(Vt<T>), D);
-    const size_t lds = sizeof(Vt<T>) * ((size_t)N * D * B + tw_lds_entries(N, sizeof(Vt<T>)));
-    dispatch((pencil_fast<T, FI, D>), dim3(total), dim3(pencil_nt(N, sizeof(Vt<T>), D)), lds, s, args, woff, np);
-}
-
-template <typename T, int FI, int D>
-void launch_row_fast_t(const RowArgs *args, const int *woff, int np, int total, const Disp &s) {
-    constexpr int N = kFastSched[FI].n;
-    constexpr int RP = fast_batch(N, sizeof(Vt<T>), D);
-    const size_t lds = sizeof(Vt<T>) * ((size_t)N * D * RP + tw_lds_entries(N, sizeof(Vt<T>)));
-    dispatch((row_fast<T, FI, D>), dim3(total), dim3(kThreads), lds, s, args, woff, np);
-}
-
-template <typename T, int FI>
-void launch_pencil_fast_d(int d, const PencilArgs *args, const int *woff, int np, int total, const Disp &s) {
-    if (d == 3)
-        launch_pencil_fast_t<T, FI, 3>(args, woff, np, total, s);
-    else
-        launch_pencil_fast_t<T, FI, 2>(args, woff, np, total, s);
-}
-
-template <typename T, int FI>
-void launch_row_fast_d(int d, const RowArgs *args, const int *woff, int np, int total, const Disp &s) {
-    if (d == 3)
-        launch_row_fast_t<T, FI, 3>(args, woff, np, total, s);
-    else
-        launch_row_fast_t<T, FI, 2>(args, woff, np, total, s);
-}
-
-template <typename T>
-void launch_pencil_fast(int fi, int d, const PencilArgs *args, const int *woff, int np, int total,
-                        const Disp &s) {
-    switch (fi) {
-        case 0: launch_pencil_fast_d<T, 0>(d, args, woff, np, total, s); break;
-        case 1: launch_pencil_fast_d<T, 1>(d, args, woff, np, total, s); break;
-        case 2: launch_pencil_fast_d<T, 2>(d, args, woff, np, total, s); break;
-        case 3: launch_pencil_fast_d<T, 3>(d, args, woff, np, total, s); break;
-        case 4: launch_pencil_fast_d<T, 4>(d, args, woff, np, total, s); break;
-        default: launch_pencil_fast_d<T, 5>(d, args, woff, np, total, s); break;
-    }
-}
-
-template <typename T>
-void launch_row_fast(int fi, int d, const RowArgs *args, const int *woff, int np, int total, const Disp &s) {
-    switch (fi) {
-        case 0: launch_row_fast_d<T, 0>(d, args, woff, np, total, s); break;
-        case 1: launch_row_fast_d<T, 1>(d, args, woff, np, total, s); break;
-        case 2: launch_row_fast_d<T, 2>(d, args, woff, np, total, s); break;
-        case 3: launch_row_fast_d<T, 3>(d, args, woff, np, total, s); break;
-        case 4: launch_row_fast_d<T, 4>(d, args, woff, np, total, s); break;
-        default: launch_row_fast_d<T, 5>(d, args, woff, np, total, s); break;
-    }
-}
-
-
-template <typename T, int FI>
-void launch_row_iso_t(const RowArgs *args, const int *woff, int np, int total, const Disp &s) {
-    if constexpr (palindromic(FI)) {
-        constexpr int N = kFastSched[FI].n;
-        if constexpr (kFastSched[FI].nst == 2) {
-            const size_t lds = sizeof(T) * (size_t)split_tb(FI) * N + sizeof(Vt<T>) * N;
-            dispatch((row_iso_split<T, FI>), dim3(total), dim3(split_nt(FI)), lds, s, args, woff, np);
-        } else {
-            const size_t lds = sizeof(Vt<T>) * ((size_t)iso_tb(FI) * N + tw_lds_entries(N, sizeof(Vt<T>)));
-            dispatch((row_iso_fast<T, FI>), dim3(total), dim3(iso_nt(FI)), lds, s, args, woff, np);
-        }
-    }
-}
-
-template <typename T, int FI>
-void launch_row_staged_t(int d, const RowArgs *args, const int *woff, int np, int total, const Disp &s) {
-    if constexpr (palindromic(FI) && kFastSched[FI].nst == 2) {
-        if (d == 3)
-            dispatch((row_iso_staged<T, FI, 3>), dim3(total), dim3(staged_nt(FI, 3, sizeof(Vt<T>))), staged_lds<T>(FI, 3),
-                               s, args, woff, np);
-        else
-            dispatch((row_iso_staged<T, FI, 2>), dim3(total), dim3(staged_nt(FI, 2, sizeof(Vt<T>))), staged_lds<T>(FI, 2),
-                               s, args, woff, np);
-    }
-}
-
-template <typename T>
-void launch_row_staged(int fi, int d, const RowArgs *args, const int *woff, int np, int total, const Disp &s) {
-    switch (fi) {
-        case 0: launch_row_staged_t<T, 0>(d, args, woff, np, total, s); break;
-        case 2: launch_row_staged_t<T, 2>(d, args, woff, np, total, s); break;
-        default: break;
-    }
-}
-
-template <typename T>
-void launch_row_iso(int fi, const RowArgs *args, const int *woff, int np, int total, const Disp &s) {
-    switch (fi) {
-        case 0: launch_row_iso_t<T, 0>(args, woff, np, total, s); break;
-        case 1: launch_row_iso_t<T, 1>(args, woff, np, total, s); break;
-        case 2: launch_row_iso_t<T, 2>(args, woff, np, total, s); break;
-        case 3: launch_row_iso_t<T, 3>(args, woff, np, total, s); break;
-        case 4: launch_row_iso_t<T, 4>(args, woff, np, total, s); break;
-        default: launch_row_iso_t<T, 5>(args, woff, np, total, s); break;
-    }
-}
-
-
-// Energy Gram quadrature (ROW_GRAM) for the specialised lengths: all d^2
-// component fields of the d solutions are transformed to the grid in one
-// in-place batch, then (A_M (E_s + e_s), E_t + e_t) is summed over the rows.
-// Row pairs per work-group: one batch within 48 KB of LDS, so that several
-// work-groups share a CU (a single pair of 225-point rows of 9 fields takes
-// 32 KB in FP64: four work-groups per CU).
-constexpr int gram_batch(int n, int es, int d) {
-    int b = 8;
-    while (b > 1 && d * d * b * n * es > 48 * 1024) b /= 2;
-    return b;
-}
-
-template <typename T, int FI, int D>
-__global__ __launch_bounds__(kThreads) void row_gram_fast(const RowArgs *__restrict__ ra, const int *__restrict__ woff,
-                                                          int np) {
-    using V = Vt<T>;
-    constexpr int N = kFastSched[FI].n;
-    constexpr int RP = gram_batch(N, sizeof(V), D);
-    constexpr int NC = D * D;
-    constexpr int NB = NC * RP;  // LDS layout [component][row pair][pos]
-    int lb;
-    const RowArgs &a = ra[find_problem(woff, np, &lb)];
-    extern __shared__ __align__(16) unsigned char smem_raw[];  // 16-byte complex doubles
-    V *X = reinterpret_cast<V *>(smem_raw);
-    const int nh = a.Nh_row;
-    const V *tw = reinterpret_cast<const V *>(a.tw) + a.f.twoff[0];
-    const V *data = reinterpret_cast<const V *>(a.data);
-    const T *g = reinterpret_cast<const T *>(a.g);
-    const int pair0 = lb * RP;
-    const int nvp = min(RP, (a.nrows + 1) / 2 - pair0);
-    const V zero = mk<T>(T(0), T(0));
-    // every global load of the work-group in flight at once: the half-spectrum
-    // rows (at most (N + 1) / 2 points each) and, for the scalar-field form,
-    // the material values of the accumulation below; the band of positions
-    // no load writes is zeroed by a loop of its own
-    constexpr int NHMAX = (N + 1) / 2;
-    constexpr int PE = (NB * NHMAX + kThreads - 1) / kThreads;
-    constexpr int GP = (RP * N + kThreads - 1) / kThreads;
-    V u1v[PE], u2v[PE];
-#pragma unroll
-    for (int t = 0; t < PE; ++t) {
-        const int idx = threadIdx.x + t * kThreads;
-        const int pc = idx / nh;
-        const int kx = idx - pc * nh;
-        const int c = pc / RP;
-        const int j = pc - c * RP;
-        const bool ok = idx < NB * nh && j < nvp;
-        const int r1 = 2 * (pair0 + (ok ? j : 0));
-        const bool two = ok && r1 + 1 < a.nrows;
-        const long o1 = ok ? (long)c * a.cs + (long)r1 * nh + kx : 0L;
-        const long o2 = two ? o1 + nh : 0L;  // in range even if the load is issued
-        u1v[t] = ok ? data[o1] : zero;
-        u2v[t] = two ? data[o2] : zero;
-    }
-    T gv1[GP], gv2[GP];
-    const bool gpre = a.nfield == 1;
-#pragma unroll
-    for (int t = 0; t < GP; ++t) {
-        const int idx = threadIdx.x + t * kThreads;
-        const int j = idx / N;
-        const int x = idx - j * N;
-        const bool ok = gpre && idx < RP * N && j < nvp;
-        const bool two = ok && 2 * (pair0 + j) + 1 < a.nrows;
-        const long r1 = 2 * (pair0 + (ok ? j : 0));
-        const long i1 = ok ? r1 * N + x : 0L, i2 = two ? i1 + N : 0L;
-        gv1[t] = ok ? g[i1] : T(0);
-        gv2[t] = two ? g[i2] : T(0);
-    }
-    const int nzb = N - 2 * nh + 1;  // positions nh .. N - nh of every field
-    for (int idx = threadIdx.x; idx < NB * nzb; idx += kThreads) {
-        const int pc = idx / nzb;
-        X[pc * N + nh + (idx - pc * nzb)] = zero;
-    }
-#pragma unroll
-    for (int t = 0; t < PE; ++t) {
-        const int idx = threadIdx.x + t * kThreads;
-        if (idx >= NB * nh) continue;
-        const int pc = idx / nh;
-        const int kx = idx - pc * nh;
-        const V u1 = u1v[t], u2 = u2v[t];  // zero for idle row pairs
-        if (kx == 0) {
-            X[pc * N] = mk<T>(u1.x, u2.x);
-        } else {
-            X[pc * N + kx] = mk<T>(u1.x - u2.y, u1.y + u2.x);
-            X[pc * N + N - kx] = mk<T>(u1.x + u2.y, u2.x - u1.y);
-        }
-    }
-    __syncthreads();
-    fft_ip<T, FI, 0, 1, 0, NB, true>(X, tw, T(1));
-    T A0[D * D], Dm[D * D];
-#pragma unroll
-    for (int i = 0; i < D * D; ++i) {
-        A0[i] = T(a.A0[i]);
-        Dm[i] = T(a.D[i]);
-    }
-    double gs[D * D];
-#pragma unroll
-    for (int i = 0; i < D * D; ++i) gs[i] = 0.0;
-#pragma unroll
-    for (int t = 0; t < GP; ++t) {
-        const int idx = threadIdx.x + t * kThreads;
-        if (idx >= RP * N) continue;
-        const int j = idx / N;
-        const int x = idx - j * N;
-        if (j >= nvp) continue;
-        const int r1 = 2 * (pair0 + j);
-#pragma unroll
-        for (int half = 0; half < 2; ++half) {
-            const int r = r1 + half;
-            if (r >= a.nrows) continue;
-            T am[D * D];
-            if (a.nfield > 1) {
-                sym_load<T>(g, a.gstride, (long)r * N + x, D, am);
-            } else {
-                const T gg = half ? gv2[t] : gv1[t];
-#pragma unroll
-                for (int i = 0; i < D * D; ++i) am[i] = A0[i] + gg * Dm[i];
-            }
-            T f[D][D];
-#pragma unroll
-            for (int sol = 0; sol < D; ++sol)
-#pragma unroll
-                for (int b = 0; b < D; ++b) {
-                    const V zv = X[((sol * D + b) * RP + j) * N + x];
-                    f[sol][b] = (half ? zv.y : zv.x) + (sol == b ? T(1) : T(0));
-                }
-#pragma unroll
-            for (int t = 0; t < D; ++t) {
-                T af[D];
-#pragma unroll
-                for (int al = 0; al < D; ++al) {
-                    T y = T(0);
-#pragma unroll
-                    for (int b = 0; b < D; ++b) y += am[al * D + b] * f[t][b];
-                    af[al] = y;
-                }
-#pragma unroll
-                for (int sol = 0; sol < D; ++sol) {
-                    T dot = T(0);
-#pragma unroll
-                    for (int al = 0; al < D; ++al) dot += f[sol][al] * af[al];
-                    gs[sol * D + t] += dot;
-                }
-            }
-        }
-    }
-    block_sum_many<D * D>(gs, a.partial + (long)lb * D * D);
-}
-
-template <int FI, int D>
-void launch_gram_fast_t(const RowArgs *args, const int *woff, int np, int total, const Disp &s) {
-    constexpr int N = kFastSched[FI].n;
-    constexpr int RP = gram_batch(N, 16, D);
-    const size_t lds = (size_t)16 * N * D * D * RP;
-    dispatch((row_gram_fast<double, FI, D>), dim3(total), dim3(kThreads), lds, s, args, woff, np);
-}
-
-template <int FI>
-void launch_gram_fast_d(int d, const RowArgs *args, const int *woff, int np, int total, const Disp &s) {
-    if (d == 3)
-        launch_gram_fast_t<FI, 3>(args, woff, np, total, s);
-    else
-        launch_gram_fast_t<FI, 2>(args, woff, np, total, s);
-}
-
-void launch_gram_fast(int fi, int d, const RowArgs *args, const int *woff, int np, int total, const Disp &s) {
-    switch (fi) {
-        case 0: launch_gram_fast_d<0>(d, args, woff, np, total, s); break;
-        case 1: launch_gram_fast_d<1>(d, args, woff, np, total, s); break;
-        case 2: launch_gram_fast_d<2>(d, args, woff, np, total, s); break;
-        case 3: launch_gram_fast_d<3>(d, args, woff, np, total, s); break;
-        case 4: launch_gram_fast_d<4>(d, args, woff, np, total, s); break;
-        default: launch_gram_fast_d<5>(d, args, woff, np, total, s); break;
-    }
-}
 
 // ---- multi-problem CG kernels (one problem per work-group for the scalar one) ----
 __global__ __launch_bounds__(kThreads) void cg_check_multi_kernel(const CgItem *__restrict__ items) {
@@ -3682,9 +1755,22 @@ __global__ __launch_bounds__(kThreads) void image_other_kernel(const double *img
 // ---------------------------------------------------------------------------
 // ---------------------------------------------------------------------------
 // ---------------------------------------------------------------------------
+template <int... I>
+static void fill_parts(FastKernels *t, std::integer_sequence<int, I...>) {
+    (fill_fast<I>(t), ...);
+}
+const FastKernels &fast_kernels(int fi) {
+    struct Table {
+        FastKernels k[kNumFast];
+        Table() { fill_parts(k, std::make_integer_sequence<int, kFastParts>()); }
+    };
+    static const Table t;
+    return t.k[fi];
+}
+
 size_t pencil_lds_bytes(const PencilArgs &a, bool fp64) {
     const size_t es = fp64 ? 16 : 8;
-    if (a.fast) return es * ((size_t)a.f.n * a.d * a.B + tw_lds_entries(a.f.n, (int)es));
+    if (a.fast) return fast_kernels(fast_index(a.f.n)).pencil[fp64][a.d - 2].lds;
     int lacc = 0;
     if (a.pro == PRO_EXPAND) lacc = a.nc * a.L_in;
     if (a.epi == EPI_PROJECT) lacc = a.nc * a.L_out;
@@ -3693,19 +1779,11 @@ size_t pencil_lds_bytes(const PencilArgs &a, bool fp64) {
 
 size_t row_lds_bytes(const RowArgs &a, bool fp64) {
     const size_t es = fp64 ? 16 : 8;
-    if (a.fast == 3) {
-        const int fi = fast_index(a.f.n);
-        if (fi == 0) return fp64 ? staged_lds<double>(0, a.d) : staged_lds<float>(0, a.d);
-        return fp64 ? staged_lds<double>(2, a.d) : staged_lds<float>(2, a.d);
+    if (a.fast) {
+        const FastKernels &k = fast_kernels(fast_index(a.f.n));
+        if (a.mode == ROW_GRAM) return k.gram[a.d - 2].lds;
+        return a.fast == 3 ? k.pairs[fp64][a.d - 2].lds : a.fast == 2 ? k.iso[fp64][a.d - 2].lds : k.row[fp64][a.d - 2].lds;
     }
-    if (a.fast == 2) {
-        const int fi = fast_index(a.f.n);
-        if (fi >= 0 && kFastSched[fi].nst == 2) return es / 2 * (size_t)a.RP * a.f.n + es * a.f.n;
-        return es * ((size_t)a.RP * a.f.n + tw_lds_entries(a.f.n, (int)es));
-    }
-    if (a.fast)
-        return es * ((size_t)a.f.n * (a.mode == ROW_GRAM ? a.d * a.d : a.d) * a.RP +
-                     (a.mode == ROW_GRAM ? 0 : tw_lds_entries(a.f.n, (int)es)));
     const int nz = row_zbufs(a);
     return es * (size_t)(a.zbatch ? 2 * nz : nz + 1) * a.RP * a.f.L;
 }
@@ -3719,16 +1797,21 @@ int row_grid(const RowArgs &a) {
     return a.fast == 2 ? (a.d * pairs + a.RP - 1) / a.RP : (pairs + a.RP - 1) / a.RP;
 }
 
-static_assert(kNumFast == 6, "launch_*_fast switch covers six sizes");
+// Index in kFastSched of the length of f when its stages are that schedule, else -1.
+static int fast_of(const FftDesc &f) {
+    const int fi = f.blue ? -1 : fast_index(f.n);
+    if (fi < 0 || f.nst != kFastSched[fi].nst) return -1;
+    for (int s = 0; s < f.nst; ++s)
+        if (f.radix[s] != kFastSched[fi].r[s]) return -1;
+    return fi;
+}
 
 void configure_pencil(PencilArgs &a, bool fp64) {
-    const int fi = a.f.blue ? -1 : fast_index(a.f.n);
-    bool ok = fi >= 0 && a.nsol == 1 && a.ncomp == a.d && a.epi != EPI_WINDOW && (a.d == 2 || a.d == 3) &&
-              a.f.nst == kFastSched[fi].nst && a.L_in <= a.f.n && a.L_out <= a.f.n;
-    for (int s = 0; ok && s < a.f.nst; ++s) ok = a.f.radix[s] == kFastSched[fi].r[s];
-    if (ok) {
+    const int fi = fast_of(a.f);
+    if (fi >= 0 && a.nsol == 1 && a.ncomp == a.d && a.epi != EPI_WINDOW && (a.d == 2 || a.d == 3) &&
+        a.L_in <= a.f.n && a.L_out <= a.f.n && fast_kernels(fi).pencil[fp64][a.d - 2].fn) {
         a.fast = 1;
-        a.B = pencil_batch(a.f.n, fp64 ? 16 : 8, a.d);
+        a.B = fast_kernels(fi).pencil[fp64][a.d - 2].B;
         return;
     }
     a.fast = 0;
@@ -3751,36 +1834,20 @@ void fit_pencil_components(PencilArgs &a, bool fp64) {
 }
 
 void configure_row(RowArgs &r, bool fp64) {
-    const int fi = r.f.blue ? -1 : fast_index(r.f.n);
-    bool ok = fi >= 0 && (r.mode == ROW_OPER || r.mode == ROW_RHS) && r.ncomp == r.d && (r.d == 2 || r.d == 3) &&
-              r.f.nst == kFastSched[fi].nst && r.Nh_row <= (r.f.n + 1) / 2;
-    for (int s = 0; ok && s < r.f.nst; ++s) ok = r.f.radix[s] == kFastSched[fi].r[s];
-    // the staged variant pays in FP64 (three waves per SIMD either way); in
-    // FP32 its register count would cost occupancy
-    if (ok && r.iso && r.mode == ROW_OPER && palindromic(fi) && kFastSched[fi].nst == 2 &&
-        r.Nh_row <= staged_nhc(r.f.n)) {
-        r.fast = 3;
-        r.RP = staged_tb(fi == 0 ? 0 : 2, r.d, fp64 ? 16 : 8);
-        return;
-    }
-    if (ok && r.iso && r.mode == ROW_OPER && palindromic(fi)) {
-        r.fast = 2;
-        r.RP = iso_tb(fi);
-        return;
-    }
-    if (ok) {
-        r.fast = 1;
-        r.RP = fast_batch(r.f.n, fp64 ? 16 : 8, r.d);
-        return;
-    }
-    const bool gram_ok = fi >= 0 && fp64 && r.mode == ROW_GRAM && r.ncomp == r.d * r.d && (r.d == 2 || r.d == 3) &&
-                         r.f.nst == kFastSched[fi].nst && r.Nh_row <= (r.f.n + 1) / 2;
-    bool sched = gram_ok;
-    for (int s = 0; sched && s < r.f.nst; ++s) sched = r.f.radix[s] == kFastSched[fi].r[s];
-    if (sched) {
-        r.fast = 1;
-        r.RP = gram_batch(r.f.n, 16, r.d);
-        return;
+    const int fi = fast_of(r.f);
+    if (fi >= 0 && (r.d == 2 || r.d == 3)) {
+        const FastKernels &k = fast_kernels(fi);
+        const bool oper = r.mode == ROW_OPER && r.ncomp == r.d;
+        auto take = [&](const FastKernels::Row &e, int fast) {
+            if (!e.fn || r.Nh_row > e.nh_max) return false;
+            r.fast = fast;
+            r.RP = e.RP;
+            return true;
+        };
+        if (oper && r.iso && take(k.pairs[fp64][r.d - 2], 3)) return;
+        if (oper && r.iso && take(k.iso[fp64][r.d - 2], 2)) return;
+        if ((oper || (r.mode == ROW_RHS && r.ncomp == r.d)) && take(k.row[fp64][r.d - 2], 1)) return;
+        if (fp64 && r.mode == ROW_GRAM && r.ncomp == r.d * r.d && take(k.gram[r.d - 2], 1)) return;
     }
     r.fast = 0;
     r.zbatch = 0;
@@ -3870,11 +1937,9 @@ hipError_t launch_pencil_multi(const PencilArgs &proto, const PencilArgs *args, 
                                bool fp64, hipStream_t st, LaunchEv ev) {
     const int fi = fast_index(proto.f.n);
     if (!proto.fast || fi < 0 || np < 1 || total < 1) return hipErrorInvalidValue;
-    const Disp s(st, ev);
-    if (fp64)
-        launch_pencil_fast<double>(fi, proto.d, args, woff, np, total, s);
-    else
-        launch_pencil_fast<float>(fi, proto.d, args, woff, np, total, s);
+    const FastKernels::Pencil &e = fast_kernels(fi).pencil[fp64][proto.d - 2];
+    if (!e.fn) return hipErrorInvalidValue;
+    e.fn(args, woff, np, total, st, ev);
     return hipGetLastError();
 }
 
@@ -3882,32 +1947,14 @@ hipError_t launch_row_multi(const RowArgs &proto, const RowArgs *args, const int
                             hipStream_t st, LaunchEv ev) {
     const int fi = fast_index(proto.f.n);
     if (!proto.fast || fi < 0 || np < 1 || total < 1) return hipErrorInvalidValue;
-    const Disp s(st, ev);
-    if (proto.mode == ROW_GRAM) {
-        if (!fp64) return hipErrorInvalidValue;
-        launch_gram_fast(fi, proto.d, args, woff, np, total, s);
-        return hipGetLastError();
-    }
-    if (proto.fast == 3) {
-        if (!(fi == 0 || fi == 2) || proto.mode != ROW_OPER) return hipErrorInvalidValue;
-        if (fp64)
-            launch_row_staged<double>(fi, proto.d, args, woff, np, total, s);
-        else
-            launch_row_staged<float>(fi, proto.d, args, woff, np, total, s);
-        return hipGetLastError();
-    }
-    if (proto.fast == 2) {
-        if (!palindromic(fi) || proto.mode != ROW_OPER) return hipErrorInvalidValue;
-        if (fp64)
-            launch_row_iso<double>(fi, args, woff, np, total, s);
-        else
-            launch_row_iso<float>(fi, args, woff, np, total, s);
-        return hipGetLastError();
-    }
-    if (fp64)
-        launch_row_fast<double>(fi, proto.d, args, woff, np, total, s);
-    else
-        launch_row_fast<float>(fi, proto.d, args, woff, np, total, s);
+    const FastKernels &k = fast_kernels(fi);
+    const FastKernels::Row &e = proto.mode == ROW_GRAM ? k.gram[proto.d - 2]
+                                : proto.fast == 3     ? k.pairs[fp64][proto.d - 2]
+                                : proto.fast == 2     ? k.iso[fp64][proto.d - 2]
+                                                      : k.row[fp64][proto.d - 2];
+    if (!e.fn || (proto.mode == ROW_GRAM && !fp64) || (proto.fast > 1 && proto.mode != ROW_OPER))
+        return hipErrorInvalidValue;
+    e.fn(args, woff, np, total, st, ev);
     return hipGetLastError();
 }
 
