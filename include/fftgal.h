@@ -94,9 +94,9 @@ enum fftgal_precision {
 #define FFTGAL_CONCURRENT 0x400
 
 /* Flag or-ed into `precision` of fftgal_workspace_bytes* and the plan
- * constructors.  By default the CG iterations of 2D Ga plans whose double
- * grid is 81 x 81 (N = 41, or smaller N with FFTGAL_FAST_GRID; FP32-iteration
- * form also 81 or 125 on either axis) run entirely inside one work-group per
+ * constructors.  By default the CG iterations of 2D Ga plans whose complex
+ * double grid fits the LDS of one work-group (up to 81 x 81 points, N = 41;
+ * FP32-iteration form up to 125 x 125) run entirely inside one work-group per
  * solve: the CG vectors
  * in registers, the operator of Algorithm 2 on the M_1 x M_2 grid in LDS, the
  * update and the stopping test in the same kernel, many iterations per launch

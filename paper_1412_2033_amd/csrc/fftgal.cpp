@@ -1505,8 +1505,12 @@ int final_checkpoint(Plan *pl, int kind, int alpha, CgStatus *h) {
 // work-group solver (2D Ga on a double grid it holds in LDS).
 bool use_solo(const Plan *pl) {
     const Dims &D = pl->D;
-    return pl->solo && D.d == 2 && !pl->gani && !pl->reduced && D.nshift == 1 && !pl->fM[0].blue &&
-           !pl->fM[1].blue && solo_fits(D.M[0], D.M[1], pl->fp64_iter());
+    SoloArgs a{};
+    a.M0 = D.M[0];
+    a.M1 = D.M[1];
+    a.N0 = D.N[0];
+    a.Nh = D.Nh;
+    return pl->solo && D.d == 2 && !pl->gani && !pl->reduced && D.nshift == 1 && solo_fits(a, pl->fM, pl->fp64_iter());
 }
 
 // Arguments of the single work-group solver for one solve (in the plan's
@@ -1539,6 +1543,7 @@ SoloArgs make_solo(Plan *pl, int kind, int alpha) {
     a.Nh = D.Nh;
     a.kind = kind;
     a.scale = 1.0 / ((double)D.nshift * D.Mtot);
+    (void)solo_fits(a, pl->fM, fp64);
     return a;
 }
 
@@ -2574,7 +2579,7 @@ struct fftgal_batch {
         size_t args_off, woff_off;
     };
     std::vector<UGroup> ugroups;
-    // members in the single work-group solver, one launch per grid and precision
+    // members in the single work-group solver, one launch per grid, order and precision
     struct SGroup {
         bool fp64;
         int np;
@@ -2687,14 +2692,14 @@ int batch_rebuild(Batch *b) {
         b->ugroups.push_back(u);
     }
     std::vector<CgItem> items;
-    std::map<std::tuple<int, int, int>, std::vector<SoloArgs>> solo_by;
+    std::map<std::tuple<int, int, int, int, int>, std::vector<SoloArgs>> solo_by;
     for (size_t m = 0; m < nm; ++m) {
         CgStatus *mirror = reinterpret_cast<CgStatus *>(b->ws) + m;
         const Batch::Member &mem = b->members[m];
         if (mem.solo) {
             SoloArgs a = mem.sargs;
             a.mirror = mirror;
-            solo_by[std::make_tuple((int)mem.cfg.fp64, a.M0, a.M1)].push_back(a);
+            solo_by[std::make_tuple((int)mem.cfg.fp64, a.M0, a.M1, a.N0, a.Nh)].push_back(a);
             continue;
         }
         items.push_back(mem.cfg.item);

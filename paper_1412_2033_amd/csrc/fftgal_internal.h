@@ -231,6 +231,11 @@ struct UpdArgs {
 // f gstride holding the entries 11, 12, 22 of A(x) (nfield = 3) on the M0 x M1
 // grid, the stage twiddles of both axes (entries tw0, tw1 of tw), the basis
 // kind and the scale 1 / (M0 M1) of the forward transforms.
+constexpr int kSoloStages = 4;
+struct SoloStage {  // of a length n known at run time: radix R, P, butterflies n / R, first twiddle
+    int R, P, TQ, tw;
+    unsigned mTQ, mP;  // multipliers of the divisions by TQ and P (solo_div)
+};
 struct SoloArgs {
     void *x, *r, *p;
     CgStatus *st;
@@ -246,6 +251,11 @@ struct SoloArgs {
     int M0, M1, N0, Nh;
     int kind;
     double scale;
+    // the kernel of run-time lengths: the stages of both axes and the
+    // multipliers of the divisions by Nh, by the 2 Nh - 1 non-zero columns
+    int nst[2];
+    SoloStage stg[2][kSoloStages];
+    unsigned mNh, mNA;
 };
 
 struct CgItem {
@@ -358,9 +368,10 @@ hipError_t launch_pencil_multi(const PencilArgs &proto, const PencilArgs *args, 
 hipError_t launch_row_multi(const RowArgs &proto, const RowArgs *args, const int *woff, int np, int total,
                             bool fp64, hipStream_t s, LaunchEv ev = LaunchEv{});
 hipError_t launch_cg_check_multi(const CgItem *items, int np, hipStream_t s, LaunchEv ev = LaunchEv{});
-// Whether a 2D Ga grid M0 x M1 has the single-work-group solver (both lengths
-// specialised, the complex grid within the LDS of one work-group).
-bool solo_fits(int M0, int M1, bool fp64);
+// Whether the 2D Ga grid of `a` (M0, M1, N0, Nh; axes transformed as f[0], f[1])
+// has the single-work-group solver (3,5,7-smooth lengths, the complex grid
+// within the LDS of one work-group); fills the stages of `a` when it does.
+bool solo_fits(SoloArgs &a, const FftDesc *f, bool fp64);
 // `niter` CG iterations (fewer once a solve is done) of each of the np solves
 // in `args` (device array; all of one grid and precision), one work-group each.
 hipError_t launch_solo(const SoloArgs &proto, const SoloArgs *args, int np, int niter, bool fp64, hipStream_t s,

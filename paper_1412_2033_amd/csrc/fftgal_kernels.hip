@@ -1296,6 +1296,12 @@ __global__ __launch_bounds__(kThreads) void cg_update_multi_kernel(const UpdArgs
 // with work-group sums in a fixed order) follow in the same work-group, so a
 // launch runs many iterations with no kernel boundary between them.
 // ---------------------------------------------------------------------------
+//
+// Two forms share the kernel: lengths of 81 or 125 points known at compile
+// time (FI0, FI1 their indices), and any 3,5,7-smooth lengths taken from the
+// arguments (FI0 = -1) for the other grids that fit; the latter use 256 or 512
+// threads on small grids, where a barrier of fewer waves costs less than the
+// idle lanes save.
 constexpr int kSoloNT = 1024;
 template <typename T>
 constexpr size_t solo_lds_bytes_t(int m0, int m1) {
@@ -1304,6 +1310,7 @@ constexpr size_t solo_lds_bytes_t(int m0, int m1) {
 
 // fixed-order sum over the 1024 threads (shuffle tree per wave, then the
 // waves in turn by thread 0), broadcast to every thread
+template <int NT>
 __device__ __forceinline__ double solo_sum(double v, double *red) {
     for (int off = 32; off > 0; off >>= 1) v += __shfl_down(v, off, 64);
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
@@ -1311,20 +1318,99 @@ __device__ __forceinline__ double solo_sum(double v, double *red) {
     __syncthreads();
     if (threadIdx.x == 0) {
         double s = 0.0;
-        for (int w = 0; w < kSoloNT / 64; ++w) s += red[w];
-        red[kSoloNT / 64] = s;
+        for (int w = 0; w < NT / 64; ++w) s += red[w];
+        red[NT / 64] = s;
     }
     __syncthreads();
-    return red[kSoloNT / 64];
+    return red[NT / 64];
 }
 
-template <typename T, int FI0, int FI1>
-__global__ __launch_bounds__(kSoloNT) void solo2d_kernel(const SoloArgs *__restrict__ sa, int niter) {
+// x / d for x < 2^32 / d, with m = floor(2^32 / d) + 1 (0 stands for d = 1)
+__device__ __forceinline__ int solo_div(int x, unsigned m) { return m == 0 ? x : (int)__umulhi((unsigned)x, m); }
+
+// Most butterflies of radix R per thread of an in-place stage: their values
+// wait in registers for the barrier.
+constexpr int solo_per(int R, bool fp64) {
+    return R == 3 ? (fp64 ? 3 : 6) : R == 5 ? (fp64 ? 2 : 4) : R == 7 ? (fp64 ? 2 : 3) : R <= 15 ? (fp64 ? 1 : 2) : 1;
+}
+
+// One in-place stage of radix R along axis 0 (COL: the NA non-zero columns of
+// the [.][M1] grid) or axis 1 (rows), over nb transforms.
+template <typename T, int R, bool COL, int NT>
+__device__ __forceinline__ void solo_stage(Vt<T> *X, const Vt<T> *tw, const SoloStage &g, int M1, int nb, int Nh,
+                                           unsigned mNA, T sg) {
+    constexpr int PER = solo_per(R, sizeof(T) == 8);
+    const int TQ = g.TQ, P = g.P;
+    const int tot = TQ * nb;
+    Vt<T> u[PER][R];
+    int base[PER], k[PER], i[PER];
+#pragma unroll
+    for (int t = 0; t < PER; ++t) {
+        const int idx = threadIdx.x + t * NT;
+        if (idx >= tot) break;
+        if (COL) {
+            i[t] = solo_div(idx, mNA);
+            const int c = idx - i[t] * nb;
+            base[t] = c < Nh ? c : c + (M1 - nb);
+        } else {
+            const int b = solo_div(idx, g.mTQ);
+            i[t] = idx - b * TQ;
+            base[t] = b * M1;
+        }
+        k[t] = i[t] - solo_div(i[t], g.mP) * P;
+#pragma unroll
+        for (int q = 0; q < R; ++q) u[t][q] = X[base[t] + (i[t] + q * TQ) * (COL ? M1 : 1)];
+    }
+    __syncthreads();
+#pragma unroll
+    for (int t = 0; t < PER; ++t) {
+        const int idx = threadIdx.x + t * NT;
+        if (idx >= tot) break;
+        if (P > 1) {
+#pragma unroll
+            for (int q = 1; q < R; ++q) {
+                Vt<T> w = tw[(q - 1) * P + k[t]];
+                w.y *= -sg;
+                u[t][q] = cmul(u[t][q], w);
+            }
+        }
+        dftn<T, R>(u[t], sg);
+        const int j = (i[t] - k[t]) * R + k[t];
+#pragma unroll
+        for (int q = 0; q < R; ++q) X[base[t] + (j + q * P) * (COL ? M1 : 1)] = u[t][q];
+    }
+    __syncthreads();
+}
+
+template <typename T, bool COL, int NT>
+__device__ __forceinline__ void solo_fft(Vt<T> *X, const Vt<T> *tw, const SoloArgs &a, int nb, T sg) {
+    for (int s = 0; s < a.nst[COL ? 0 : 1]; ++s) {
+        const SoloStage &g = a.stg[COL ? 0 : 1][s];
+        const Vt<T> *t = tw + g.tw;
+        switch (g.R) {
+            case 3: solo_stage<T, 3, COL, NT>(X, t, g, a.M1, nb, a.Nh, a.mNA, sg); break;
+            case 5: solo_stage<T, 5, COL, NT>(X, t, g, a.M1, nb, a.Nh, a.mNA, sg); break;
+            case 7: solo_stage<T, 7, COL, NT>(X, t, g, a.M1, nb, a.Nh, a.mNA, sg); break;
+            case 9: solo_stage<T, 9, COL, NT>(X, t, g, a.M1, nb, a.Nh, a.mNA, sg); break;
+            case 15: solo_stage<T, 15, COL, NT>(X, t, g, a.M1, nb, a.Nh, a.mNA, sg); break;
+            default: solo_stage<T, 25, COL, NT>(X, t, g, a.M1, nb, a.Nh, a.mNA, sg); break;
+        }
+    }
+}
+
+// coefficients per thread: the half spectrum of the compile-time grid, or two
+// (1024 threads) and one otherwise
+constexpr int solo_cpt(int fi0, int fi1, int nt) {
+    if (fi0 < 0) return nt == 1024 ? 2 : 1;
+    return ((kFastSched[fi0].n + 1) / 2 * ((kFastSched[fi1].n + 3) / 4) + nt - 1) / nt;
+}
+template <typename T, int FI0, int FI1, int NT>
+__global__ __launch_bounds__(NT) void solo2d_kernel(const SoloArgs *__restrict__ sa, int niter) {
     using V = Vt<T>;
-    constexpr int M0 = kFastSched[FI0].n, M1 = kFastSched[FI1].n;
-    constexpr int NT = kSoloNT;
-    constexpr int CPT = ((M0 + 1) / 2 * ((M1 + 3) / 4) + NT - 1) / NT;  // coefficients per thread
+    constexpr bool ANY = FI0 < 0;  // lengths from the arguments
+    constexpr int CPT = solo_cpt(FI0, FI1, NT);
     const SoloArgs &a = sa[blockIdx.x];
+    const int M0 = ANY ? a.M0 : kFastSched[ANY ? 0 : FI0].n, M1 = ANY ? a.M1 : kFastSched[ANY ? 0 : FI1].n;
     __shared__ CgStatus S;
     __shared__ double red[NT / 64 + 1];
     extern __shared__ __align__(16) unsigned char smem_raw[];
@@ -1352,7 +1438,7 @@ __global__ __launch_bounds__(kSoloNT) void solo2d_kernel(const SoloArgs *__restr
         const int idx = threadIdx.x + j * NT;
         own[j] = idx < ns;
         const int id = own[j] ? idx : 0;
-        const int l = id / Nh;
+        const int l = ANY ? solo_div(id, a.mNh) : id / Nh;
         const int k1 = id - l * Nh;
         const int k0 = wrapi(l, N0);
         T tb[2][3];
@@ -1412,8 +1498,14 @@ __global__ __launch_bounds__(kSoloNT) void solo2d_kernel(const SoloArgs *__restr
         // columns: only the N_2 = (M_2 + 1) / 2 non-zero ones (zero-padded
         // frequencies stay zero, and only they are read back after the
         // forward transform)
-        fft_ip<T, FI0, 0, 1, 0, M1, false, NT, (M1 + 1) / 2>(Z, tw0, T(1));
-        fft_ip<T, FI1, 0, 1, 0, M0, true, NT>(Z, tw1, T(1));
+        if constexpr (ANY) {
+            solo_fft<T, true, NT>(Z, tw0, a, 2 * Nh - 1, T(1));
+            solo_fft<T, false, NT>(Z, tw1, a, M0, T(1));
+        } else {
+            constexpr int C0 = kFastSched[FI0].n, C1 = kFastSched[FI1].n;
+            fft_ip<T, FI0, 0, 1, 0, C1, false, NT, (C1 + 1) / 2>(Z, tw0, T(1));
+            fft_ip<T, FI1, 0, 1, 0, C0, true, NT>(Z, tw1, T(1));
+        }
         if (a.nfield == 1) {
             for (int i = threadIdx.x; i < M0 * M1; i += NT) {
                 const V z = Z[i];
@@ -1429,8 +1521,14 @@ __global__ __launch_bounds__(kSoloNT) void solo2d_kernel(const SoloArgs *__restr
             }
         }
         __syncthreads();
-        fft_ip<T, FI1, 0, 1, 0, M0, true, NT>(Z, tw1, T(-1));
-        fft_ip<T, FI0, 0, 1, 0, M1, false, NT, (M1 + 1) / 2>(Z, tw0, T(-1));
+        if constexpr (ANY) {
+            solo_fft<T, false, NT>(Z, tw1, a, M0, T(-1));
+            solo_fft<T, true, NT>(Z, tw0, a, 2 * Nh - 1, T(-1));
+        } else {
+            constexpr int C0 = kFastSched[FI0].n, C1 = kFastSched[FI1].n;
+            fft_ip<T, FI1, 0, 1, 0, C0, true, NT>(Z, tw1, T(-1));
+            fft_ip<T, FI0, 0, 1, 0, C1, false, NT, (C1 + 1) / 2>(Z, tw0, T(-1));
+        }
         // projection q = -i scale sum_c t_c Y'_c and the partial of (p, q)
         T qr[CPT], qi[CPT];
         double part = 0.0;
@@ -1447,7 +1545,7 @@ __global__ __launch_bounds__(kSoloNT) void solo2d_kernel(const SoloArgs *__restr
             qi[j] = -(s0 * y0x + s1 * y1x);
             part += (double)wgt[j] * ((double)pr[j] * (double)qr[j] + (double)pi_[j] * (double)qi[j]);
         }
-        const double pq = solo_sum(part, red);
+        const double pq = solo_sum<NT>(part, red);
         const bool bad = !(pq > 0.0) || !isfinite(pq);
         if (threadIdx.x == 0) {
             S.pq = pq;
@@ -1476,7 +1574,7 @@ __global__ __launch_bounds__(kSoloNT) void solo2d_kernel(const SoloArgs *__restr
             ri[j] = ri[j] - alpha * qi[j];
             part2 += (double)wgt[j] * ((double)rr_[j] * rr_[j] + (double)ri[j] * ri[j]);
         }
-        const double rr = solo_sum(part2, red);
+        const double rr = solo_sum<NT>(part2, red);
         if (threadIdx.x == 0) {
             // the stopping test of cg_check_multi_kernel
             const int iter = S.iter + 1;
@@ -1896,22 +1994,71 @@ hipError_t launch_row(const RowArgs &a, bool fp64, hipStream_t s) {
     return hipGetLastError();
 }
 
-bool solo_fits(int M0, int M1, bool fp64) {
-    const int f0 = fast_index(M0), f1 = fast_index(M1);
-    if (!((f0 == 0 || f0 == 1) && (f1 == 0 || f1 == 1))) return false;
-    const size_t lds = fp64 ? solo_lds_bytes_t<double>(M0, M1) : solo_lds_bytes_t<float>(M0, M1);
-    return lds + 1024 <= 160 * 1024;
+// Index of the compile-time grid of the single-work-group solver, or -1.
+static int solo_fast(int m) {
+    const int fi = fast_index(m);
+    return fi == 0 || fi == 1 ? fi : -1;
+}
+static size_t solo_lds(int M0, int M1, bool fp64) {
+    return fp64 ? solo_lds_bytes_t<double>(M0, M1) : solo_lds_bytes_t<float>(M0, M1);
+}
+constexpr size_t kSoloLds = 160 * 1024 - 1024;
+
+// Threads of the run-time-length form: few on small grids, then whatever the
+// registers of the in-place stages (solo_per) and of the CG vectors
+// (solo_cpt) need; 0 if the grid does not fit.
+static int solo_threads(const SoloArgs &a, bool fp64) {
+    const long pts = (long)a.M0 * a.M1;
+    for (int nt = pts <= 1500 ? 256 : pts <= 4000 ? 512 : 1024; nt <= 1024; nt *= 2) {
+        bool ok = (long)a.N0 * a.Nh <= (long)nt * solo_cpt(-1, -1, nt);
+        for (int x = 0; x < 2; ++x)
+            for (int s = 0; s < a.nst[x]; ++s) {
+                const SoloStage &g = a.stg[x][s];
+                ok = ok && (long)g.TQ * (x == 0 ? 2 * a.Nh - 1 : a.M0) <= (long)nt * solo_per(g.R, fp64);
+            }
+        if (ok) return nt;
+    }
+    return 0;
+}
+
+bool solo_fits(SoloArgs &a, const FftDesc *f, bool fp64) {
+    if (f[0].blue || f[1].blue || solo_lds(a.M0, a.M1, fp64) > kSoloLds) return false;
+    if (solo_fast(a.M0) >= 0 && solo_fast(a.M1) >= 0) return true;
+    auto mult = [](int d) { return d == 1 ? 0u : (unsigned)((1ull << 32) / (unsigned)d) + 1u; };
+    for (int x = 0; x < 2; ++x) {
+        if (f[x].nst > kSoloStages) return false;
+        a.nst[x] = f[x].nst;
+        int p = 1;
+        for (int s = 0; s < f[x].nst; ++s) {
+            const int r = f[x].radix[s];
+            if (r != 3 && r != 5 && r != 7 && r != 9 && r != 15 && r != 25) return false;
+            a.stg[x][s] = {r, p, f[x].n / r, f[x].twoff[s] - f[x].twoff[0], mult(f[x].n / r), mult(p)};
+            p *= r;
+        }
+    }
+    a.mNh = mult(a.Nh);
+    a.mNA = mult(2 * a.Nh - 1);
+    return solo_threads(a, fp64) > 0;
 }
 
 template <typename T, int FI0, int FI1>
 void launch_solo_t(const SoloArgs *args, int np, int niter, const Disp &s) {
     constexpr size_t lds = solo_lds_bytes_t<T>(kFastSched[FI0].n, kFastSched[FI1].n);
-    if constexpr (lds + 1024 <= 160 * 1024)
-        dispatch((solo2d_kernel<T, FI0, FI1>), dim3(np), dim3(kSoloNT), lds, s, args, niter);
+    if constexpr (lds <= kSoloLds)
+        dispatch((solo2d_kernel<T, FI0, FI1, kSoloNT>), dim3(np), dim3(kSoloNT), lds, s, args, niter);
 }
 
 template <typename T>
-void launch_solo_d(int f0, int f1, const SoloArgs *args, int np, int niter, const Disp &s) {
+void launch_solo_d(const SoloArgs &proto, const SoloArgs *args, int np, int niter, const Disp &s) {
+    const int f0 = solo_fast(proto.M0), f1 = solo_fast(proto.M1);
+    if (f0 < 0 || f1 < 0) {
+        const size_t lds = solo_lds_bytes_t<T>(proto.M0, proto.M1);
+        const int nt = solo_threads(proto, sizeof(T) == 8);
+        if (nt == 256) dispatch((solo2d_kernel<T, -1, -1, 256>), dim3(np), dim3(256), lds, s, args, niter);
+        if (nt == 512) dispatch((solo2d_kernel<T, -1, -1, 512>), dim3(np), dim3(512), lds, s, args, niter);
+        if (nt == 1024) dispatch((solo2d_kernel<T, -1, -1, 1024>), dim3(np), dim3(1024), lds, s, args, niter);
+        return;
+    }
     if (f0 == 0 && f1 == 0) launch_solo_t<T, 0, 0>(args, np, niter, s);
     if (f0 == 0 && f1 == 1) launch_solo_t<T, 0, 1>(args, np, niter, s);
     if (f0 == 1 && f1 == 0) launch_solo_t<T, 1, 0>(args, np, niter, s);
@@ -1920,13 +2067,14 @@ void launch_solo_d(int f0, int f1, const SoloArgs *args, int np, int niter, cons
 
 hipError_t launch_solo(const SoloArgs &proto, const SoloArgs *args, int np, int niter, bool fp64, hipStream_t st,
                        LaunchEv ev) {
-    if (np < 1 || niter < 1 || !solo_fits(proto.M0, proto.M1, fp64)) return hipErrorInvalidValue;
-    const int f0 = fast_index(proto.M0), f1 = fast_index(proto.M1);
+    if (np < 1 || niter < 1 || solo_lds(proto.M0, proto.M1, fp64) > kSoloLds) return hipErrorInvalidValue;
+    if ((solo_fast(proto.M0) < 0 || solo_fast(proto.M1) < 0) && solo_threads(proto, fp64) == 0)
+        return hipErrorInvalidValue;
     const Disp s(st, ev);
     if (fp64)
-        launch_solo_d<double>(f0, f1, args, np, niter, s);
+        launch_solo_d<double>(proto, args, np, niter, s);
     else
-        launch_solo_d<float>(f0, f1, args, np, niter, s);
+        launch_solo_d<float>(proto, args, np, niter, s);
     return hipGetLastError();
 }
 
