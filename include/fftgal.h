@@ -194,7 +194,10 @@ typedef struct fftgal_info {
 /*
  * Bytes of device workspace a plan of dimension d (2 or 3), orders N[0..d-1]
  * (odd, >= 1) and precision needs; 0 if the arguments are invalid.  Used for
- * admission by HBM footprint.  If voxel images with resolution P other than
+ * admission by HBM footprint.  For grids that one solve leaves the GPU idle on
+ * it holds up to 32 MiB with which the d or 2d solves of one call run at once;
+ * a plan also takes a workspace without that room and then runs them one after
+ * another, with bitwise the same results.  If voxel images with resolution P other than
  * the plan's M will be set, pass the largest P through fftgal_workspace_bytes_p.
  */
 size_t fftgal_workspace_bytes(int d, const int32_t *N, int precision);
@@ -275,7 +278,9 @@ int fftgal_solve_dual(struct fftgal_plan *plan, int alpha, double rtol, int maxi
  * solves at once: every launch of an iteration covers all unfinished ones (a
  * small grid fills the GPU that one solve leaves idle), each with its own
  * reductions, so every result equals bitwise that of its solve alone.  Other
- * plans run them one after another.  Returns the first non-OK outcome
+ * plans do the same on small grids, as far as their workspace holds (see
+ * fftgal_workspace_bytes; while kernel timing is enabled the solves run one
+ * after another).  Returns the first non-OK outcome
  * (ENOTCONV, EBREAKDOWN) after all solves ran, or ESTATE / EINVAL / EDEVICE.
  */
 int fftgal_solve_all(struct fftgal_plan *plan, double rtol, int maxit, fftgal_info *info);

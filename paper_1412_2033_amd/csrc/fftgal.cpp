@@ -191,6 +191,12 @@ struct Layout {
     // solve slots: the per-solve region [T1 .. part_c] repeated nslots times
     int nslots;
     size_t slot_bytes;
+    // solves run at once by plans of one solve slot (plan_at_once): slot s > 0
+    // keeps its vectors and partial sums [r .. part_c] in a copy after the
+    // layout, and its intermediates in the s-th d components of T1 and T2 (laid
+    // out for d^2), or, from slot d on, after the layout too
+    int at_once;
+    size_t once_vec, once_t, once_bytes;
 };
 
 constexpr size_t kMultiArgsBytes = 64 * 1024;  // argument tables of multi-shift passes
@@ -280,13 +286,36 @@ Layout make_layout(const Dims &D, int precision, bool grouped = true, int nsl = 
     L.gB64 = take(nfld * 8);
     L.gA32 = take(precision == FFTGAL_FP32_ITER ? nfld * 4 : 0);
     L.gB32 = take(precision == FFTGAL_FP32_ITER ? nfld * 4 : 0);
-    L.gram = take(64 * 8);
+    L.gram = take((size_t)std::max(64, 32 * D.nshift) * 8);
     L.args = take(kArgsBytes);
     L.margs = take(slots ? kMultiArgsBytes : 0);
     L.status = take(6 * sizeof(CgStatus));
     L.hist = take((size_t)6 * 2 * (kMaxHist + 1) * 8);
     L.total = align256(off);
+    L.at_once = 1;
+    L.once_vec = L.T1 + L.slot_bytes - L.r;
+    L.once_t = align256((L.t1_slot + L.t2_slot) * 16);
+    L.once_bytes = 0;
     return L;
+}
+
+// How many of its solves a plan without FFTGAL_CONCURRENT runs at once: all 2d
+// or the d of one kind, when the copies that takes (after the layout; a voxel
+// image's scratch shares the place, since no solve runs while a material is
+// set) hold at most kOnceBytes.  Larger grids, whose single solve fills the
+// GPU, run one after another (3D order 81 and above: nothing to gain, the
+// passes of one solve already run at the memory's rate).
+constexpr size_t kOnceBytes = (size_t)32 << 20;
+size_t bws_bytes(int d);
+void plan_at_once(const Dims &D, Layout *L) {
+    if (D.nshift > 1 || L->nslots > 1) return;
+    for (int n : {2 * D.d, D.d}) {
+        const size_t b = (size_t)(n - 1) * L->once_vec + (size_t)(n - D.d) * L->once_t + bws_bytes(D.d);
+        if (b > kOnceBytes) continue;
+        L->at_once = n;
+        L->once_bytes = b;
+        return;
+    }
 }
 
 constexpr long double kPiL = 3.141592653589793238462643383279502884L;
@@ -442,7 +471,18 @@ struct fftgal_plan {
     char *T2s() { return ws + so(Lo.T2) + (size_t)islot * Lo.t2_slot * 16; }
     // solve slot whose per-solve region the passes being built use
     int slot = 0;
-    size_t so(size_t off) const { return off + (size_t)slot * Lo.slot_bytes; }
+    int at_once = 1;  // solves the plan runs at once (Layout::at_once, or its solve slots)
+    size_t so(size_t off) const {
+        if (slot == 0 || Lo.nslots > 1) return off + (size_t)slot * Lo.slot_bytes;
+        const size_t vecs = (size_t)(Lo.at_once - 1) * Lo.once_vec;
+        if (off == Lo.T1 || off == Lo.T2) {
+            const size_t t1 = off == Lo.T2 ? Lo.t1_slot * 16 : 0;
+            if (slot < D.d) return off + (size_t)slot * (off == Lo.T1 ? Lo.t1_slot : Lo.t2_slot) * 16;
+            return Lo.total + vecs + (size_t)(slot - D.d) * Lo.once_t + t1;
+        }
+        return Lo.total + (size_t)(slot - 1) * Lo.once_vec + (off - Lo.r);
+    }
+    std::vector<std::vector<unsigned char>> stage_host;  // host images of uploads in flight (run_stages)
     std::vector<unsigned char> margs_host;  // staging of the multi-shift argument tables
     int ring = 0;
     unsigned char ring_host[kRingSlots][kArgSlot] = {};
@@ -1382,18 +1422,14 @@ int checkpoint(Plan *pl, int kind, int alpha, bool final) {
     return FFTGAL_OK;
 }
 
-// Right-hand side r_0 = -P^* F_M (A_M E), ||A_M E||, status initialisation,
-// x = p = 0 (stream ordered; no host synchronisation).
-int start_solve(Plan *pl, int kind, int alpha, double rtol, int maxit) {
+// Right-hand side r_0 = -P^* F_M (A_M E) and ||A_M E|| (run, or recorded while
+// passes are captured), and the arguments of the status initialisation.
+int build_rhs(Plan *pl, int kind, int alpha, double rtol, int maxit, InitArgs *init) {
     const Dims &D = pl->D;
     const bool fp64 = pl->fp64_iter();
-    CgStatus *st = pl->status(kind, alpha);
-    void *x = pl->xsol(kind, alpha);
     pl->hist_on = maxit <= kMaxHist;
     pl->hist_valid[kind][alpha] = pl->hist_on;
     pl->cur_alpha = alpha;
-    const size_t es = fp64 ? 16 : 8;
-    const size_t vbytes = (size_t)pl->nc(kind) * D.Ns * es;
     void *rows = pl->ws + (D.d == 3 ? pl->so(pl->Lo.T2) : pl->so(pl->Lo.T1));
     // one pass per shifted grid (reduced Ga; one grid otherwise), the load
     // partials of shift s at offset s * nload, the projected loads summed in r
@@ -1413,21 +1449,61 @@ int start_solve(Plan *pl, int kind, int alpha, double rtol, int maxit) {
                             pl->at<double>(pl->so(pl->Lo.part_a)), &nrr, FFTGAL_K_RHS, FFTGAL_K_RHS, s, s > 0);
         if (rc) return rc;
     }
-    nload *= D.nshift;
-    // FP32 iterations keep b for the exact energies of the checkpoints
-    if (!fp64) HIPCHECK(pl, launch_copy_vec(pl->ws + pl->so(pl->Lo.bvec), pl->ws + pl->so(pl->Lo.r), vbytes, pl->stream));
     // The load sums |A_M E|^2 over grid points; (., .)_{R^{d x M}} divides by |M|.
-    const double floor_rel = (fp64 ? kFloor64 : kFloor32) / std::sqrt(npts);
+    InitArgs a{};
+    a.st = pl->status(kind, alpha);
+    a.rr_part = pl->at<double>(pl->so(pl->Lo.part_a));
+    a.n_rr = nrr;
+    a.load_part = pl->at<double>(pl->so(pl->Lo.part_b));
+    a.work_part = pl->at<double>(pl->so(pl->Lo.part_c));
+    a.n_load = nload * D.nshift;
+    a.inv_mtot = 1.0 / npts;
+    a.tol = rtol;
+    a.floor_rel = (fp64 ? kFloor64 : kFloor32) / std::sqrt(npts);
+    a.maxit = maxit;
+    a.btol = pl->btol;
+    a.hist = pl->hist(kind, alpha);
+    *init = a;
+    return FFTGAL_OK;
+}
+
+// Bytes of one CG vector of a solve, and the vector operations that start it
+// from x = p = 0 (FP32: with b kept for the exact energies of the checkpoints).
+size_t solve_vec_bytes(Plan *pl, int kind) {
+    return (size_t)pl->nc(kind) * pl->D.Ns * (pl->fp64_iter() ? 16 : 8);
+}
+void start_vectors(Plan *pl, int kind, int alpha, VecOps *v) {
+    const size_t words = solve_vec_bytes(pl, kind) / 4;
+    v->op[v->n++] = {pl->xsol(kind, alpha), nullptr, words};
+    v->op[v->n++] = {pl->ws + pl->so(pl->Lo.p), nullptr, words};
+    if (pl->fp64_iter()) return;
+    v->op[v->n++] = {pl->ws + pl->so(pl->Lo.xbest), nullptr, words};
+    v->op[v->n++] = {pl->ws + pl->so(pl->Lo.bvec), pl->ws + pl->so(pl->Lo.r), words};
+}
+
+// Right-hand side, status initialisation, x = p = 0 or the warm start (stream
+// ordered; no host synchronisation).
+int start_solve(Plan *pl, int kind, int alpha, double rtol, int maxit) {
+    const Dims &D = pl->D;
+    const bool fp64 = pl->fp64_iter();
+    CgStatus *st = pl->status(kind, alpha);
+    void *x = pl->xsol(kind, alpha);
+    const size_t vbytes = solve_vec_bytes(pl, kind);
+    InitArgs init{};
+    int rc = build_rhs(pl, kind, alpha, rtol, maxit, &init);
+    if (rc) return rc;
     if (!pl->warm[kind][alpha]) {
         Timed t(pl, FFTGAL_K_CG_SCALAR);
-        HIPCHECK(pl, launch_cg_init(st, pl->at<double>(pl->so(pl->Lo.part_a)), nrr, pl->at<double>(pl->so(pl->Lo.part_b)), nload,
-                                    pl->at<double>(pl->so(pl->Lo.part_c)), 1.0 / npts, rtol, floor_rel, maxit, pl->btol,
-                                    pl->hist(kind, alpha), pl->stream));
-        HIPCHECK(pl, launch_fill_zero(x, vbytes, pl->stream));
-        HIPCHECK(pl, launch_fill_zero(pl->ws + pl->so(pl->Lo.p), vbytes, pl->stream));
-        if (!fp64) HIPCHECK(pl, launch_fill_zero(pl->ws + pl->so(pl->Lo.xbest), vbytes, pl->stream));
+        HIPCHECK(pl, launch_cg_init(init, pl->stream));
+        VecOps v{};
+        start_vectors(pl, kind, alpha, &v);
+        HIPCHECK(pl, launch_vec_ops(v, pl->stream));
         return FFTGAL_OK;
     }
+    // FP32 iterations keep b for the exact energies of the checkpoints
+    if (!fp64) HIPCHECK(pl, launch_copy_vec(pl->ws + pl->so(pl->Lo.bvec), pl->ws + pl->so(pl->Lo.r), vbytes, pl->stream));
+    const int nrr = init.n_rr, nload = init.n_load;
+    const double floor_rel = init.floor_rel;
     // Warm start from the iterate x0 already in x: keep (b, b), |A_M E|^2 and
     // (A_M E).E as scalars, apply the operator to x0, then r_0 = b - K x0.
     pl->warm[kind][alpha] = false;
@@ -1577,6 +1653,29 @@ int run_solve_solo(Plan *pl, int kind, int alpha, int maxit, fftgal_info *info) 
     return finish_solve(pl, kind, alpha, h, info);
 }
 
+// Iterations to enqueue next, from the residual reduction since the previous
+// read of the status (at the first read: since the start): an iteration
+// enqueued past convergence costs its seven no-op launches, one too few a read
+// of the status.
+struct ChunkRate {
+    int it = -1;  // iterations at the previous read (-1: none yet)
+    double rr = 0.0;
+    int next(const CgStatus &h, int chunk) {
+        const double target = std::max(h.tol2 * h.rr0, h.floor2);
+        int n = 2 * chunk;
+        const int i0 = it < 0 ? 0 : it;
+        const double r0v = it < 0 ? h.rr0 : rr;
+        if (h.iter > i0 && h.rr < r0v && h.rr > 0.0 && target > 0.0) {
+            const double rate = std::log(h.rr / r0v) / (h.iter - i0);  // < 0
+            const double remain = std::log(target / h.rr) / rate;
+            n = (int)std::ceil(remain) + 2;
+        }
+        it = h.iter;
+        rr = h.rr;
+        return std::max(2, std::min(n, 64));
+    }
+};
+
 int run_solve(Plan *pl, int kind, int alpha, double rtol, int maxit, fftgal_info *info) {
     const bool fp64 = pl->fp64_iter();
     CgStatus *st = pl->status(kind, alpha);
@@ -1595,9 +1694,7 @@ int run_solve(Plan *pl, int kind, int alpha, double rtol, int maxit, fftgal_info
     CgStatus h{};
     int chunk = 8;
     int enq = 0;
-    int it_prev = 0;
-    double rr_prev = 0.0;
-    bool first = true;
+    ChunkRate rate;
     for (;;) {
         const int todo = std::min(chunk, std::max(0, maxit - enq));
         for (int i = 0; i < todo; ++i) {
@@ -1609,26 +1706,14 @@ int run_solve(Plan *pl, int kind, int alpha, double rtol, int maxit, fftgal_info
         HIPCHECK(pl, hipMemcpyAsync(&h, st, sizeof h, hipMemcpyDeviceToHost, pl->stream));
         HIPCHECK(pl, hipStreamSynchronize(pl->stream));
         if (h.done || enq >= maxit) break;
-        const double target = std::max(h.tol2 * h.rr0, h.floor2);
-        int next = 2 * chunk;
-        // the rate since the previous read (at the first read: since the start,
-        // from the initial residual); an iteration enqueued past convergence
-        // costs its seven no-op launches, one too few a read of the status
-        const int i0 = first ? 0 : it_prev;
-        const double r0v = first ? h.rr0 : rr_prev;
-        if (h.iter > i0 && h.rr < r0v && h.rr > 0.0 && target > 0.0) {
-            const double rate = std::log(h.rr / r0v) / (h.iter - i0);  // < 0
-            const double remain = std::log(target / h.rr) / rate;
-            next = (int)std::ceil(remain) + 2;
-        }
-        first = false;
-        chunk = std::max(2, std::min(next, 64));
-        it_prev = h.iter;
-        rr_prev = h.rr;
+        chunk = rate.next(h, chunk);
     }
     if ((rc = final_checkpoint(pl, kind, alpha, &h))) return rc;
     return finish_solve(pl, kind, alpha, h, info);
 }
+
+int group_solve(Plan *pl, const std::vector<std::pair<int, int>> &jobs, double rtol, int maxit, fftgal_info *info);
+int run_stages(Plan *pl, const std::vector<PassRec> &ps, int width, int cls);
 
 int solve_entry(Plan *pl, int kind, int alpha, double rtol, int maxit, fftgal_info *info) {
     if (!pl) return FFTGAL_EINVAL;
@@ -1639,6 +1724,11 @@ int solve_entry(Plan *pl, int kind, int alpha, double rtol, int maxit, fftgal_in
     int worst = FFTGAL_OK;
     const int a0 = alpha < 0 ? 0 : alpha;
     const int a1 = alpha < 0 ? pl->D.d : alpha + 1;
+    if (a1 - a0 > 1 && pl->at_once > 1 && pl->timing_mask == 0) {
+        std::vector<std::pair<int, int>> jobs;
+        for (int a = a0; a < a1; ++a) jobs.push_back({kind, a});
+        return group_solve(pl, jobs, rtol, maxit, info);
+    }
     for (int a = a0; a < a1; ++a) {
         const int rc = run_solve(pl, kind, a, rtol, maxit, info ? info + (a - a0) : nullptr);
         if (rc == FFTGAL_EDEVICE || rc == FFTGAL_EINVAL) return rc;
@@ -1933,7 +2023,8 @@ int scalar_inclusions(Plan *pl, const fftgal_material *m, std::vector<InclDev> &
     return FFTGAL_OK;
 }
 
-size_t workspace_bytes(int d, const int32_t *N, int precision, const int32_t *P, int scheme) {
+// least: without the copies of the solves run at once (a plan takes either).
+size_t workspace_bytes(int d, const int32_t *N, int precision, const int32_t *P, int scheme, bool least = false) {
     Dims D;
     const bool lean = (precision & FFTGAL_REDUCED_LEAN) != 0;
     const bool tensor = (precision & FFTGAL_TENSOR) != 0;
@@ -1947,8 +2038,10 @@ size_t workspace_bytes(int d, const int32_t *N, int precision, const int32_t *P,
     if (conc && scheme == kSchemeReduced) return 0;
     if (fastg && scheme != kSchemeGa) return 0;
     if (!make_dims(d, N, nullptr, &D, scheme, tensor, fastg)) return 0;
-    const size_t base = make_layout(D, precision, !lean, conc ? 2 * d : 1).total + (conc ? bws_bytes(d) : 0);
-    if (P == nullptr) return base;
+    Layout Lo = make_layout(D, precision, !lean, conc ? 2 * d : 1);
+    if (!least) plan_at_once(D, &Lo);
+    const size_t base = Lo.total + (conc ? bws_bytes(d) : 0);
+    if (P == nullptr) return base + Lo.once_bytes;
     Dims DP;
     if (!make_dims(d, N, P, &DP, scheme, tensor, fastg)) return 0;
     // a plan lays out its regions without P: an image that does not fit them
@@ -1961,7 +2054,8 @@ size_t workspace_bytes(int d, const int32_t *N, int precision, const int32_t *P,
     }
     size_t need_u = 0, need_w = 0;
     voxel_scratch(D, Pv, &need_u, &need_w);
-    return base + align256(entry * 16) + align256(entry * 8) + align256(need_u) + align256(need_w);
+    return base + std::max(Lo.once_bytes,
+                           align256(entry * 16) + align256(entry * 8) + align256(need_u) + align256(need_w));
 }
 
 int make_plan(struct fftgal_plan **out, int d, const int32_t *N, int precision, void *dev_workspace, size_t bytes,
@@ -1992,7 +2086,14 @@ int make_plan(struct fftgal_plan **out, int d, const int32_t *N, int precision, 
     if (dev_workspace == nullptr || (reinterpret_cast<uintptr_t>(dev_workspace) & 255u))
         return fail(nullptr, FFTGAL_EINVAL, "workspace must be a 256-byte aligned device pointer");
     Layout Lo = make_layout(D, precision, !lean, conc ? 2 * d : 1);
-    const size_t bws = conc ? bws_bytes(d) : 0;  // the internal batch of fftgal_solve_all
+    const size_t bws = conc ? bws_bytes(d) : 0;  // the internal batch of the solves run at once
+    // a workspace without room for the copies of the solves run at once is
+    // taken too: the solves then run one after another
+    plan_at_once(D, &Lo);
+    if (bytes < Lo.total + Lo.once_bytes) {
+        Lo.at_once = 1;
+        Lo.once_bytes = 0;
+    }
     if (bytes < Lo.total + bws)
         return fail(nullptr, FFTGAL_ENOMEM, "workspace has %zu bytes, needs %zu", bytes, Lo.total + bws);
     // a larger workspace provisions voxel images up to the largest P that fits
@@ -2005,8 +2106,9 @@ int make_plan(struct fftgal_plan **out, int d, const int32_t *N, int precision, 
     pl->grouped = !lean && D.nshift > 1;
     pl->precision = precision;
     pl->slot_used.assign(Lo.nslots, 0);
-    pl->bws_off = Lo.total;
-    pl->bws_len = bws;
+    pl->at_once = conc ? Lo.nslots : Lo.at_once;
+    pl->bws_off = conc ? Lo.total : Lo.total + Lo.once_bytes - bws_bytes(d);
+    pl->bws_len = conc ? bws : Lo.once_bytes > 0 ? bws_bytes(d) : 0;
     pl->stream = reinterpret_cast<hipStream_t>(hip_stream);
     pl->ws = reinterpret_cast<char *>(dev_workspace);
     pl->ws_bytes = bytes;
@@ -2077,8 +2179,9 @@ int fftgal_plan(struct fftgal_plan **out, int d, const int32_t *N, int precision
 int fftgal_plan_static(struct fftgal_plan **out, int d, const int32_t *N, int precision, void *hip_stream) {
     if (out == nullptr) return fail(nullptr, FFTGAL_EINVAL, "out is NULL");
     *out = nullptr;
-    const size_t need = fftgal_workspace_bytes(d, N, precision);
+    size_t need = fftgal_workspace_bytes(d, N, precision);
     if (need == 0) return fail(nullptr, FFTGAL_EINVAL, "d must be 2 or 3, every N odd and >= 1, precision known");
+    if (need > kStaticBytes) need = workspace_bytes(d, N, precision, nullptr, kSchemeGa, true);
     if (need > kStaticBytes)
         return fail(nullptr, FFTGAL_ENOMEM, "the plan needs %zu bytes; the static workspace holds %zu", need,
                     kStaticBytes);
@@ -2323,30 +2426,37 @@ int fftgal_bounds(struct fftgal_plan *pl, double *upper, double *lower, double *
             st_ss = (long)(pl->vec_bytes() / 16);
         }
         // the energy quadrature on every shifted grid (reduced Ga: the
-        // quadratic form of Lemma reduce_grid), the d^2 sums of shift s in
-        // gram + 16 s, added on the host in shift order
-        for (int i = 0; i < d * d; ++i) gram[kind][i] = 0.0;
+        // quadratic form of Lemma reduce_grid), the d^2 sums of shift s of this
+        // kind in gram + 16 (kind nshift + s), added on the host in shift order
         for (int s = 0; s < D.nshift; ++s) {
+            std::vector<PassRec> ps;
             void *rows = nullptr;
+            pl->capture = &ps;
             int rc = inverse_passes(pl, true, kind, xs, st_ss, d, false, nullptr, &rows, FFTGAL_K_BOUNDS,
                                     FFTGAL_K_BOUNDS, s);
-            if (rc) return rc;
             RowArgs r = base_row(pl, true, ROW_GRAM, rows, kind, s);
             r.ncomp = d * d;
             r.partial = pl->at<double>(pl->so(pl->Lo.part_b));
-            rc = run_row(pl, r, true, FFTGAL_K_BOUNDS);
+            if (!rc) rc = run_row(pl, r, true, FFTGAL_K_BOUNDS);
+            pl->capture = nullptr;
+            if (!rc) rc = run_stages(pl, ps, d, FFTGAL_K_BOUNDS);
             if (rc) return rc;
             Timed t(pl, FFTGAL_K_BOUNDS);
-            HIPCHECK(pl, launch_sum_partials(pl->at<double>(pl->Lo.gram), pl->at<double>(pl->so(pl->Lo.part_b)), row_grid(r),
-                                             d * d, pl->stream));
-            double gs[9];
-            HIPCHECK(pl, hipMemcpyAsync(gs, pl->at<double>(pl->Lo.gram), d * d * 8, hipMemcpyDeviceToHost,
-                                        pl->stream));
-            HIPCHECK(pl, hipStreamSynchronize(pl->stream));
-            for (int i = 0; i < d * d; ++i) gram[kind][i] += gs[i];
+            HIPCHECK(pl, launch_sum_partials(pl->at<double>(pl->Lo.gram) + 16 * (kind * D.nshift + s),
+                                             pl->at<double>(pl->so(pl->Lo.part_b)), row_grid(r), d * d, pl->stream));
         }
-        for (int i = 0; i < d * d; ++i) gram[kind][i] /= (double)D.nshift * D.Mtot;
     }
+    std::vector<double> gs((size_t)32 * D.nshift);
+    HIPCHECK(pl, hipMemcpyAsync(gs.data(), pl->at<double>(pl->Lo.gram), gs.size() * 8, hipMemcpyDeviceToHost,
+                                pl->stream));
+    HIPCHECK(pl, hipStreamSynchronize(pl->stream));
+    pl->stage_host.clear();
+    for (int kind = 0; kind < 2; ++kind)
+        for (int i = 0; i < d * d; ++i) {
+            double g = 0.0;
+            for (int s = 0; s < D.nshift; ++s) g += gs[16 * (kind * D.nshift + s) + i];
+            gram[kind][i] = g / ((double)D.nshift * D.Mtot);
+        }
     double up[9], bh[9], lo[9];
     for (int i = 0; i < d; ++i)
         for (int j = 0; j < d; ++j) {
@@ -2553,6 +2663,8 @@ struct fftgal_batch {
         Plan *pl;
         int kind, alpha, id;
         IterCfg cfg;
+        std::vector<PassRec> rhs;  // internal batch: the right-hand side's passes (empty: already run)
+        InitArgs init{};
         int enq = 0;  // iterations enqueued (FP32 checkpoints every kCkptEvery)
         int slot = 0;  // the plan's solve slot
         bool solo = false;  // iterations in the single work-group solver
@@ -2573,6 +2685,12 @@ struct fftgal_batch {
         PassRec proto;
     };
     std::vector<Group> groups;
+    // internal batch (group_solve): its members start together, and the single
+    // work-group solves run on the batch's own stream
+    bool internal = false;
+    std::vector<Group> rhs_groups;
+    size_t init_off = 0;
+    int n_init = 0;
     struct UGroup {
         bool fp64;
         int np, total;
@@ -2629,47 +2747,79 @@ size_t blob_put(std::vector<unsigned char> &blob, const void *p, size_t n) {
 
 bool pass_fast(const PassRec &r) { return r.type == 0 ? r.pa.fast != 0 : r.ra.fast != 0; }
 
-// Group the members' specialised passes by (pass index, kernel, length,
-// dimension, precision, kernel variant) and lay out their argument tables, work-group
-// offsets, CG update arguments and CG items in one blob; upload it.
+// Group the specialised i-th passes of the given lists by (kernel, length,
+// dimension, precision, kernel variant) and lay out their argument tables and
+// work-group offsets in the blob.
+void group_passes(const std::vector<const std::vector<PassRec> *> &lists, size_t i, std::vector<unsigned char> &blob,
+                  std::vector<Batch::Group> *out) {
+    std::map<std::tuple<int, int, int, int>, std::vector<const PassRec *>> by;
+    for (const auto *ps : lists) {
+        if (i >= ps->size() || !pass_fast((*ps)[i])) continue;
+        const PassRec &r = (*ps)[i];
+        const int n = r.type == 0 ? r.pa.f.n : r.ra.f.n;
+        const int d = r.type == 0 ? r.pa.d : r.ra.d;
+        const int fm = r.type == 0 ? r.pa.fast : r.ra.fast;
+        by[std::make_tuple(r.type, n, d, (int)r.fp64 * 4 + fm)].push_back(&r);
+    }
+    for (auto &kv : by) {
+        const auto &ms = kv.second;
+        const PassRec &proto = *ms[0];
+        const size_t sz = proto.type == 0 ? sizeof(PencilArgs) : sizeof(RowArgs);
+        std::vector<unsigned char> tab(sz * ms.size());
+        std::vector<int> woff(ms.size());
+        int total = 0;
+        for (size_t j = 0; j < ms.size(); ++j) {
+            const PassRec &r = *ms[j];
+            std::memcpy(tab.data() + j * sz, r.type == 0 ? (const void *)&r.pa : (const void *)&r.ra, sz);
+            woff[j] = total;
+            total += r.grid;
+        }
+        Batch::Group g;
+        g.pass = i;
+        g.np = (int)ms.size();
+        g.total = total;
+        g.proto = proto;
+        g.args_off = blob_put(blob, tab.data(), tab.size());
+        g.woff_off = blob_put(blob, woff.data(), woff.size() * sizeof(int));
+        out->push_back(g);
+    }
+}
+
+// Launch a group whose tables lie at `base`, or a pass of the generic kernels.
+hipError_t launch_group(const Batch::Group &g, const char *base, hipStream_t s, LaunchEv ev = LaunchEv{}) {
+    const int *woff = reinterpret_cast<const int *>(base + g.woff_off);
+    if (g.proto.type == 0)
+        return launch_pencil_multi(g.proto.pa, reinterpret_cast<const PencilArgs *>(base + g.args_off), woff, g.np,
+                                   g.total, g.proto.fp64, s, ev);
+    return launch_row_multi(g.proto.ra, reinterpret_cast<const RowArgs *>(base + g.args_off), woff, g.np, g.total,
+                            g.proto.fp64, s, ev);
+}
+hipError_t launch_generic(const PassRec &r, hipStream_t s) {
+    return r.type == 0 ? launch_pencil(r.pa, r.nouter, r.fp64, s) : launch_row(r.ra, r.fp64, s);
+}
+
+// Group the members' specialised passes and lay out their argument tables,
+// work-group offsets, CG update arguments and CG items in one blob; upload it.
 int batch_rebuild(Batch *b) {
     b->blob.clear();
     b->groups.clear();
     b->ugroups.clear();
+    b->rhs_groups.clear();
     const size_t nm = b->members.size();
-    for (size_t i = 0; i < 5; ++i) {
-        std::map<std::tuple<int, int, int, int>, std::vector<size_t>> by;
-        for (size_t m = 0; m < nm; ++m) {
-            const auto &ps = b->members[m].cfg.passes;
-            if (b->members[m].solo || i >= ps.size() || !pass_fast(ps[i])) continue;
-            const PassRec &r = ps[i];
-            const int n = r.type == 0 ? r.pa.f.n : r.ra.f.n;
-            const int d = r.type == 0 ? r.pa.d : r.ra.d;
-            const int fm = r.type == 0 ? r.pa.fast : r.ra.fast;
-            by[std::make_tuple(r.type, n, d, (int)r.fp64 * 4 + fm)].push_back(m);
+    std::vector<const std::vector<PassRec> *> lists;
+    for (const auto &m : b->members)
+        if (!m.solo) lists.push_back(&m.cfg.passes);
+    for (size_t i = 0; i < 5; ++i) group_passes(lists, i, b->blob, &b->groups);
+    if (b->internal) {
+        lists.clear();
+        std::vector<InitArgs> init;
+        for (const auto &m : b->members) {
+            lists.push_back(&m.rhs);
+            if (!m.rhs.empty()) init.push_back(m.init);
         }
-        for (auto &kv : by) {
-            const auto &ms = kv.second;
-            const PassRec &proto = b->members[ms[0]].cfg.passes[i];
-            const size_t sz = proto.type == 0 ? sizeof(PencilArgs) : sizeof(RowArgs);
-            std::vector<unsigned char> tab(sz * ms.size());
-            std::vector<int> woff(ms.size());
-            int total = 0;
-            for (size_t j = 0; j < ms.size(); ++j) {
-                const PassRec &r = b->members[ms[j]].cfg.passes[i];
-                std::memcpy(tab.data() + j * sz, r.type == 0 ? (const void *)&r.pa : (const void *)&r.ra, sz);
-                woff[j] = total;
-                total += r.grid;
-            }
-            Batch::Group g;
-            g.pass = i;
-            g.np = (int)ms.size();
-            g.total = total;
-            g.proto = proto;
-            g.args_off = blob_put(b->blob, tab.data(), tab.size());
-            g.woff_off = blob_put(b->blob, woff.data(), woff.size() * sizeof(int));
-            b->groups.push_back(g);
-        }
+        for (size_t i = 0; i < 3; ++i) group_passes(lists, i, b->blob, &b->rhs_groups);
+        b->n_init = (int)init.size();
+        if (!init.empty()) b->init_off = blob_put(b->blob, init.data(), init.size() * sizeof(InitArgs));
     }
     for (int f = 0; f < 2; ++f) {
         std::vector<UpdArgs> ua;
@@ -2721,6 +2871,216 @@ int batch_rebuild(Batch *b) {
                                 b->stream));
     b->dirty = false;
     return FFTGAL_OK;
+}
+
+// Launches of `iterations` iterations of every member (the tables are built).
+int batch_enqueue(Batch *b, int iterations) {
+    char *base = b->ws + b->blob_base;
+    const CgItem *items = reinterpret_cast<const CgItem *>(base + b->items_off);
+    if (!b->sgroups.empty()) {
+        // single work-group solves: on the side stream, in launches up to the
+        // next FP32 checkpoint of any of them (the checkpoints fall on the same
+        // iteration counts as when solved alone)
+        if (!b->internal) {
+            if (!b->side) {
+                BHIPCHECK(b, hipStreamCreateWithFlags(&b->side, hipStreamNonBlocking));
+                BHIPCHECK(b, hipEventCreateWithFlags(&b->ev_fork, hipEventDisableTiming));
+                BHIPCHECK(b, hipEventCreateWithFlags(&b->ev_join, hipEventDisableTiming));
+            }
+            BHIPCHECK(b, hipEventRecord(b->ev_fork, b->stream));
+            BHIPCHECK(b, hipStreamWaitEvent(b->side, b->ev_fork, 0));
+        }
+        const hipStream_t side = b->internal ? b->stream : b->side;
+        int left = iterations;
+        while (left > 0) {
+            int n = left;
+            for (const auto &m : b->members)
+                if (m.solo && !m.cfg.fp64) n = std::min(n, kCkptEvery - m.enq % kCkptEvery);
+            for (const auto &g : b->sgroups)
+                BHIPCHECK(b, launch_solo(g.proto, reinterpret_cast<const SoloArgs *>(base + g.args_off), g.np, n,
+                                         g.fp64, side));
+            for (auto &m : b->members) {
+                if (!m.solo) continue;
+                m.enq += n;
+                if (m.cfg.fp64 || m.enq % kCkptEvery) continue;
+                m.pl->slot = m.slot;
+                const hipStream_t own = m.pl->stream;
+                m.pl->stream = side;
+                const int rc = checkpoint(m.pl, m.kind, m.alpha, false);
+                m.pl->stream = own;
+                m.pl->slot = 0;
+                if (rc) return bfail(b, rc, "checkpoint failed: %s", m.pl->err.c_str());
+            }
+            left -= n;
+        }
+        if (!b->internal) BHIPCHECK(b, hipEventRecord(b->ev_join, b->side));
+    }
+    for (int it = 0; it < iterations && b->n_items > 0; ++it) {
+        for (size_t i = 0; i < 5; ++i) {
+            for (const auto &g : b->groups) {
+                if (g.pass != i) continue;
+                BHIPCHECK(b, launch_group(g, base, b->stream));
+            }
+            for (auto &m : b->members) {
+                if (m.solo || i >= m.cfg.passes.size() || pass_fast(m.cfg.passes[i])) continue;
+                BHIPCHECK(b, launch_generic(m.cfg.passes[i], b->stream));
+            }
+        }
+        for (const auto &u : b->ugroups)
+            BHIPCHECK(b, launch_cg_update_multi(reinterpret_cast<const UpdArgs *>(base + u.args_off),
+                                                reinterpret_cast<const int *>(base + u.woff_off), u.np, u.total,
+                                                u.fp64, b->stream));
+        BHIPCHECK(b, launch_cg_check_multi(items, b->n_items, b->stream));
+        // FP32 members: best-iterate checkpoints at the same iteration counts
+        // as when solved alone
+        for (auto &m : b->members) {
+            if (m.solo) continue;
+            ++m.enq;
+            if (m.cfg.fp64 || m.enq % kCkptEvery) continue;
+            m.pl->slot = m.slot;
+            const int rc = checkpoint(m.pl, m.kind, m.alpha, false);
+            m.pl->slot = 0;
+            if (rc) return bfail(b, rc, "checkpoint failed: %s", m.pl->err.c_str());
+        }
+    }
+    if (!b->sgroups.empty() && !b->internal) BHIPCHECK(b, hipStreamWaitEvent(b->stream, b->ev_join, 0));
+    return FFTGAL_OK;
+}
+
+// Run captured passes in order, `width` consecutive ones of the same kernel
+// (the solutions of the energy quadrature) in one launch.  The argument tables
+// go up in one copy to the iteration slots, which no solve is using.
+int run_stages(Plan *pl, const std::vector<PassRec> &ps, int width, int cls) {
+    std::vector<std::vector<PassRec>> stages;
+    for (size_t i = 0; i < ps.size();) {
+        const size_t w = i + width <= ps.size() ? width : 1;
+        stages.emplace_back(ps.begin() + i, ps.begin() + i + w);
+        i += w;
+    }
+    std::vector<unsigned char> blob;
+    std::vector<std::vector<Batch::Group>> groups(stages.size());
+    for (size_t k = 0; k < stages.size(); ++k) {
+        std::vector<std::vector<PassRec>> one;  // one list per pass: passes of equal index share a launch
+        for (const auto &r : stages[k]) one.push_back({r});
+        std::vector<const std::vector<PassRec> *> lists;
+        for (const auto &l : one) lists.push_back(&l);
+        group_passes(lists, 0, blob, &groups[k]);
+    }
+    if (blob.size() > (size_t)kIterSlots * kArgSlot) return fail(pl, FFTGAL_EINVAL, "argument tables too large");
+    char *base = pl->iter_slot(0);
+    if (!blob.empty()) {
+        pl->stage_host.push_back(std::move(blob));  // until the caller has waited for the stream
+        const auto &h = pl->stage_host.back();
+        HIPCHECK(pl, hipMemcpyAsync(base, h.data(), h.size(), hipMemcpyHostToDevice, pl->stream));
+    }
+    for (size_t k = 0; k < stages.size(); ++k) {
+        for (const auto &g : groups[k]) {
+            TimedLaunch t(pl, cls);
+            HIPCHECK(pl, launch_group(g, base, pl->stream, t.ev));
+        }
+        for (const auto &r : stages[k]) {
+            if (pass_fast(r)) continue;
+            Timed t(pl, cls);
+            HIPCHECK(pl, launch_generic(r, pl->stream));
+        }
+    }
+    return FFTGAL_OK;
+}
+
+// All `jobs` (kind, alpha) of a plan, at most pl->at_once of them together: the
+// right-hand sides, the iterations and the reads of the status are shared by
+// the solves of a group, so a grid that one solve leaves the GPU idle on costs
+// the launches and waits of one solve (FP64, to bounds: 2D 95 x 67, four
+// solves, 9.7 -> 3.5 ms; 3D order 21, six, 6.9 -> 1.5 ms; 2D order 41, four
+// work-groups side by side, 4.6 -> 1.24 ms; 2D order 1013, two at a time, 43.3
+// -> 36.8 ms).  Every solve keeps its own reductions: its result equals bitwise that of the solve alone.  Returns the
+// first non-OK outcome after all solves ran, or a hard error at once; `info`
+// (may be NULL) receives the outcomes in the order of the jobs.
+int group_solve(Plan *pl, const std::vector<std::pair<int, int>> &jobs, double rtol, int maxit, fftgal_info *info) {
+    const bool fp64 = pl->fp64_iter();
+    int worst = FFTGAL_OK;
+    for (size_t j0 = 0; j0 < jobs.size(); j0 += pl->at_once) {
+        const size_t n = std::min(jobs.size() - j0, (size_t)pl->at_once);
+        Batch b;
+        b.internal = true;
+        b.stream = pl->stream;
+        b.ws = pl->ws + pl->bws_off;
+        b.bytes = pl->bws_len;
+        b.cap = 2 * pl->D.d;
+        b.blob_base = align256((size_t)b.cap * sizeof(CgStatus));
+        VecOps start{};
+        int rc = FFTGAL_OK;
+        const bool solo = use_solo(pl);
+        for (size_t j = 0; j < n && !rc; ++j) {
+            Batch::Member m;
+            m.pl = pl;
+            m.kind = jobs[j0 + j].first;
+            m.alpha = jobs[j0 + j].second;
+            m.slot = (int)j;
+            m.id = (int)j;
+            pl->slot = m.slot;
+            if (pl->warm[m.kind][m.alpha]) {
+                rc = start_solve(pl, m.kind, m.alpha, rtol, maxit);
+            } else {
+                pl->capture = &m.rhs;
+                rc = build_rhs(pl, m.kind, m.alpha, rtol, maxit, &m.init);
+                pl->capture = nullptr;
+                if (!rc) start_vectors(pl, m.kind, m.alpha, &start);
+            }
+            if (!rc) rc = capture_iteration(pl, m.kind, m.alpha, fp64, &m.cfg);
+            if (!rc && solo) {
+                m.solo = true;
+                m.sargs = make_solo(pl, m.kind, m.alpha);
+            }
+            pl->slot = 0;
+            b.members.push_back(std::move(m));
+        }
+        if (rc) return rc;
+        auto bad = [&](int code) { return fail(pl, code, "%s", b.err.c_str()); };
+        if ((rc = batch_rebuild(&b))) return bad(rc);
+        const char *base = b.ws + b.blob_base;
+        for (size_t i = 0; i < 3; ++i) {
+            for (const auto &g : b.rhs_groups)
+                if (g.pass == i) HIPCHECK(pl, launch_group(g, base, pl->stream));
+            for (const auto &m : b.members)
+                if (i < m.rhs.size() && !pass_fast(m.rhs[i])) HIPCHECK(pl, launch_generic(m.rhs[i], pl->stream));
+        }
+        if (b.n_init > 0) {
+            HIPCHECK(pl, launch_cg_init_multi(reinterpret_cast<const InitArgs *>(base + b.init_off), b.n_init,
+                                              pl->stream));
+            HIPCHECK(pl, launch_vec_ops(start, pl->stream));
+        }
+        std::vector<ChunkRate> rate(n);
+        b.mirror_host.resize(n);
+        int chunk = 8, enq = 0;
+        for (;;) {
+            // the single work-group kernel stops by itself: up to the next FP32
+            // checkpoint, or to the end
+            const int want = solo ? (fp64 ? maxit : kCkptEvery) : chunk;
+            const int todo = std::max(1, std::min(want, maxit - enq));
+            if ((rc = batch_enqueue(&b, todo))) return bad(rc);
+            enq += todo;
+            HIPCHECK(pl, hipMemcpyAsync(b.mirror_host.data(), b.ws, n * sizeof(CgStatus), hipMemcpyDeviceToHost,
+                                        pl->stream));
+            HIPCHECK(pl, hipStreamSynchronize(pl->stream));
+            int next = 0;
+            for (size_t j = 0; j < n; ++j)
+                if (!b.mirror_host[j].done) next = std::max(next, rate[j].next(b.mirror_host[j], chunk));
+            if (next == 0 || enq >= maxit) break;
+            chunk = next;
+        }
+        for (size_t j = 0; j < n; ++j) {
+            const Batch::Member &m = b.members[j];
+            CgStatus h = b.mirror_host[j];
+            pl->slot = m.slot;
+            rc = final_checkpoint(pl, m.kind, m.alpha, &h);
+            pl->slot = 0;
+            if (rc) return rc;
+            rc = finish_solve(pl, m.kind, m.alpha, h, info ? info + j0 + j : nullptr);
+            if (rc != FFTGAL_OK && worst == FFTGAL_OK) worst = rc;
+        }
+    }
+    return worst;
 }
 
 }  // namespace
@@ -2808,82 +3168,7 @@ int fftgal_batch_step(struct fftgal_batch *b, int iterations, int *n_active) {
         const int rc = batch_rebuild(b);
         if (rc) return rc;
     }
-    char *base = b->ws + b->blob_base;
-    const CgItem *items = reinterpret_cast<const CgItem *>(base + b->items_off);
-    if (!b->sgroups.empty()) {
-        // single work-group solves: on the side stream, in launches up to the
-        // next FP32 checkpoint of any of them (the checkpoints fall on the same
-        // iteration counts as when solved alone)
-        if (!b->side) {
-            BHIPCHECK(b, hipStreamCreateWithFlags(&b->side, hipStreamNonBlocking));
-            BHIPCHECK(b, hipEventCreateWithFlags(&b->ev_fork, hipEventDisableTiming));
-            BHIPCHECK(b, hipEventCreateWithFlags(&b->ev_join, hipEventDisableTiming));
-        }
-        BHIPCHECK(b, hipEventRecord(b->ev_fork, b->stream));
-        BHIPCHECK(b, hipStreamWaitEvent(b->side, b->ev_fork, 0));
-        int left = iterations;
-        while (left > 0) {
-            int n = left;
-            for (const auto &m : b->members)
-                if (m.solo && !m.cfg.fp64) n = std::min(n, kCkptEvery - m.enq % kCkptEvery);
-            for (const auto &g : b->sgroups)
-                BHIPCHECK(b, launch_solo(g.proto, reinterpret_cast<const SoloArgs *>(base + g.args_off), g.np, n,
-                                         g.fp64, b->side));
-            for (auto &m : b->members) {
-                if (!m.solo) continue;
-                m.enq += n;
-                if (m.cfg.fp64 || m.enq % kCkptEvery) continue;
-                m.pl->slot = m.slot;
-                const hipStream_t own = m.pl->stream;
-                m.pl->stream = b->side;
-                const int rc = checkpoint(m.pl, m.kind, m.alpha, false);
-                m.pl->stream = own;
-                m.pl->slot = 0;
-                if (rc) return bfail(b, rc, "checkpoint failed: %s", m.pl->err.c_str());
-            }
-            left -= n;
-        }
-        BHIPCHECK(b, hipEventRecord(b->ev_join, b->side));
-    }
-    for (int it = 0; it < iterations && b->n_items > 0; ++it) {
-        for (size_t i = 0; i < 5; ++i) {
-            for (const auto &g : b->groups) {
-                if (g.pass != i) continue;
-                const int *woff = reinterpret_cast<const int *>(base + g.woff_off);
-                if (g.proto.type == 0)
-                    BHIPCHECK(b, launch_pencil_multi(g.proto.pa, reinterpret_cast<const PencilArgs *>(base + g.args_off),
-                                                     woff, g.np, g.total, g.proto.fp64, b->stream));
-                else
-                    BHIPCHECK(b, launch_row_multi(g.proto.ra, reinterpret_cast<const RowArgs *>(base + g.args_off),
-                                                  woff, g.np, g.total, g.proto.fp64, b->stream));
-            }
-            for (auto &m : b->members) {
-                if (m.solo || i >= m.cfg.passes.size() || pass_fast(m.cfg.passes[i])) continue;
-                const PassRec &r = m.cfg.passes[i];
-                if (r.type == 0)
-                    BHIPCHECK(b, launch_pencil(r.pa, r.nouter, r.fp64, b->stream));
-                else
-                    BHIPCHECK(b, launch_row(r.ra, r.fp64, b->stream));
-            }
-        }
-        for (const auto &u : b->ugroups)
-            BHIPCHECK(b, launch_cg_update_multi(reinterpret_cast<const UpdArgs *>(base + u.args_off),
-                                                reinterpret_cast<const int *>(base + u.woff_off), u.np, u.total,
-                                                u.fp64, b->stream));
-        BHIPCHECK(b, launch_cg_check_multi(items, b->n_items, b->stream));
-        // FP32 members: best-iterate checkpoints at the same iteration counts
-        // as when solved alone
-        for (auto &m : b->members) {
-            if (m.solo) continue;
-            ++m.enq;
-            if (m.cfg.fp64 || m.enq % kCkptEvery) continue;
-            m.pl->slot = m.slot;
-            const int rc = checkpoint(m.pl, m.kind, m.alpha, false);
-            m.pl->slot = 0;
-            if (rc) return bfail(b, rc, "checkpoint failed: %s", m.pl->err.c_str());
-        }
-    }
-    if (!b->sgroups.empty()) BHIPCHECK(b, hipStreamWaitEvent(b->stream, b->ev_join, 0));
+    if (const int rc = batch_enqueue(b, iterations)) return rc;
     b->mirror_host.resize(nm);
     BHIPCHECK(b, hipMemcpyAsync(b->mirror_host.data(), b->ws, nm * sizeof(CgStatus), hipMemcpyDeviceToHost,
                                 b->stream));
@@ -2953,45 +3238,21 @@ int fftgal_solve_all(struct fftgal_plan *pl, double rtol, int maxit, fftgal_info
     if (!(rtol >= 0.0) || maxit < 0) return fail(pl, FFTGAL_EINVAL, "rtol must be >= 0 and maxit >= 0");
     const int d = pl->D.d;
     auto hard = [](int rc) { return rc == FFTGAL_EDEVICE || rc == FFTGAL_EINVAL || rc == FFTGAL_ESTATE; };
-    if ((int)pl->slot_used.size() < 2 * d || pl->bws_len == 0) {
-        // one solve slot: the d primal, then the d dual solves
+    const bool conc = (int)pl->slot_used.size() >= 2 * d;
+    if (!conc && (pl->at_once < 2 * d || pl->timing_mask != 0)) {
+        // the d primal, then the d dual solves
         const int r1 = solve_entry(pl, KIND_E, -1, rtol, maxit, info);
         if (hard(r1)) return r1;
         const int r2 = solve_entry(pl, KIND_J, -1, rtol, maxit, info ? info + d : nullptr);
         if (hard(r2)) return r2;
         return r1 != FFTGAL_OK ? r1 : r2;
     }
-    // all 2d solves as members of one batch: every launch of an iteration
-    // covers all of them; each keeps its own reductions, so the results equal
-    // those of the solves run one after another
-    Batch *b = nullptr;
-    int rc = fftgal_batch_create(&b, 2 * d, pl->ws + pl->bws_off, pl->bws_len, pl->stream);
-    if (rc) return fail(pl, rc, "internal batch: %s", fftgal_last_error(nullptr));
-    int ids[6];
-    for (int k = 0; k < 2 && !rc; ++k)
-        for (int a = 0; a < d && !rc; ++a) {
-            rc = fftgal_batch_add(b, pl, k, a, rtol, maxit, &ids[k * d + a]);
-            if (rc) fail(pl, rc, "internal batch: %s", b->err.c_str());
-        }
-    int active = rc ? 0 : 2 * d;
-    while (!rc && active > 0) {
-        rc = fftgal_batch_step(b, 16, &active);
-        if (rc) fail(pl, rc, "internal batch: %s", b->err.c_str());
-    }
-    int worst = FFTGAL_OK;
-    int sid = 0, st = 0;
-    fftgal_info inf{};
-    while (fftgal_batch_poll(b, &sid, &inf, &st)) {
-        for (int j = 0; j < 2 * d; ++j)
-            if (ids[j] == sid) {
-                if (info) info[j] = inf;
-                if (st != FFTGAL_OK && worst == FFTGAL_OK) worst = st;
-            }
-    }
-    fftgal_batch_destroy(b);
-    if (rc) return rc;
-    if (worst == FFTGAL_EBREAKDOWN) return fail(pl, worst, "CG breakdown (non-SPD or non-finite material)");
-    if (worst == FFTGAL_ENOTCONV) return fail(pl, worst, "a solve did not converge (see info)");
+    std::vector<std::pair<int, int>> jobs;
+    for (int k = 0; k < 2; ++k)
+        for (int a = 0; a < d; ++a) jobs.push_back({k, a});
+    const int worst = group_solve(pl, jobs, rtol, maxit, info);
+    if (conc && worst == FFTGAL_EBREAKDOWN) return fail(pl, worst, "CG breakdown (non-SPD or non-finite material)");
+    if (conc && worst == FFTGAL_ENOTCONV) return fail(pl, worst, "a solve did not converge (see info)");
     return worst;
 }
 

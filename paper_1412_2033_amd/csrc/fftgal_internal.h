@@ -327,9 +327,28 @@ hipError_t launch_tensor_check(const double *img, long n, int d, double *part, i
 // out[i] = entry (a, b) of voxel i's matrix, or of its inverse (invert = 1).
 hipError_t launch_tensor_component(const double *img, long n, int d, int a, int b, int invert, double *out,
                                    hipStream_t s);
-hipError_t launch_cg_init(CgStatus *st, const double *rr_part, int n_rr, const double *load_part, int n_load,
-                          const double *work_part, double inv_mtot, double tol, double floor_rel, int maxit,
-                          double btol, double *hist, hipStream_t s);
+// Start of a solve from e_0 = 0: sums of the right-hand side's partials into the status.
+struct InitArgs {
+    CgStatus *st;
+    const double *rr_part, *load_part, *work_part;
+    int n_rr, n_load;
+    double inv_mtot, tol, floor_rel, btol;
+    int maxit;
+    double *hist;
+};
+hipError_t launch_cg_init(const InitArgs &a, hipStream_t s);
+hipError_t launch_cg_init_multi(const InitArgs *args, int np, hipStream_t s);
+// Up to kVecOps copies (src set) or clears (src null) of word-aligned vectors in one launch.
+constexpr int kVecOps = 24;
+struct VecOps {
+    struct Op {
+        void *dst;
+        const void *src;
+        unsigned long long words;
+    } op[kVecOps];
+    int n = 0;
+};
+hipError_t launch_vec_ops(const VecOps &ops, hipStream_t s);
 // Multi-problem launches: `args` and `woff` are device arrays; problem i
 // owns work-groups [woff[i], woff[i + 1]) of a grid of `total` work-groups.
 // Optional pair of events that a dispatch records itself at its start and at

@@ -918,13 +918,14 @@ __device__ double sum_fixed(const double *part, int n) {
 
 // hist[0] = (r_0, r_0); hist[1] = the energy (A_M E, E) of the initial iterate
 // e_0 = 0 (the Voigt entry), from the right-hand side pass's sums of (A_M E).E.
-__global__ __launch_bounds__(kThreads) void cg_init_kernel(CgStatus *st, const double *rr_part, int n_rr,
-                                                           const double *load_part, int n_load,
-                                                           const double *work_part, double inv_mtot, double tol,
-                                                           double floor_rel, int maxit, double btol, double *hist) {
-    const double rr = sum_fixed(rr_part, n_rr);
-    const double load = sum_fixed(load_part, n_load);
-    const double work = work_part != nullptr ? sum_fixed(work_part, n_load) : 0.0;
+__device__ void cg_init(const InitArgs &a) {
+    CgStatus *st = a.st;
+    double *hist = a.hist;
+    const double inv_mtot = a.inv_mtot, tol = a.tol, floor_rel = a.floor_rel, btol = a.btol;
+    const int maxit = a.maxit;
+    const double rr = sum_fixed(a.rr_part, a.n_rr);
+    const double load = sum_fixed(a.load_part, a.n_load);
+    const double work = a.work_part != nullptr ? sum_fixed(a.work_part, a.n_load) : 0.0;
     if (threadIdx.x == 0) {
         st->rr = rr;
         st->rr0 = rr;
@@ -956,6 +957,9 @@ __global__ __launch_bounds__(kThreads) void cg_init_kernel(CgStatus *st, const d
         }
     }
 }
+
+__global__ __launch_bounds__(kThreads) void cg_init_kernel(InitArgs a) { cg_init(a); }
+__global__ __launch_bounds__(kThreads) void cg_init_multi_kernel(const InitArgs *a) { cg_init(a[blockIdx.x]); }
 
 // Warm start from an admissible initial iterate x0 (Remark CG: CG from an
 // initial approximation in the minimisation space): r_0 = b - K x0 with r
@@ -1077,6 +1081,14 @@ __global__ __launch_bounds__(kThreads) void prolong_kernel(const Vt<TS> *src, Vt
 __global__ void fill_zero_kernel(unsigned int *p, size_t nwords) {
     for (size_t i = blockIdx.x * (size_t)blockDim.x + threadIdx.x; i < nwords; i += (size_t)gridDim.x * blockDim.x)
         p[i] = 0u;
+}
+
+__global__ __launch_bounds__(kThreads) void vec_ops_kernel(VecOps v) {
+    const VecOps::Op &o = v.op[blockIdx.y];
+    unsigned int *d = static_cast<unsigned int *>(o.dst);
+    const unsigned int *s = static_cast<const unsigned int *>(o.src);
+    for (size_t i = blockIdx.x * (size_t)kThreads + threadIdx.x; i < o.words; i += (size_t)gridDim.x * kThreads)
+        d[i] = s != nullptr ? s[i] : 0u;
 }
 
 __global__ void f2d_kernel(double *dst, const float *src, size_t n) {
@@ -2165,11 +2177,22 @@ hipError_t launch_copy_vec(void *dst, const void *src, size_t bytes, hipStream_t
     return hipGetLastError();
 }
 
-hipError_t launch_cg_init(CgStatus *st, const double *rr_part, int n_rr, const double *load_part, int n_load,
-                          const double *work_part, double inv_mtot, double tol, double floor_rel, int maxit,
-                          double btol, double *hist, hipStream_t s) {
-    hipLaunchKernelGGL(cg_init_kernel, dim3(1), dim3(kThreads), 0, s, st, rr_part, n_rr, load_part, n_load, work_part,
-                       inv_mtot, tol, floor_rel, maxit, btol, hist);
+hipError_t launch_cg_init(const InitArgs &a, hipStream_t s) {
+    hipLaunchKernelGGL(cg_init_kernel, dim3(1), dim3(kThreads), 0, s, a);
+    return hipGetLastError();
+}
+
+hipError_t launch_cg_init_multi(const InitArgs *args, int np, hipStream_t s) {
+    hipLaunchKernelGGL(cg_init_multi_kernel, dim3(np), dim3(kThreads), 0, s, args);
+    return hipGetLastError();
+}
+
+hipError_t launch_vec_ops(const VecOps &ops, hipStream_t s) {
+    size_t most = 0;
+    for (int i = 0; i < ops.n; ++i) most = std::max<size_t>(most, ops.op[i].words);
+    if (most == 0) return hipSuccess;
+    const int nb = (int)std::min<size_t>((most + kThreads - 1) / kThreads, 2048);
+    hipLaunchKernelGGL(vec_ops_kernel, dim3(nb, ops.n), dim3(kThreads), 0, s, ops);
     return hipGetLastError();
 }
 

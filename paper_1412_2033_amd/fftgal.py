@@ -445,12 +445,11 @@ class Plan:
         self.set_material(micro)
         if warm_from is not None:
             self.warm_start(warm_from)
+        ip, idl, code = fftgal_solve_all(self.handle, self.d, rtol, maxit)
         if self.concurrent:
-            ip, idl, code = fftgal_solve_all(self.handle, self.d, rtol, maxit)
             cp = cd = code
-        else:
-            ip, cp = self.solve_primal(-1, rtol, maxit)
-            idl, cd = self.solve_dual(-1, rtol, maxit)
+        else:  # the outcome of each side: OK or ENOTCONV
+            cp, cd = (0 if all(i["converged"] for i in infos) else -4 for infos in (ip, idl))
         up, lo, gap = self.bounds()
         return {"upper": up, "lower": lo, "gap": gap, "info_primal": ip, "info_dual": idl,
                 "status_primal": cp, "status_dual": cd}
