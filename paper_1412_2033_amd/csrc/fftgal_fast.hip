@@ -7,6 +7,152 @@
 namespace fftgal {
 namespace {
 
+// ---- transforms in LDS: the stages in order, and transposed in reverse order ----
+constexpr bool palindromic(int fi) {
+    const int s = kFastSched[fi].nst;
+    for (int i = 0; i < s; ++i)
+        if (kFastSched[fi].r[i] != kFastSched[fi].r[s - 1 - i]) return false;
+    return true;
+}
+constexpr int sched_p(int fi, int st) {
+    int p = 1;
+    for (int i = 0; i < st; ++i) p *= kFastSched[fi].r[i];
+    return p;
+}
+constexpr int sched_off(int fi, int st) {
+    int off = 0, p = 1;
+    for (int i = 0; i < st; ++i) {
+        off += (kFastSched[fi].r[i] - 1) * p;
+        p *= kFastSched[fi].r[i];
+    }
+    return off;
+}
+template <typename T, int FI, int S, int SEND, int NB, int NT, bool ROWL = true>
+__device__ __forceinline__ void fft_mid(Vt<T> *X, const Vt<T> *tw, T sg) {
+    if constexpr (S < SEND) {
+        stage_ip<T, kFastSched[FI].r[S], kFastSched[FI].n, sched_p(FI, S), NB, ROWL, NT>(X, tw + sched_off(FI, S), sg);
+        fft_mid<T, FI, S + 1, SEND, NB, NT, ROWL>(X, tw, sg);
+    }
+}
+
+// One in-place stage of the transposed flow: butterfly i reads (i - k) R + k + q P,
+// transforms, applies the twiddles and writes i + q N / R.
+template <typename T, int R, int N, int P, int NB, int NT, bool ROWL = true>
+__device__ __forceinline__ void stage_tr(Vt<T> *X, const Vt<T> *__restrict__ tw, T sg) {
+    constexpr int TQ = N / R;
+    constexpr int TOT = TQ * NB;
+    constexpr int PER = (TOT + NT - 1) / NT;
+    Vt<T> u[PER][R];
+#pragma unroll
+    for (int t = 0; t < PER; ++t) {
+        const int idx = threadIdx.x + t * NT;
+        if (PER * NT == TOT || idx < TOT) {
+            const int b = ROWL ? idx / TQ : idx % NB, i = ROWL ? idx % TQ : idx / NB;
+            const int k = i % P;
+            const int j = (i - k) * R + k;
+#pragma unroll
+            for (int q = 0; q < R; ++q) u[t][q] = ROWL ? X[b * N + j + q * P] : X[(j + q * P) * NB + b];
+        }
+    }
+    __syncthreads();
+#pragma unroll
+    for (int t = 0; t < PER; ++t) {
+        const int idx = threadIdx.x + t * NT;
+        if (PER * NT == TOT || idx < TOT) {
+            const int b = ROWL ? idx / TQ : idx % NB, i = ROWL ? idx % TQ : idx / NB;
+            dftn<T, R>(u[t], sg);
+            if constexpr (P > 1) {
+                const int k = i % P;
+#pragma unroll
+                for (int q = 1; q < R; ++q) {
+                    Vt<T> w = tw[(q - 1) * P + k];
+                    w.y *= -sg;
+                    u[t][q] = cmul(u[t][q], w);
+                }
+            }
+#pragma unroll
+            for (int q = 0; q < R; ++q) {
+                if (ROWL)
+                    X[b * N + i + q * TQ] = u[t][q];
+                else
+                    X[(i + q * TQ) * NB + b] = u[t][q];
+            }
+        }
+    }
+    __syncthreads();
+}
+
+// Stages S .. S1 of the transposed flow, downwards.
+template <typename T, int FI, int S, int NB, int NT, int S1 = 0, bool ROWL = true>
+__device__ __forceinline__ void fft_tr(Vt<T> *X, const Vt<T> *tw, T sg) {
+    if constexpr (S >= S1) {
+        stage_tr<T, kFastSched[FI].r[S], kFastSched[FI].n, sched_p(FI, S), NB, NT, ROWL>(X, tw + sched_off(FI, S), sg);
+        fft_tr<T, FI, S - 1, NB, NT, S1, ROWL>(X, tw, sg);
+    }
+}
+
+// ---- Bluestein transforms (FftDesc): NB circular convolutions of length L = N ----
+// Convolution lengths with Bluestein kernels: those of the non-smooth transform
+// lengths from 11 on.
+constexpr bool has_blue(int fi, int d) {
+    return kFastSched[fi].n >= 21 && (d == 2 || kFastSched[fi].n <= kMaxFast3);
+}
+
+// The last forward stage, the product with the filter for the sign sg, and
+// the first stage of the transposed way back: all on the thread's own points.
+template <typename T, int FI, int NB, int NT, bool ROWL>
+__device__ __forceinline__ void blue_mid(Vt<T> *X, const Vt<T> *__restrict__ tw, const Vt<T> *__restrict__ H, T sg) {
+    constexpr int N = kFastSched[FI].n, S = kFastSched[FI].nst, R = kFastSched[FI].r[S - 1];
+    constexpr int TQ = N / R, OFF = sched_off(FI, S - 1);
+    constexpr int TOT = TQ * NB;
+    for (int idx = threadIdx.x; idx < TOT; idx += NT) {
+        const int b = ROWL ? idx / TQ : idx % NB, i = ROWL ? idx % TQ : idx / NB;
+        Vt<T> *x = ROWL ? X + b * N + i : X + i * NB + b;
+        constexpr int LS = ROWL ? TQ : TQ * NB;
+        Vt<T> u[R];
+#pragma unroll
+        for (int q = 0; q < R; ++q) u[q] = x[q * LS];
+#pragma unroll
+        for (int q = 1; q < R; ++q) u[q] = cmul(u[q], tw[OFF + (q - 1) * TQ + i]);
+        dftn<T, R>(u, T(-1));
+#pragma unroll
+        for (int q = 0; q < R; ++q) {
+            const int k = i + q * TQ;  // H_k, or conj(H_{-k}) for sg = -1
+            Vt<T> h = H[sg > T(0) || k == 0 ? k : N - k];
+            h.y *= sg;
+            u[q] = cmul(u[q], h);
+        }
+        dftn<T, R>(u, T(1));
+#pragma unroll
+        for (int q = 1; q < R; ++q) {
+            Vt<T> w = tw[OFF + (q - 1) * TQ + i];
+            w.y = -w.y;
+            u[q] = cmul(u[q], w);
+        }
+#pragma unroll
+        for (int q = 0; q < R; ++q) x[q * LS] = u[q];
+    }
+    __syncthreads();
+}
+
+// The convolution of inputs already multiplied by the chirp and padded with
+// zeros; the outputs still need the chirp.  S1 > 0 leaves the transposed
+// stages below S1 to the caller.
+template <typename T, int FI, int NB, int NT, bool ROWL, int S0 = 0, int S1 = 0>
+__device__ __forceinline__ void blue_conv(Vt<T> *X, const Vt<T> *tw, const Vt<T> *H, T sg) {
+    constexpr int S = kFastSched[FI].nst;
+    fft_mid<T, FI, S0, S - 1, NB, NT, ROWL>(X, tw, T(-1));
+    blue_mid<T, FI, NB, NT, ROWL>(X, tw, H, sg);
+    fft_tr<T, FI, S - 2, NB, NT, S1, ROWL>(X, tw, T(1));
+}
+
+// c_m = exp(sg i pi m^2 / n)
+template <typename T> __device__ __forceinline__ Vt<T> chirp_at(const Vt<T> *chirp, int m, T sg) {
+    Vt<T> c = chirp[m];
+    c.y *= sg;
+    return c;
+}
+
 // row pairs per work-group of the specialised anisotropic row pass so that
 // one batch of all d components stays within 24 KB of LDS (the passes are
 // latency-bound: smaller work-groups put more of them on a CU)
@@ -31,7 +177,16 @@ constexpr int fast_batch(int n, int es, int d) {
 // points (order 365) take 3 pencils with 512 threads (486 of the 2 x 3 x 81
 // radix-9 butterflies busy in one round, against two rounds for 2 pencils and
 // 256 threads): a batch of 16 such solves 7 % faster.
-constexpr int pencil_batch(int n, int es, int d) {
+// Bluestein tiles: up to 8 pencils within 24 KB for the short lengths (their
+// grids are small), 48 KB for the others, whose two transforms per pencil need
+// the lanes.
+constexpr int pencil_batch(int n, int es, int d, bool blue = false) {
+    if (blue) {
+        const int most = n <= 105 ? 24 * 1024 : 48 * 1024;
+        int b = 8;
+        while (b > 1 && d * b * n * es > most) b /= 2;
+        return b;
+    }
     if (d == 3 && n == 225) return es >= 16 ? 7 : 9;
     if (es < 16 && d == 2 && n == 729) return 3;
     const int cap = (es >= 16 && d == 3 && n > 225) ? 48 * 1024 : 24 * 1024;
@@ -45,19 +200,23 @@ constexpr int pencil_batch(int n, int es, int d) {
 // tiles of 729 points and the 3D tiles of 225 points (315 or 405 transforms of
 // 15 points per stage), so that every stage of the transform takes one round
 // of the threads; else 256
-constexpr int pencil_nt(int n, int es, int d) {
+constexpr int pencil_nt(int n, int es, int d, bool blue = false) {
+    if (blue) return n >= 1125 ? 512 : kThreads;
     return ((es >= 16 && d == 2 && n >= 2025) || (es < 16 && d == 2 && n == 729) || (d == 3 && n == 225))
                ? 512
                : kThreads;
 }
 
-template <typename T, int FI, int D>
-__global__ __launch_bounds__(pencil_nt(kFastSched[FI].n, sizeof(Vt<T>), D))
+// BLUE: Bluestein transforms of the length a.f.n through the convolution
+// length N; the inputs are multiplied by the chirp on their way into LDS, the
+// outputs on their way out.
+template <typename T, int FI, int D, bool BLUE>
+__global__ __launch_bounds__(pencil_nt(kFastSched[FI].n, sizeof(Vt<T>), D, BLUE))
 void pencil_fast(const PencilArgs *__restrict__ pa, const int *__restrict__ woff, int np) {
     using V = Vt<T>;
     constexpr int N = kFastSched[FI].n;
-    constexpr int NT = pencil_nt(N, sizeof(V), D);
-    constexpr int B = pencil_batch(N, sizeof(V), D);
+    constexpr int NT = pencil_nt(N, sizeof(V), D, BLUE);
+    constexpr int B = pencil_batch(N, sizeof(V), D, BLUE);
     constexpr int NB = D * B;  // LDS layout [pos][component][batch]
     constexpr int LPI = NT / NB;  // positions per step of the plain prologue / epilogue
     int lb;
@@ -76,6 +235,10 @@ void pencil_fast(const PencilArgs *__restrict__ pa, const int *__restrict__ woff
     const T sg = T(a.sgn);
     const T scale = T(a.scale);
     const V zero = mk<T>(T(0), T(0));
+    const int n = BLUE ? a.f.n : N;  // transform length
+    const V *chirp = reinterpret_cast<const V *>(a.tw) + a.f.choff;
+    const V *H = reinterpret_cast<const V *>(a.tw) + a.f.hoff;
+    auto place = [&](int k) { return BLUE ? (k < 0 ? k + n : k) : posmod(k, N); };  // position of frequency k
     // pencil b0 + bb sits at (b0 + bb) / Nh, (b0 + bb) % Nh: one division per
     // work-group, then at most one carry per pencil (B <= Nh is not assumed)
     const int q0 = b0 / a.Nh, r0 = b0 - q0 * a.Nh;
@@ -110,6 +273,12 @@ void pencil_fast(const PencilArgs *__restrict__ pa, const int *__restrict__ woff
     // compile-time bounds: inputs of at most (N + 1) / 2 points (zero-padded
     // transforms) or of N points.
     const int khi = (a.L_in + 1) / 2;
+    // zero position z of the N - L_in ones (BLUE: the high input frequencies
+    // end at n - 1, and n .. N - 1 are zeros too)
+    auto zpos = [&](int z) {
+        const int p = khi + z;
+        return BLUE && p >= n - (a.L_in - khi) ? p + (a.L_in - khi) : p;
+    };
     if (a.pro == PRO_EXPAND) {
       // the CG vectors hold at most (N + 1) / 2 frequencies per axis (Ga), or N
       // (GaNi, transforms on the grid of the approximation order itself)
@@ -138,7 +307,12 @@ void pencil_fast(const PencilArgs *__restrict__ pa, const int *__restrict__ woff
                 by[t][c] = vb.y;
             }
         }
-        for (int idx = threadIdx.x; idx < (N - a.L_in) * NB; idx += NT) X[khi * NB + idx] = zero;
+        for (int idx = threadIdx.x; idx < (N - a.L_in) * NB; idx += NT) {
+            if constexpr (BLUE)
+                X[zpos(idx / NB) * NB + idx % NB] = zero;
+            else
+                X[khi * NB + idx] = zero;
+        }
 #pragma unroll
         for (int t = 0; t < PE; ++t) {
             const int idx = threadIdx.x + t * NT;
@@ -146,7 +320,7 @@ void pencil_fast(const PencilArgs *__restrict__ pa, const int *__restrict__ woff
             const int l = idx / B;
             if (idx >= a.L_in * B) continue;
             if (bb >= nbw) {  // idle pencil of a ragged tile
-                const int pos = posmod(wrapi(l, a.L_in), N);
+                const int pos = place(wrapi(l, a.L_in));
 #pragma unroll
                 for (int al = 0; al < D; ++al) X[pos * NB + al * B + bb] = zero;
                 continue;
@@ -168,7 +342,7 @@ void pencil_fast(const PencilArgs *__restrict__ pa, const int *__restrict__ woff
                     }
                 }
             }
-            const int pos = posmod(k1, N);
+            const int pos = place(k1);
             double pc = 1.0, ps = 0.0;
             if (has_shift(a)) shift_phase(a, k1, k2, k3, &pc, &ps);
 #pragma unroll
@@ -186,14 +360,16 @@ void pencil_fast(const PencilArgs *__restrict__ pa, const int *__restrict__ woff
                     ey = ex * T(ps) + ey * T(pc);
                     ex = nx;
                 }
-                X[pos * NB + al * B + bb] = mk<T>(ex, ey);
+                V v1 = mk<T>(ex, ey);
+                if constexpr (BLUE) v1 = cmul(v1, chirp_at<T>(chirp, pos, sg));
+                X[pos * NB + al * B + bb] = v1;
             }
         }
       };
-      if (2 * a.L_in <= N + 1)
+      if (BLUE || 2 * a.L_in <= N + 1)
           expand(std::integral_constant<int, (N + 1) / 2>{});
       else
-          expand(std::integral_constant<int, N>{});
+          expand(std::integral_constant<int, BLUE ? 1 : N>{});
     } else {
         // every thread owns one LDS slot rr (component c, pencil bb) of LPI
         // positions per step, so its addresses advance by a constant stride;
@@ -217,21 +393,29 @@ void pencil_fast(const PencilArgs *__restrict__ pa, const int *__restrict__ woff
                 vy[t] = ok ? v.y : T(0);
             }
             const int nz = N - a.L_in;  // zero band: positions khi .. khi + nz - 1
-            for (int l = l0; act && l < nz; l += LPI) X[(khi + l) * NB + rr] = zero;
+            for (int l = l0; act && l < nz; l += LPI) X[zpos(l) * NB + rr] = zero;
 #pragma unroll
             for (int t = 0; t < P; ++t) {
                 const int l = l0 + t * LPI;
-                if (act && l < a.L_in) X[posmod(wrapi(l, a.L_in), N) * NB + rr] = mk<T>(vx[t], vy[t]);
+                if (act && l < a.L_in) {
+                    const int pos = place(wrapi(l, a.L_in));
+                    V v1 = mk<T>(vx[t], vy[t]);
+                    if constexpr (BLUE) v1 = cmul(v1, chirp_at<T>(chirp, pos, sg));
+                    X[pos * NB + rr] = v1;
+                }
             }
         };
-        if (2 * a.L_in <= N + 1)
+        if (BLUE || 2 * a.L_in <= N + 1)
             load(std::integral_constant<int, (N + 1) / 2>{});
         else
-            load(std::integral_constant<int, N>{});
+            load(std::integral_constant<int, BLUE ? 1 : N>{});
     }
     __syncthreads();
     __builtin_amdgcn_s_setprio(0);
-    fft_ip<T, FI, 0, 1, 0, NB, false, NT>(X, tw, sg);
+    if constexpr (BLUE)
+        blue_conv<T, FI, NB, NT, false>(X, tw, H, sg);
+    else
+        fft_ip<T, FI, 0, 1, 0, NB, false, NT>(X, tw, sg);
     auto *out = gbl(reinterpret_cast<V *>(a.out));
     if (a.epi == EPI_PROJECT) {
       // the projected vector holds at most (N + 1) / 2 frequencies per axis (Ga) or N (GaNi)
@@ -266,10 +450,15 @@ void pencil_fast(const PencilArgs *__restrict__ pa, const int *__restrict__ woff
             freq(l, a.L_out, bb, &k1, &k2, &k3);
             T tb[2][3];
             const int nt = basis<T>(D, a.kind, k1, k2, k3, tb);
-            const int pos = posmod(k1, N);
+            const int pos = place(k1);
             V y[D];
 #pragma unroll
             for (int al = 0; al < D; ++al) y[al] = X[pos * NB + al * B + bb];
+            if constexpr (BLUE) {
+                const V ch = chirp_at<T>(chirp, pos, sg);
+#pragma unroll
+                for (int al = 0; al < D; ++al) y[al] = cmul(y[al], ch);
+            }
             const double w = (D == 3 ? k3 : k2) == 0 ? 1.0 : 2.0;  // half spectrum: k_d > 0 counts twice
             double pc = 1.0, ps = 0.0;
             if (has_shift(a)) shift_phase(a, k1, k2, k3, &pc, &ps);
@@ -307,8 +496,8 @@ void pencil_fast(const PencilArgs *__restrict__ pa, const int *__restrict__ woff
         }
         return part;
       };
-      const double part = (2 * a.L_out <= N + 1) ? project(std::integral_constant<int, (N + 1) / 2>{})
-                                                 : project(std::integral_constant<int, N>{});
+      const double part = (BLUE || 2 * a.L_out <= N + 1) ? project(std::integral_constant<int, (N + 1) / 2>{})
+                                                         : project(std::integral_constant<int, BLUE ? 1 : N>{});
         const double s = block_sum_t<NT>(part);
         if (threadIdx.x == 0) a.partial[lb] = s;
     } else {
@@ -318,7 +507,9 @@ void pencil_fast(const PencilArgs *__restrict__ pa, const int *__restrict__ woff
         if (threadIdx.x < LPI * NB && bb < nbw) {
             auto *ob = out + (long)c * a.out_cs + (long)o * a.out_os + b0 + bb;
             for (int l = threadIdx.x / NB; l < a.L_out; l += LPI) {
-                V v = X[posmod(wrapi(l, a.L_out), N) * NB + rr];
+                const int pos = place(wrapi(l, a.L_out));
+                V v = X[pos * NB + rr];
+                if constexpr (BLUE) v = cmul(v, chirp_at<T>(chirp, pos, sg));
                 v.x *= scale;
                 v.y *= scale;
                 gst(ob + (long)l * a.out_ls, v);
@@ -538,25 +729,6 @@ __global__ __launch_bounds__(kThreads) void row_fast(const RowArgs *__restrict__
 // material multiply is applied and the first forward stage (same radix, same
 // points) follows in registers.  Only the middle stages, the exchanges
 // between stages and the final Hermitian unpacking go through LDS.
-constexpr bool palindromic(int fi) {
-    const int s = kFastSched[fi].nst;
-    for (int i = 0; i < s; ++i)
-        if (kFastSched[fi].r[i] != kFastSched[fi].r[s - 1 - i]) return false;
-    return true;
-}
-constexpr int sched_p(int fi, int st) {
-    int p = 1;
-    for (int i = 0; i < st; ++i) p *= kFastSched[fi].r[i];
-    return p;
-}
-constexpr int sched_off(int fi, int st) {
-    int off = 0, p = 1;
-    for (int i = 0; i < st; ++i) {
-        off += (kFastSched[fi].r[i] - 1) * p;
-        p *= kFastSched[fi].r[i];
-    }
-    return off;
-}
 // transforms per work-group and work-group size: every thread of the first
 // and last stages owns one butterfly of radix r[0]
 constexpr int iso_tb(int fi) {
@@ -572,8 +744,8 @@ constexpr int iso_nt(int fi) {
 
 constexpr bool has_iso(int fi) { return fi < kNumGridLengths && palindromic(fi); }
 constexpr bool has_staged(int fi) { return has_iso(fi) && kFastSched[fi].nst == 2; }
-constexpr size_t pencil_lds(int n, int es, int d) {
-    return (size_t)es * ((size_t)n * d * pencil_batch(n, es, d) + tw_lds_entries(n, es));
+constexpr size_t pencil_lds(int n, int es, int d, bool blue = false) {
+    return (size_t)es * ((size_t)n * d * pencil_batch(n, es, d, blue) + tw_lds_entries(n, es));
 }
 constexpr size_t row_lds(int n, int es, int d) {
     return (size_t)es * ((size_t)n * d * fast_batch(n, es, d) + tw_lds_entries(n, es));
@@ -582,15 +754,6 @@ template <typename T> constexpr size_t iso_lds(int fi) {
     const int n = kFastSched[fi].n;
     if (kFastSched[fi].nst == 2) return sizeof(T) * (size_t)iso_tb(fi) * n + sizeof(Vt<T>) * n;
     return sizeof(Vt<T>) * ((size_t)iso_tb(fi) * n + tw_lds_entries(n, sizeof(Vt<T>)));
-}
-
-template <typename T, int FI, int S, int SEND, int NB, int NT>
-__device__ __forceinline__ void fft_mid(Vt<T> *X, const Vt<T> *tw, T sg) {
-    if constexpr (S < SEND) {
-        stage_ip<T, kFastSched[FI].r[S], kFastSched[FI].n, sched_p(FI, S), NB, true, NT>(X, tw + sched_off(FI, S),
-                                                                                          sg);
-        fft_mid<T, FI, S + 1, SEND, NB, NT>(X, tw, sg);
-    }
 }
 
 template <typename T, int FI>
@@ -1373,56 +1536,6 @@ constexpr size_t pairs_lds(int fi, int es, int d) {
     return (size_t)es * n * pairs_tb(n, es, d) + es * tw_lds_entries(n, es) + g;
 }
 
-// One in-place stage of the transposed flow: butterfly i reads (i - k) R + k + q P,
-// transforms, applies the twiddles and writes i + q N / R.
-template <typename T, int R, int N, int P, int NB, int NT>
-__device__ __forceinline__ void stage_tr(Vt<T> *X, const Vt<T> *__restrict__ tw, T sg) {
-    constexpr int TQ = N / R;
-    constexpr int TOT = TQ * NB;
-    constexpr int PER = (TOT + NT - 1) / NT;
-    Vt<T> u[PER][R];
-#pragma unroll
-    for (int t = 0; t < PER; ++t) {
-        const int idx = threadIdx.x + t * NT;
-        if (PER * NT == TOT || idx < TOT) {
-            const int b = idx / TQ, i = idx % TQ;
-            const int k = i % P;
-            const int j = (i - k) * R + k;
-#pragma unroll
-            for (int q = 0; q < R; ++q) u[t][q] = X[b * N + j + q * P];
-        }
-    }
-    __syncthreads();
-#pragma unroll
-    for (int t = 0; t < PER; ++t) {
-        const int idx = threadIdx.x + t * NT;
-        if (PER * NT == TOT || idx < TOT) {
-            const int b = idx / TQ, i = idx % TQ;
-            dftn<T, R>(u[t], sg);
-            if constexpr (P > 1) {
-                const int k = i % P;
-#pragma unroll
-                for (int q = 1; q < R; ++q) {
-                    Vt<T> w = tw[(q - 1) * P + k];
-                    w.y *= -sg;
-                    u[t][q] = cmul(u[t][q], w);
-                }
-            }
-#pragma unroll
-            for (int q = 0; q < R; ++q) X[b * N + i + q * TQ] = u[t][q];
-        }
-    }
-    __syncthreads();
-}
-
-template <typename T, int FI, int S, int NB, int NT>
-__device__ __forceinline__ void fft_tr(Vt<T> *X, const Vt<T> *tw, T sg) {
-    if constexpr (S >= 0) {
-        stage_tr<T, kFastSched[FI].r[S], kFastSched[FI].n, sched_p(FI, S), NB, NT>(X, tw + sched_off(FI, S), sg);
-        fft_tr<T, FI, S - 1, NB, NT>(X, tw, sg);
-    }
-}
-
 template <typename T, int FI, int D>
 __global__ __launch_bounds__(pairs_nt(FI, sizeof(Vt<T>), D))
 void row_iso_pairs(const RowArgs *__restrict__ ra, const int *__restrict__ woff, int np) {
@@ -1587,12 +1700,161 @@ void row_iso_pairs(const RowArgs *__restrict__ ra, const int *__restrict__ woff,
         store(std::integral_constant<int, (N + 1) / 2>{});
 }
 
-// ---- launchers and the table of a part ----
+// Row pass of an isotropic material with Bluestein transforms (rows of any
+// length n = a.f.n <= (N + 1) / 2): as row_iso_pairs, with each transform a
+// convolution of length N.  Between the inverse and the forward transform the
+// last transposed stage leaves a thread the points i + q N / R0, where the
+// chirp of the one, the material and the chirp of the other multiply the n
+// points of the row (the rest is zero padding) and the first stage of the
+// forward convolution follows on the same points.
+constexpr int blue_pw(int n, int es, int d) {
+    int p = d == 3 ? 4 : 2;
+    while (p > 1 && d * p * n * es > 24 * 1024) --p;
+    return p;
+}
+constexpr bool blue_one(int n, int es, int d) { return d * n * es > 24 * 1024; }
+constexpr int blue_tb(int n, int es, int d) { return blue_one(n, es, d) ? 1 : d * blue_pw(n, es, d); }
+constexpr int blue_nt(int fi, int es, int d) {
+    const int n = kFastSched[fi].n, t = blue_tb(n, es, d) * (n / kFastSched[fi].r[0]);
+    const int nt = (t + 63) / 64 * 64;
+    return nt < 64 ? 64 : nt > 256 ? 256 : nt;
+}
+constexpr size_t blue_lds(int fi, int es, int d) {
+    const int n = kFastSched[fi].n;
+    return (size_t)es * ((size_t)n * blue_tb(n, es, d) + tw_lds_entries(n, es));
+}
+
 template <typename T, int FI, int D>
+__global__ __launch_bounds__(blue_nt(FI, sizeof(Vt<T>), D))
+void row_iso_blue(const RowArgs *__restrict__ ra, const int *__restrict__ woff, int np) {
+    using V = Vt<T>;
+    constexpr int N = kFastSched[FI].n;
+    constexpr int R = kFastSched[FI].r[0];
+    constexpr int TQ = N / R;
+    constexpr bool ONE = blue_one(N, sizeof(V), D);
+    constexpr int PW = ONE ? 1 : blue_pw(N, sizeof(V), D);
+    constexpr int TB = blue_tb(N, sizeof(V), D);  // transforms: component c0 + c of pair p is c PW + p
+    constexpr int NT = blue_nt(FI, sizeof(V), D);
+    constexpr int NHC = ((N + 1) / 2 + 1) / 2;  // stored points of a row of at most (N + 1) / 2
+    int lb;
+    const RowArgs &a = ra[find_problem(woff, np, &lb)];
+    if (a.status != nullptr && a.status->done) return;
+    __builtin_amdgcn_s_setprio(3);
+    extern __shared__ __align__(16) unsigned char smem_raw[];  // 16-byte complex doubles
+    V *X = reinterpret_cast<V *>(smem_raw);
+    const int n = a.f.n;
+    const int nh = a.Nh_row;
+    const int pr0 = ONE ? lb / D : lb * PW;
+    const int c0 = ONE ? lb - pr0 * D : 0;
+    const int nrow_wg = min(2 * PW, a.nrows - 2 * pr0);  // rows of this work-group
+    const V *tab = reinterpret_cast<const V *>(a.tw);
+    const V *chirp = tab + a.f.choff;
+    const V *H = tab + a.f.hoff;
+    auto *data = gbl(reinterpret_cast<V *>(a.data) + (long)c0 * a.cs + (long)2 * pr0 * nh);
+    constexpr int PL = (TB * NHC + NT - 1) / NT;
+    T x1[PL], y1[PL], x2[PL], y2[PL];
+#pragma unroll
+    for (int t = 0; t < PL; ++t) {
+        const int idx = threadIdx.x + t * NT;
+        const int tr = idx / NHC, k = idx % NHC;
+        const int c = tr / PW, p = tr % PW;
+        const bool ok = idx < TB * NHC && k < nh && 2 * p < nrow_wg;
+        const bool ok2 = ok && 2 * p + 1 < nrow_wg;
+        const long off = ok ? (long)c * a.cs + 2 * p * nh + k : 0L;
+        const V u1 = gld(data + off);
+        const V u2 = gld(data + (ok2 ? off + nh : off));
+        x1[t] = ok ? u1.x : T(0);
+        y1[t] = ok ? u1.y : T(0);
+        x2[t] = ok2 ? u2.x : T(0);
+        y2[t] = ok2 ? u2.y : T(0);
+    }
+    const V *tw = twiddles_to_lds<T, N, NT>(X + TB * N, tab + a.f.twoff[0]);
+    // zeros: nh .. n - nh, and the padding n .. N - 1
+    const int nz = n - 2 * nh + 1, nzt = nz + N - n;
+    for (int idx = threadIdx.x; idx < TB * nzt; idx += NT) {
+        const int tr = idx / nzt, z = idx - tr * nzt;
+        X[tr * N + (z < nz ? nh + z : n + z - nz)] = mk<T>(T(0), T(0));
+    }
+#pragma unroll
+    for (int t = 0; t < PL; ++t) {
+        const int idx = threadIdx.x + t * NT;
+        const int tr = idx / NHC, k = idx % NHC;
+        if (idx >= TB * NHC || k >= nh) continue;
+        V *xr = X + tr * N;
+        if (k == 0) {
+            xr[0] = mk<T>(x1[t], x2[t]);  // c_0 = 1
+        } else {
+            xr[k] = cmul(mk<T>(x1[t] - y2[t], y1[t] + x2[t]), chirp[k]);
+            xr[n - k] = cmul(mk<T>(x1[t] + y2[t], x2[t] - y1[t]), chirp[n - k]);
+        }
+    }
+    __syncthreads();
+    __builtin_amdgcn_s_setprio(0);
+    blue_conv<T, FI, TB, NT, true, 0, 1>(X, tw, H, T(1));
+    {
+        // transposed stage 0 of the inverse, the products, stage 0 of the forward
+        const T a0 = T(a.A0[0]);
+        const T da = T(a.D[0]);
+        const auto *g = gbl(reinterpret_cast<const T *>(a.g) + (long)2 * pr0 * n);
+        for (int idx = threadIdx.x; idx < TQ * TB; idx += NT) {
+            const int tr = idx / TQ, i = idx % TQ;
+            const int p = tr % PW;
+            const bool v1 = 2 * p < nrow_wg, v2 = 2 * p + 1 < nrow_wg;
+            V *xr = X + tr * N + i * R;
+            T g1[R], g2[R];
+#pragma unroll
+            for (int q = 0; q < R; ++q) {  // points past the row and missing rows read entry 0
+                const int x = i + q * TQ;
+                g1[q] = g[x < n && v1 ? 2 * p * n + x : 0];
+                g2[q] = g[x < n && v2 ? (2 * p + 1) * n + x : 0];
+            }
+            V u[R];
+#pragma unroll
+            for (int q = 0; q < R; ++q) u[q] = xr[q];
+            dftn<T, R>(u, T(1));
+#pragma unroll
+            for (int q = 0; q < R; ++q) {
+                const int x = i + q * TQ;
+                const V c = chirp[x < n ? x : 0];
+                V v = cmul(u[q], c);
+                v.x *= a0 + g1[q] * da;
+                v.y *= a0 + g2[q] * da;
+                v = cmul(v, mk<T>(c.x, -c.y));
+                u[q] = x < n ? v : mk<T>(T(0), T(0));
+            }
+            dftn<T, R>(u, T(-1));
+#pragma unroll
+            for (int q = 0; q < R; ++q) xr[q] = u[q];
+        }
+        __syncthreads();
+    }
+    blue_conv<T, FI, TB, NT, true, 1, 0>(X, tw, H, T(-1));
+    const T half = T(a.scale) * T(0.5);
+    for (int idx = threadIdx.x; idx < TB * NHC; idx += NT) {
+        const int tr = idx / NHC, k = idx % NHC;
+        const int c = tr / PW, p = tr % PW;
+        if (k >= nh || 2 * p >= nrow_wg) continue;
+        const int km = k == 0 ? 0 : n - k;
+        const V w = cmul(X[tr * N + k], chirp_at<T>(chirp, k, T(-1)));
+        const V wm = cmul(X[tr * N + km], chirp_at<T>(chirp, km, T(-1)));
+        auto *o = data + (long)c * a.cs + 2 * p * nh + k;
+        gst(o, mk<T>((w.x + wm.x) * half, (w.y - wm.y) * half));
+        if (2 * p + 1 < nrow_wg) gst(o + nh, mk<T>((w.y + wm.y) * half, (wm.x - w.x) * half));
+    }
+}
+
+// ---- launchers and the table of a part ----
+template <typename T, int FI, int D, bool BLUE>
 void launch_pencil_t(const PencilArgs *args, const int *woff, int np, int total, hipStream_t s, LaunchEv ev) {
     constexpr int N = kFastSched[FI].n;
-    dispatch((pencil_fast<T, FI, D>), dim3(total), dim3(pencil_nt(N, sizeof(Vt<T>), D)),
-             pencil_lds(N, sizeof(Vt<T>), D), Disp(s, ev), args, woff, np);
+    dispatch((pencil_fast<T, FI, D, BLUE>), dim3(total), dim3(pencil_nt(N, sizeof(Vt<T>), D, BLUE)),
+             pencil_lds(N, sizeof(Vt<T>), D, BLUE), Disp(s, ev), args, woff, np);
+}
+
+template <typename T, int FI, int D>
+void launch_blue_row_t(const RowArgs *args, const int *woff, int np, int total, hipStream_t s, LaunchEv ev) {
+    dispatch((row_iso_blue<T, FI, D>), dim3(total), dim3(blue_nt(FI, sizeof(Vt<T>), D)), blue_lds(FI, sizeof(Vt<T>), D),
+             Disp(s, ev), args, woff, np);
 }
 
 template <typename T, int FI, int D>
@@ -1631,7 +1893,13 @@ template <typename T, int FI, int D>
 void fill_dim(FastKernels &k) {
     constexpr int n = kFastSched[FI].n, es = sizeof(Vt<T>), p = sizeof(T) == 8;
     if constexpr (fast_dim(FI, D)) {
-        k.pencil[p][D - 2] = {launch_pencil_t<T, FI, D>, pencil_batch(n, es, D), pencil_lds(n, es, D)};
+        k.pencil[p][D - 2] = {launch_pencil_t<T, FI, D, false>, pencil_batch(n, es, D), pencil_lds(n, es, D)};
+        if constexpr (has_blue(FI, D)) {
+            k.blue_pencil[p][D - 2] = {launch_pencil_t<T, FI, D, true>, pencil_batch(n, es, D, true),
+                                       pencil_lds(n, es, D, true)};
+            k.blue_row[p][D - 2] = {launch_blue_row_t<T, FI, D>, blue_tb(n, es, D), ((n + 1) / 2 + 1) / 2,
+                                    blue_lds(FI, es, D)};
+        }
         k.row[p][D - 2] = {launch_row_t<T, FI, D>, fast_batch(n, es, D), (n + 1) / 2, row_lds(n, es, D)};
         if constexpr (has_staged(FI))
             k.pairs[p][D - 2] = {launch_staged_t<T, FI, D>, staged_tb(FI, D, es), staged_nhc(n), staged_lds<T>(FI, D)};

@@ -378,6 +378,9 @@ struct FastKernels {
     Row iso[2][2];    // isotropic: RP transforms (row pair, component)
     Row pairs[2][2];  // isotropic: RP transforms of whole row pairs
     Row gram[2];      // FP64 energy Gram: RP row pairs
+    // Bluestein transforms through this convolution length
+    Pencil blue_pencil[2][2];
+    Row blue_row[2][2];  // isotropic: RP transforms, of whole row pairs or one
 };
 constexpr int kFastParts = 8;
 template <int PART> void fill_fast(FastKernels *table);  // entries fi with fi % kFastParts == PART

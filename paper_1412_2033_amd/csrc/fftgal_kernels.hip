@@ -1878,9 +1878,28 @@ const FastKernels &fast_kernels(int fi) {
     return t.k[fi];
 }
 
+// The table entry of a pass that configure_pencil / configure_row gave a
+// specialised kernel: pencils 1 (a length of kFastSched), 2 (Bluestein); rows
+// 1 (any material; energy Gram), 2 (isotropic, single transforms), 3
+// (isotropic, whole row pairs), 4 and 5 (Bluestein: whole row pairs, single).
+static const FastKernels::Pencil &fast_pencil(const PencilArgs &a, bool fp64) {
+    const FastKernels &k = fast_kernels(fast_index(a.f.L));
+    return a.fast == 2 ? k.blue_pencil[fp64][a.d - 2] : k.pencil[fp64][a.d - 2];
+}
+static const FastKernels::Row &fast_row(const RowArgs &a, bool fp64) {
+    const FastKernels &k = fast_kernels(fast_index(a.f.L));
+    if (a.mode == ROW_GRAM) return k.gram[a.d - 2];
+    switch (a.fast) {
+        case 1: return k.row[fp64][a.d - 2];
+        case 2: return k.iso[fp64][a.d - 2];
+        case 3: return k.pairs[fp64][a.d - 2];
+        default: return k.blue_row[fp64][a.d - 2];
+    }
+}
+
 size_t pencil_lds_bytes(const PencilArgs &a, bool fp64) {
     const size_t es = fp64 ? 16 : 8;
-    if (a.fast) return fast_kernels(fast_index(a.f.n)).pencil[fp64][a.d - 2].lds;
+    if (a.fast) return fast_pencil(a, fp64).lds;
     int lacc = 0;
     if (a.pro == PRO_EXPAND) lacc = a.nc * a.L_in;
     if (a.epi == EPI_PROJECT) lacc = a.nc * a.L_out;
@@ -1890,9 +1909,7 @@ size_t pencil_lds_bytes(const PencilArgs &a, bool fp64) {
 size_t row_lds_bytes(const RowArgs &a, bool fp64) {
     const size_t es = fp64 ? 16 : 8;
     if (a.fast) {
-        const FastKernels &k = fast_kernels(fast_index(a.f.n));
-        if (a.mode == ROW_GRAM) return k.gram[a.d - 2].lds;
-        return a.fast == 3 ? k.pairs[fp64][a.d - 2].lds : a.fast == 2 ? k.iso[fp64][a.d - 2].lds : k.row[fp64][a.d - 2].lds;
+        return fast_row(a, fp64).lds;
     }
     const int nz = row_zbufs(a);
     return es * (size_t)(a.zbatch ? 2 * nz : nz + 1) * a.RP * a.f.L;
@@ -1903,13 +1920,14 @@ int row_grid(const RowArgs &a) {
     if (a.RP < 1) return 0;
     if (a.mode == ROW_GRAM && a.gpack && !a.fast) return (a.nrows + a.RP - 1) / a.RP;
     const int pairs = (a.nrows + 1) / 2;
-    if (a.fast == 3) return (pairs + a.RP / a.d - 1) / (a.RP / a.d);
-    return a.fast == 2 ? (a.d * pairs + a.RP - 1) / a.RP : (pairs + a.RP - 1) / a.RP;
+    if (a.fast == 3 || a.fast == 4) return (pairs + a.RP / a.d - 1) / (a.RP / a.d);
+    return a.fast == 2 || a.fast == 5 ? (a.d * pairs + a.RP - 1) / a.RP : (pairs + a.RP - 1) / a.RP;
 }
 
-// Index in kFastSched of the length of f when its stages are that schedule, else -1.
+// Index in kFastSched of the transform (Bluestein: convolution) length of f
+// when its stages are that schedule, else -1.
 static int fast_of(const FftDesc &f) {
-    const int fi = f.blue ? -1 : fast_index(f.n);
+    const int fi = fast_index(f.L);
     if (fi < 0 || f.nst != kFastSched[fi].nst) return -1;
     for (int s = 0; s < f.nst; ++s)
         if (f.radix[s] != kFastSched[fi].r[s]) return -1;
@@ -1919,10 +1937,12 @@ static int fast_of(const FftDesc &f) {
 void configure_pencil(PencilArgs &a, bool fp64) {
     const int fi = fast_of(a.f);
     if (fi >= 0 && a.nsol == 1 && a.ncomp == a.d && a.epi != EPI_WINDOW && (a.d == 2 || a.d == 3) &&
-        a.L_in <= a.f.n && a.L_out <= a.f.n && fast_kernels(fi).pencil[fp64][a.d - 2].fn) {
-        a.fast = 1;
-        a.B = fast_kernels(fi).pencil[fp64][a.d - 2].B;
-        return;
+        a.L_in <= a.f.n && a.L_out <= a.f.n) {
+        a.fast = a.f.blue ? 2 : 1;
+        if (fast_pencil(a, fp64).fn) {
+            a.B = fast_pencil(a, fp64).B;
+            return;
+        }
     }
     a.fast = 0;
     a.cb = 1;
@@ -1954,10 +1974,15 @@ void configure_row(RowArgs &r, bool fp64) {
             r.RP = e.RP;
             return true;
         };
-        if (oper && r.iso && take(k.pairs[fp64][r.d - 2], 3)) return;
-        if (oper && r.iso && take(k.iso[fp64][r.d - 2], 2)) return;
-        if ((oper || (r.mode == ROW_RHS && r.ncomp == r.d)) && take(k.row[fp64][r.d - 2], 1)) return;
-        if (fp64 && r.mode == ROW_GRAM && r.ncomp == r.d * r.d && take(k.gram[r.d - 2], 1)) return;
+        if (r.f.blue) {
+            const FastKernels::Row &e = k.blue_row[fp64][r.d - 2];
+            if (oper && r.iso && take(e, e.RP > 1 ? 4 : 5)) return;
+        } else {
+            if (oper && r.iso && take(k.pairs[fp64][r.d - 2], 3)) return;
+            if (oper && r.iso && take(k.iso[fp64][r.d - 2], 2)) return;
+            if ((oper || (r.mode == ROW_RHS && r.ncomp == r.d)) && take(k.row[fp64][r.d - 2], 1)) return;
+            if (fp64 && r.mode == ROW_GRAM && r.ncomp == r.d * r.d && take(k.gram[r.d - 2], 1)) return;
+        }
     }
     r.fast = 0;
     r.zbatch = 0;
@@ -2095,9 +2120,8 @@ int update_blocks(long n) { return (int)std::max<long>(1, (n + (long)kThreads * 
 
 hipError_t launch_pencil_multi(const PencilArgs &proto, const PencilArgs *args, const int *woff, int np, int total,
                                bool fp64, hipStream_t st, LaunchEv ev) {
-    const int fi = fast_index(proto.f.n);
-    if (!proto.fast || fi < 0 || np < 1 || total < 1) return hipErrorInvalidValue;
-    const FastKernels::Pencil &e = fast_kernels(fi).pencil[fp64][proto.d - 2];
+    if (!proto.fast || fast_index(proto.f.L) < 0 || np < 1 || total < 1) return hipErrorInvalidValue;
+    const FastKernels::Pencil &e = fast_pencil(proto, fp64);
     if (!e.fn) return hipErrorInvalidValue;
     e.fn(args, woff, np, total, st, ev);
     return hipGetLastError();
@@ -2105,13 +2129,8 @@ hipError_t launch_pencil_multi(const PencilArgs &proto, const PencilArgs *args, 
 
 hipError_t launch_row_multi(const RowArgs &proto, const RowArgs *args, const int *woff, int np, int total, bool fp64,
                             hipStream_t st, LaunchEv ev) {
-    const int fi = fast_index(proto.f.n);
-    if (!proto.fast || fi < 0 || np < 1 || total < 1) return hipErrorInvalidValue;
-    const FastKernels &k = fast_kernels(fi);
-    const FastKernels::Row &e = proto.mode == ROW_GRAM ? k.gram[proto.d - 2]
-                                : proto.fast == 3     ? k.pairs[fp64][proto.d - 2]
-                                : proto.fast == 2     ? k.iso[fp64][proto.d - 2]
-                                                      : k.row[fp64][proto.d - 2];
+    if (!proto.fast || fast_index(proto.f.L) < 0 || np < 1 || total < 1) return hipErrorInvalidValue;
+    const FastKernels::Row &e = fast_row(proto, fp64);
     if (!e.fn || (proto.mode == ROW_GRAM && !fp64) || (proto.fast > 1 && proto.mode != ROW_OPER))
         return hipErrorInvalidValue;
     e.fn(args, woff, np, total, st, ev);
