@@ -48,10 +48,13 @@ int smooth_odd(int m) {
 
 bool is_smooth_odd(int n) { return n >= 1 && smooth_odd(n) == n; }
 
+// Lengths transformed by Stockham stages (the others by Bluestein's identity).
+bool direct_length(int n) { return is_smooth_odd(n) || fast_index(n) >= 0; }
+
 // Complex table entries a transform of length n takes (stage twiddles of a
 // smooth n; for a Bluestein transform those of L plus the chirp and the filter).
 size_t fft_table_len(int n) {
-    if (is_smooth_odd(n)) return (size_t)n;
+    if (direct_length(n)) return (size_t)n;
     const int L = smooth_odd(2 * n - 1);
     return (size_t)L + (size_t)n + (size_t)L;
 }
@@ -346,7 +349,7 @@ void build_fft(int n, size_t tw_base_entry, std::vector<double> &tab, FftDesc *f
     f->L = n;
     f->blue = 0;
     f->choff = f->hoff = 0;
-    if (is_smooth_odd(n)) {
+    if (direct_length(n)) {
         stage_twiddles(n, pos, tab, f);
         return;
     }

@@ -100,43 +100,6 @@ template <> __device__ constexpr double csin<7>(int j) {
                   : 0.43388373911755812047576833284836;
 }
 
-// In-register DFT of odd length R: U[m] = sum_q u[q] exp(sg 2 pi i q m / R),
-// computed from the symmetric and antisymmetric pair sums u[q] +- u[R-q].
-template <typename T, int R>
-__device__ __forceinline__ void dft(Vt<T> *u, T sg) {
-    constexpr int H = (R - 1) / 2;
-    Vt<T> sp[H], sm[H];
-#pragma unroll
-    for (int q = 1; q <= H; ++q) {
-        sp[q - 1] = cadd(u[q], u[R - q]);
-        sm[q - 1] = csub(u[q], u[R - q]);
-    }
-    const Vt<T> u0 = u[0];
-    Vt<T> tot = u0;
-#pragma unroll
-    for (int q = 0; q < H; ++q) tot = cadd(tot, sp[q]);
-#pragma unroll
-    for (int m = 1; m <= H; ++m) {
-        Vt<T> a = u0;
-        Vt<T> b = mk<T>(T(0), T(0));
-#pragma unroll
-        for (int q = 1; q <= H; ++q) {
-            const int j = (q * m) % R;
-            const T cv = T(j <= H ? ccos<R>(j) : ccos<R>(R - j));
-            const T sv = T(j <= H ? csin<R>(j) : -csin<R>(R - j));
-            a.x += cv * sp[q - 1].x;
-            a.y += cv * sp[q - 1].y;
-            b.x += sv * sm[q - 1].x;
-            b.y += sv * sm[q - 1].y;
-        }
-        b.x *= sg;
-        b.y *= sg;
-        u[m] = mk<T>(a.x - b.y, a.y + b.x);
-        u[R - m] = mk<T>(a.x + b.y, a.y - b.x);
-    }
-    u[0] = tot;
-}
-
 constexpr double kPiD = 3.14159265358979323846;
 constexpr double cx_sin_small(double x) {
     double x2 = x * x, t = x, s = x;
@@ -178,19 +141,61 @@ template <int R> struct TrigTab {
 };
 template <int R> struct Trig { static constexpr TrigTab<R> v{}; };
 
+template <> __device__ constexpr double ccos<11>(int j) { return Trig<11>::v.c[j]; }
+template <> __device__ constexpr double csin<11>(int j) { return Trig<11>::v.s[j]; }
+template <> __device__ constexpr double ccos<13>(int j) { return Trig<13>::v.c[j]; }
+template <> __device__ constexpr double csin<13>(int j) { return Trig<13>::v.s[j]; }
+
+// In-register DFT of odd length R: U[m] = sum_q u[q] exp(sg 2 pi i q m / R),
+// computed from the symmetric and antisymmetric pair sums u[q] +- u[R-q].
+template <typename T, int R>
+__device__ __forceinline__ void dft(Vt<T> *u, T sg) {
+    constexpr int H = (R - 1) / 2;
+    Vt<T> sp[H], sm[H];
+#pragma unroll
+    for (int q = 1; q <= H; ++q) {
+        sp[q - 1] = cadd(u[q], u[R - q]);
+        sm[q - 1] = csub(u[q], u[R - q]);
+    }
+    const Vt<T> u0 = u[0];
+    Vt<T> tot = u0;
+#pragma unroll
+    for (int q = 0; q < H; ++q) tot = cadd(tot, sp[q]);
+#pragma unroll
+    for (int m = 1; m <= H; ++m) {
+        Vt<T> a = u0;
+        Vt<T> b = mk<T>(T(0), T(0));
+#pragma unroll
+        for (int q = 1; q <= H; ++q) {
+            const int j = (q * m) % R;
+            const T cv = T(j <= H ? ccos<R>(j) : ccos<R>(R - j));
+            const T sv = T(j <= H ? csin<R>(j) : -csin<R>(R - j));
+            a.x += cv * sp[q - 1].x;
+            a.y += cv * sp[q - 1].y;
+            b.x += sv * sm[q - 1].x;
+            b.y += sv * sm[q - 1].y;
+        }
+        b.x *= sg;
+        b.y *= sg;
+        u[m] = mk<T>(a.x - b.y, a.y + b.x);
+        u[R - m] = mk<T>(a.x + b.y, a.y - b.x);
+    }
+    u[0] = tot;
+}
+
 constexpr int smallest_prime_factor(int n) {
     for (int p = 2; p * p <= n; ++p)
         if (n % p == 0) return p;
     return n;
 }
 
-// In-register DFT of length R (any product of 3, 5, 7): prime lengths use the
+// In-register DFT of length R (any product of 3, 5, 7, 11, 13): prime lengths use the
 // symmetric butterflies above, composite ones R = R1 R2 a Cooley-Tukey split
 // (R2 DFTs of length R1, twiddles exp(sg 2 pi i n2 k1 / R), R1 DFTs of length
 // R2, output index k1 + R1 k2).
 template <typename T, int R>
 __device__ __forceinline__ void dftn(Vt<T> *u, T sg) {
-    if constexpr (R == 3 || R == 5 || R == 7) {
+    if constexpr (R == 3 || R == 5 || R == 7 || R == 11 || R == 13) {
         dft<T, R>(u, sg);
     } else if constexpr (R == 15) {
         // Good-Thomas split 15 = 3 * 5 (coprime, no twiddles): input index

@@ -94,8 +94,13 @@ __device__ __forceinline__ void fft_tr(Vt<T> *X, const Vt<T> *tw, T sg) {
 // ---- Bluestein transforms (FftDesc): NB circular convolutions of length L = N ----
 // Convolution lengths with Bluestein kernels: those of the non-smooth transform
 // lengths from 11 on.
+constexpr bool seven_smooth(int n) {
+    for (int p : {3, 5, 7})
+        while (n % p == 0) n /= p;
+    return n == 1;
+}
 constexpr bool has_blue(int fi, int d) {
-    return kFastSched[fi].n >= 21 && (d == 2 || kFastSched[fi].n <= kMaxFast3);
+    return seven_smooth(kFastSched[fi].n) && kFastSched[fi].n >= 21 && (d == 2 || kFastSched[fi].n <= kMaxFast3);
 }
 
 // The last forward stage, the product with the filter for the sign sg, and

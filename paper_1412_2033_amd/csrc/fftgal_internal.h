@@ -35,9 +35,13 @@ struct FftDesc {
 
 // Transform lengths with compile-time specialised kernels, and their radix
 // schedules (composite radices are done in registers): every odd 3,5,7-smooth
-// length from 9 to 2025.  The host builds the twiddle tables of these lengths
+// length from 9 to 2025, the lengths a double grid takes, and, for the plans
+// whose transforms have the length of the order itself (GaNi, reduced Ga), the
+// odd lengths up to 385 with prime factors up to 13, which would otherwise run
+// Bluestein's convolution of twice the length (3D GaNi of order 99 with its
+// bounds, FP64: 121 -> 67 ms).  The host builds the twiddle tables of these lengths
 // with the same schedule, and the generic kernels run it too (radices 3, 5, 7,
-// 9, 15, 25).  The schedules of the first six read the same forwards and
+// 9, 11, 13, 15, 25).  The schedules of the first six read the same forwards and
 // backwards where the length allows: then the last stage of an inverse
 // transform leaves each thread holding exactly the points that the first stage
 // of a forward transform consumes.  The others get that from running the
@@ -63,6 +67,13 @@ constexpr FastSched kFastSched[] = {
     {1215, 3, {9, 15, 9, 0}},   {1225, 4, {7, 5, 5, 7}},   {1323, 4, {7, 9, 3, 7}},
     {1575, 3, {15, 7, 15, 0}},  {1701, 4, {9, 7, 3, 9}},   {1715, 4, {7, 5, 7, 7}},
     {1875, 4, {5, 15, 5, 5}},
+    {11, 1, {11, 0, 0, 0}},     {13, 1, {13, 0, 0, 0}},    {33, 2, {11, 3, 0, 0}},
+    {39, 2, {13, 3, 0, 0}},     {55, 2, {11, 5, 0, 0}},    {65, 2, {13, 5, 0, 0}},
+    {77, 2, {11, 7, 0, 0}},     {91, 2, {13, 7, 0, 0}},    {99, 2, {11, 9, 0, 0}},
+    {117, 2, {13, 9, 0, 0}},    {121, 2, {11, 11, 0, 0}},  {143, 2, {13, 11, 0, 0}},
+    {165, 3, {5, 11, 3, 0}},    {169, 2, {13, 13, 0, 0}},  {195, 3, {5, 13, 3, 0}},
+    {231, 3, {7, 11, 3, 0}},    {273, 3, {7, 13, 3, 0}},   {297, 3, {9, 11, 3, 0}},
+    {325, 3, {5, 13, 5, 0}},    {385, 3, {7, 11, 5, 0}},
 };
 // The lengths FFTGAL_FAST_GRID chooses from (the first entries of kFastSched).
 constexpr int kNumGridLengths = 6;

@@ -76,6 +76,8 @@ __device__ __forceinline__ Vt<T> *fft_stages(Vt<T> *A, Vt<T> *Bf, const FftDesc 
             case 5: stage<T, 5, ROWL>(X, Y, f.L, p, nb, t, sg); break;
             case 7: stage<T, 7, ROWL>(X, Y, f.L, p, nb, t, sg); break;
             case 9: stage<T, 9, ROWL>(X, Y, f.L, p, nb, t, sg); break;
+            case 11: stage<T, 11, ROWL>(X, Y, f.L, p, nb, t, sg); break;
+            case 13: stage<T, 13, ROWL>(X, Y, f.L, p, nb, t, sg); break;
             case 15: stage<T, 15, ROWL>(X, Y, f.L, p, nb, t, sg); break;
             default: stage<T, 25, ROWL>(X, Y, f.L, p, nb, t, sg); break;
         }

@@ -11,7 +11,8 @@ pair of rows half empty) and an anisotropic inclusion (the general row pass).
 The FP32-iteration form must match the FP64 run of K32 steps at contrast 10 to
 1e-7.  The orders are the largest with 2 N - 1 <= n, so that the rows hold the
 most points a Ga plan can have.  GaNi plans of order n transform rows of full
-length and must match the oracle's matrices of the same iterates.
+length and must match the oracle's matrices of the same iterates; those of
+orders with factors 11 and 13 run lengths no double grid takes.
 """
 
 import numpy as np
@@ -26,6 +27,8 @@ K = 4
 K32 = 2
 LENGTHS = (9, 15, 21, 25, 35, 45, 49, 63, 75, 105, 135, 147, 175, 189, 243, 315, 343, 375, 405, 441, 525, 567,
            625, 675, 735, 875, 945, 1029, 1125, 1215, 1225, 1323, 1575, 1701, 1715, 1875)
+# orders with factors 11 and 13, which GaNi and reduced plans transform directly
+LENGTHS_13 = (11, 13, 33, 39, 55, 65, 77, 91, 99, 117, 121, 143, 165, 169, 195, 231, 273, 297, 325, 385)
 LENGTHS_3D = tuple(n for n in LENGTHS if n <= 405)
 
 
@@ -96,10 +99,14 @@ def test_length_3d(fg, n, kind):
     _check(fg, n, 3, kind)
 
 
-@pytest.mark.parametrize("n", (9, 27, 49, 75, 147, 315, 735))
+@pytest.mark.parametrize("n", (9, 27, 49, 75, 147, 315, 735) + LENGTHS_13)
 def test_full_rows(fg, n):
-    for N in ((5, n), (n, 5)):
+    grids = [(5, n), (n, 5)] + ([(n, 5, 3), (5, n, 3), (3, 5, n)] if n <= 231 else [])
+    for N in grids:
         micro = _micro(N, "voxels", 50.0, P=N)
-        res = _run(fg, micro, N, "fp64", K, n, int(N[1] == n), scheme="gani")
+        res = _run(fg, micro, N, "fp64", K, n, N.index(n), scheme="gani")
         ref = gani.gani(micro, N, tol=0.0, maxit=K)
         assert _err(res, {"upper": ref["A_gani"], "lower": np.linalg.inv(ref["B_gani"])}) <= 1e-11
+        easy = _micro(N, "voxels", 10.0, P=N)
+        assert _err(_run(fg, easy, N, "fp32", K32, n, N.index(n), scheme="gani"),
+                    _run(fg, easy, N, "fp64", K32, n, N.index(n), scheme="gani")) <= 1e-7
