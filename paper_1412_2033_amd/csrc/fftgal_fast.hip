@@ -161,9 +161,10 @@ template <typename T> __device__ __forceinline__ Vt<T> chirp_at(const Vt<T> *chi
 // row pairs per work-group of the specialised anisotropic row pass so that
 // one batch of all d components stays within 24 KB of LDS (the passes are
 // latency-bound: smaller work-groups put more of them on a CU)
+constexpr bool small_tile(int n, int es, int d);
 constexpr int fast_batch(int n, int es, int d) {
     const int cap = 24 * 1024;
-    int b = 16;
+    int b = !small_tile(n, es, d) || (n == 125 && d == 3) ? 16 : d == 2 ? 2 : 4;
     while (b > 1 && d * b * n * es > cap) b /= 2;
     return b;
 }
@@ -182,6 +183,15 @@ constexpr int fast_batch(int n, int es, int d) {
 // points (order 365) take 3 pencils with 512 threads (486 of the 2 x 3 x 81
 // radix-9 butterflies busy in one round, against two rounds for 2 pencils and
 // 256 threads): a batch of 16 such solves 7 % faster.
+// Small grids take small tiles, so that their few pencils spread over the CUs:
+// in 2D transforms below 300 points one pencil (n / 4 pencils make a pass), in
+// 3D up to 63 points two, and the 3D FP32 transforms of 125 points four (of
+// the eight that fit).  Per iteration of all 2d solves: 2D 189 x 135 FP64 33.3
+// -> 29.3 us, 2D 315^2 FP32 30.3 -> 27.2, 3D 45^3 FP32 36.2 -> 29.5, 3D 125^3
+// FP32 269 -> 255; at 405^2 one pencil cost 5 %, at 75^3 two cost 6 %.
+constexpr bool small_tile(int n, int es, int d) {
+    return d == 2 ? n < 330 : n <= 63 || (n == 125 && es < 16);
+}
 // Bluestein tiles: up to 8 pencils within 24 KB for the short lengths (their
 // grids are small), 48 KB for the others, whose two transforms per pencil need
 // the lanes.
@@ -194,6 +204,7 @@ constexpr int pencil_batch(int n, int es, int d, bool blue = false) {
     }
     if (d == 3 && n == 225) return es >= 16 ? 7 : 9;
     if (es < 16 && d == 2 && n == 729) return 3;
+    if (small_tile(n, es, d)) return d == 2 ? 1 : es >= 16 || n < 125 ? 2 : 4;
     const int cap = (es >= 16 && d == 3 && n > 225) ? 48 * 1024 : 24 * 1024;
     int b = 16;
     while (b > 1 && d * b * n * es > cap) b /= 2;
@@ -207,6 +218,7 @@ constexpr int pencil_batch(int n, int es, int d, bool blue = false) {
 // of the threads; else 256
 constexpr int pencil_nt(int n, int es, int d, bool blue = false) {
     if (blue) return n >= 1125 ? 512 : kThreads;
+    if (small_tile(n, es, d)) return n == 125 && d == 3 ? kThreads : 128;
     return ((es >= 16 && d == 2 && n >= 2025) || (es < 16 && d == 2 && n == 729) || (d == 3 && n == 225))
                ? 512
                : kThreads;
@@ -1519,7 +1531,7 @@ __global__ __launch_bounds__(kThreads) void row_gram_fast(const RowArgs *__restr
 constexpr bool pairs_one(int n, int es, int d) { return d * n * es > 16 * 1024; }
 constexpr int pairs_pw(int n, int es, int d) {
     const int cap = 20 * 1024;
-    int p = d == 3 ? 4 : 2;
+    int p = d == 3 ? 4 : n < 330 ? 1 : 2;
     while (p > 1 && d * p * n * es > cap) --p;
     return p;
 }
@@ -1712,16 +1724,18 @@ void row_iso_pairs(const RowArgs *__restrict__ ra, const int *__restrict__ woff,
 // chirp of the one, the material and the chirp of the other multiply the n
 // points of the row (the rest is zero padding) and the first stage of the
 // forward convolution follows on the same points.
+// (one pair of 225 FP64 points, 64 threads: 46.6 us at order 99 against 50.6
+// for two pairs and 128 threads)
 constexpr int blue_pw(int n, int es, int d) {
     int p = d == 3 ? 4 : 2;
-    while (p > 1 && d * p * n * es > 24 * 1024) --p;
+    while (p > 1 && d * p * n * es > 18 * 1024) --p;
     return p;
 }
 constexpr bool blue_one(int n, int es, int d) { return d * n * es > 24 * 1024; }
 constexpr int blue_tb(int n, int es, int d) { return blue_one(n, es, d) ? 1 : d * blue_pw(n, es, d); }
 constexpr int blue_nt(int fi, int es, int d) {
     const int n = kFastSched[fi].n, t = blue_tb(n, es, d) * (n / kFastSched[fi].r[0]);
-    const int nt = (t + 63) / 64 * 64;
+    const int nt = t / 64 * 64 > t * 3 / 4 ? t / 64 * 64 : (t + 63) / 64 * 64;
     return nt < 64 ? 64 : nt > 256 ? 256 : nt;
 }
 constexpr size_t blue_lds(int fi, int es, int d) {
