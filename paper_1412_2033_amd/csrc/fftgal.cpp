@@ -720,6 +720,15 @@ void set_shift(Plan *pl, PencilArgs &a, int shift) {
     }
 }
 
+// Whether the passes of this kind carry two components between axis 1 and axis
+// 2: gradient fields in 3D, both axes in the specialised kernels.  On smaller
+// grids all 2d solves run at once, and primal and dual passes share launches
+// only while they run the same kernel.
+constexpr long kTwoMinPoints = 343000;
+bool two_components(const Plan *pl, int kind, bool fp64) {
+    return pl->D.d == 3 && kind == KIND_E && pl->D.Mtot >= kTwoMinPoints && fast_pencils(pl->fM[0], fp64) && fast_pencils(pl->fM[1], fp64);
+}
+
 // The inverse half of the operator: CG state (n_c components per solution)
 // -> d spatial components per solution on the M-grid, stored as half-spectrum
 // rows along the last axis (T1 in 2D, T2 in 3D).
@@ -728,6 +737,7 @@ int inverse_passes(Plan *pl, bool fp64, int kind, const void *state, long st_ss,
     const Dims &D = pl->D;
     const int d = D.d;
     const size_t es = fp64 ? 16 : 8;
+    const bool two = two_components(pl, kind, fp64);
     // several solutions (the energy quadrature): one launch per solution, so
     // that each takes the specialised kernels; solution s fills the
     // components s d .. s d + d - 1 of the intermediates
@@ -738,7 +748,7 @@ int inverse_passes(Plan *pl, bool fp64, int kind, const void *state, long st_ss,
         a.epi = EPI_PLAIN;
         a.kind = kind;
         a.nc = pl->nc(kind);
-        a.ncomp = d;
+        a.ncomp = two ? 2 : d;
         a.nsol = 1;
         a.sgn = +1;
         a.L_in = D.N[0];
@@ -777,6 +787,7 @@ int inverse_passes(Plan *pl, bool fp64, int kind, const void *state, long st_ss,
         b.pro = PRO_PLAIN;
         b.epi = EPI_PLAIN;
         b.ncomp = d;
+        b.grad = two ? 1 : 0;
         b.sgn = +1;
         b.L_in = D.N[1];
         b.L_out = D.M[1];
@@ -804,12 +815,14 @@ int forward_passes(Plan *pl, bool fp64, int kind, void *rows, void *q, const voi
                    bool accumulate = false) {
     const Dims &D = pl->D;
     const int d = D.d;
+    const bool two = two_components(pl, kind, fp64);
     void *src = rows;
     if (d == 3) {
         PencilArgs b = base_pencil(pl, pl->fM[1], fp64);
         b.pro = PRO_PLAIN;
         b.epi = EPI_PLAIN;
         b.ncomp = d;
+        b.grad = two ? 1 : 0;
         b.sgn = -1;
         b.L_in = D.M[1];
         b.L_out = D.N[1];
@@ -834,7 +847,7 @@ int forward_passes(Plan *pl, bool fp64, int kind, void *rows, void *q, const voi
     a.epi = EPI_PROJECT;
     a.kind = kind;
     a.nc = pl->nc(kind);
-    a.ncomp = d;
+    a.ncomp = two ? 2 : d;
     a.sgn = -1;
     a.scale = scale;
     a.L_in = D.M[0];

@@ -340,6 +340,13 @@ __device__ __forceinline__ int basis(int d, int kind, int k1, int k2, int k3, T 
     return nn == T(0) ? 0 : (primal || two) ? 1 : 2;
 }
 
+// 1 / |k| as basis() forms it (0 at k = 0)
+template <typename T> __device__ __forceinline__ T inv_norm(int k1, int k2, int k3) {
+    const T a = T(k1), b = T(k2), c = T(k3);
+    const T nn = a * a + b * b + c * c;
+    return nn == T(0) ? T(0) : rsqrt(nn);
+}
+
 // exp(-i pi sum_a s_a k_a / N_a) of the shift s (S(s) of Lemma reduce_grid);
 // 1 when no shift is set.
 __device__ __forceinline__ void shift_phase(const PencilArgs &a, int k1, int k2, int k3, double *c, double *s) {

@@ -192,10 +192,29 @@ constexpr int fast_batch(int n, int es, int d) {
 constexpr bool small_tile(int n, int es, int d) {
     return d == 2 ? n < 330 : n <= 63 || (n == 125 && es < 16);
 }
+// Two components of 225 points: 9 FP64 (13 FP32) pencils and 512 threads, 716
+// (496) tiles for the 113 x 57 pencils of an axis-1 pass; expand / project per
+// launch 31.4 / 29.4 -> 25.9 / 23.5 us (FP32 17.7 / 16.4 -> 15.5 / 13.8)
+// against three components; 7, 8, 10 and 12 FP64 pencils took 28.5, 29.5, 31.8
+// and 36.3 us, 8, 9, 10 and 16 FP32 ones 17.3, 15.6, 20.9 and 16.6.
+constexpr int two_batch(int n, int es, bool blue) {
+    if (!blue && n == 225) return es >= 16 ? 9 : 13;
+    if (!blue && small_tile(n, es, 3)) return es >= 16 || n < 125 ? 2 : 4;
+    const int cap = blue && n > 105 ? 36 * 1024 : 20 * 1024;
+    int b = blue ? 8 : 16;
+    while (b > 1 && 2 * b * n * es > cap) b /= 2;
+    return b;
+}
+constexpr int two_nt(int n, int es, bool blue) {
+    if (!blue && n == 225) return 512;
+    return !blue && small_tile(n, es, 3) && n <= 63 ? 128 : kThreads;
+}
 // Bluestein tiles: up to 8 pencils within 24 KB for the short lengths (their
 // grids are small), 48 KB for the others, whose two transforms per pencil need
 // the lanes.
+// d = 1 stands for the two-component passes of 3D gradient fields.
 constexpr int pencil_batch(int n, int es, int d, bool blue = false) {
+    if (d == 1) return two_batch(n, es, blue);
     if (blue) {
         const int most = n <= 105 ? 24 * 1024 : 48 * 1024;
         int b = 8;
@@ -217,6 +236,7 @@ constexpr int pencil_batch(int n, int es, int d, bool blue = false) {
 // 15 points per stage), so that every stage of the transform takes one round
 // of the threads; else 256
 constexpr int pencil_nt(int n, int es, int d, bool blue = false) {
+    if (d == 1) return two_nt(n, es, blue);
     if (blue) return n >= 1125 ? 512 : kThreads;
     if (small_tile(n, es, d)) return n == 125 && d == 3 ? kThreads : 128;
     return ((es >= 16 && d == 2 && n >= 2025) || (es < 16 && d == 2 && n == 729) || (d == 3 && n == 225))
@@ -227,14 +247,23 @@ constexpr int pencil_nt(int n, int es, int d, bool blue = false) {
 // BLUE: Bluestein transforms of the length a.f.n through the convolution
 // length N; the inputs are multiplied by the chirp on their way into LDS, the
 // outputs on their way out.
-template <typename T, int FI, int D, bool BLUE>
-__global__ __launch_bounds__(pencil_nt(kFastSched[FI].n, sizeof(Vt<T>), D, BLUE))
+//
+// TWO: EXPAND and PROJECT passes of 3D gradient fields (E_N) in two components.
+// The field i k c / |k| has the components 2 and 3 equal to k2 v and k3 v with
+// one v = i c / |k|, and k2, k3 are constant along axis 1: between the axis-1
+// and axis-2 passes only (i k1 c / |k|, v) are transformed and stored, the axis-2
+// inverse pass (a.grad) scales v into its components 2 and 3 as it loads them,
+// and the axis-2 forward pass stores k2 y2 + k3 y3 for the projection.  The
+// intermediate is a third smaller each way, and so is the axis-1 work.
+template <typename T, int FI, int D, bool BLUE, bool TWO>
+__global__ __launch_bounds__(pencil_nt(kFastSched[FI].n, sizeof(Vt<T>), TWO ? 1 : D, BLUE))
 void pencil_fast(const PencilArgs *__restrict__ pa, const int *__restrict__ woff, int np) {
     using V = Vt<T>;
     constexpr int N = kFastSched[FI].n;
-    constexpr int NT = pencil_nt(N, sizeof(V), D, BLUE);
-    constexpr int B = pencil_batch(N, sizeof(V), D, BLUE);
-    constexpr int NB = D * B;  // LDS layout [pos][component][batch]
+    constexpr int NC = TWO ? 2 : D;  // components transformed
+    constexpr int NT = pencil_nt(N, sizeof(V), TWO ? 1 : D, BLUE);
+    constexpr int B = pencil_batch(N, sizeof(V), TWO ? 1 : D, BLUE);
+    constexpr int NB = NC * B;  // LDS layout [pos][component][batch]
     constexpr int LPI = NT / NB;  // positions per step of the plain prologue / epilogue
     int lb;
     const PencilArgs &a = pa[find_problem(woff, np, &lb)];
@@ -339,13 +368,14 @@ void pencil_fast(const PencilArgs *__restrict__ pa, const int *__restrict__ woff
             if (bb >= nbw) {  // idle pencil of a ragged tile
                 const int pos = place(wrapi(l, a.L_in));
 #pragma unroll
-                for (int al = 0; al < D; ++al) X[pos * NB + al * B + bb] = zero;
+                for (int al = 0; al < NC; ++al) X[pos * NB + al * B + bb] = zero;
                 continue;
             }
             int k1, k2, k3;
             freq(l, a.L_in, bb, &k1, &k2, &k3);
             T tb[2][3];
             const int nt = basis<T>(D, a.kind, k1, k2, k3, tb);
+            if constexpr (TWO) tb[0][1] = inv_norm<T>(k1, k2, k3);
             V v[2];
 #pragma unroll
             for (int c = 0; c < 2; ++c) {
@@ -363,7 +393,7 @@ void pencil_fast(const PencilArgs *__restrict__ pa, const int *__restrict__ woff
             double pc = 1.0, ps = 0.0;
             if (has_shift(a)) shift_phase(a, k1, k2, k3, &pc, &ps);
 #pragma unroll
-            for (int al = 0; al < D; ++al) {
+            for (int al = 0; al < NC; ++al) {
                 T ex = T(0), ey = T(0);
 #pragma unroll
                 for (int c = 0; c < 2; ++c) {
@@ -397,7 +427,9 @@ void pencil_fast(const PencilArgs *__restrict__ pa, const int *__restrict__ woff
         const bool act = threadIdx.x < LPI * NB;
         const int c = rr / B;
         const int bb = rr - c * B;
-        const auto *in = gbl(reinterpret_cast<const V *>(a.in) + (long)o * a.in_os + b0 + (long)c * a.in_cs + bb);
+        const bool grad_in = !TWO && D == 3 && a.grad && a.sgn > 0;
+        const auto *in = gbl(reinterpret_cast<const V *>(a.in) + (long)o * a.in_os + b0 +
+                             (long)(grad_in ? min(c, 1) : c) * a.in_cs + bb);
         auto load = [&](auto cap) {
             constexpr int P = (decltype(cap)::value + LPI - 1) / LPI;
             T vx[P], vy[P];
@@ -417,6 +449,11 @@ void pencil_fast(const PencilArgs *__restrict__ pa, const int *__restrict__ woff
                 if (act && l < a.L_in) {
                     const int pos = place(wrapi(l, a.L_in));
                     V v1 = mk<T>(vx[t], vy[t]);
+                    if (grad_in && c > 0) {  // component 2: k2 v, component 3: k3 v
+                        const T k = T(c == 1 ? wrapi(l, a.L_in) : b0 + bb);
+                        v1.x *= k;
+                        v1.y *= k;
+                    }
                     if constexpr (BLUE) v1 = cmul(v1, chirp_at<T>(chirp, pos, sg));
                     X[pos * NB + rr] = v1;
                 }
@@ -467,14 +504,15 @@ void pencil_fast(const PencilArgs *__restrict__ pa, const int *__restrict__ woff
             freq(l, a.L_out, bb, &k1, &k2, &k3);
             T tb[2][3];
             const int nt = basis<T>(D, a.kind, k1, k2, k3, tb);
+            if constexpr (TWO) tb[0][1] = inv_norm<T>(k1, k2, k3);
             const int pos = place(k1);
-            V y[D];
+            V y[NC];
 #pragma unroll
-            for (int al = 0; al < D; ++al) y[al] = X[pos * NB + al * B + bb];
+            for (int al = 0; al < NC; ++al) y[al] = X[pos * NB + al * B + bb];
             if constexpr (BLUE) {
                 const V ch = chirp_at<T>(chirp, pos, sg);
 #pragma unroll
-                for (int al = 0; al < D; ++al) y[al] = cmul(y[al], ch);
+                for (int al = 0; al < NC; ++al) y[al] = cmul(y[al], ch);
             }
             const double w = (D == 3 ? k3 : k2) == 0 ? 1.0 : 2.0;  // half spectrum: k_d > 0 counts twice
             double pc = 1.0, ps = 0.0;
@@ -485,7 +523,7 @@ void pencil_fast(const PencilArgs *__restrict__ pa, const int *__restrict__ woff
                     T qx = T(0), qy = T(0);
                     if (c < nt) {
 #pragma unroll
-                        for (int al = 0; al < D; ++al) {
+                        for (int al = 0; al < NC; ++al) {
                             const T tt = tb[c][al] * scale;
                             qx += tt * y[al].y;
                             qy -= tt * y[al].x;
@@ -521,11 +559,18 @@ void pencil_fast(const PencilArgs *__restrict__ pa, const int *__restrict__ woff
         const int rr = threadIdx.x % NB;
         const int c = rr / B;
         const int bb = rr - c * B;
-        if (threadIdx.x < LPI * NB && bb < nbw) {
+        const bool grad_out = !TWO && D == 3 && a.grad && a.sgn < 0;
+        if (threadIdx.x < LPI * NB && bb < nbw && !(grad_out && c == 2)) {
             auto *ob = out + (long)c * a.out_cs + (long)o * a.out_os + b0 + bb;
             for (int l = threadIdx.x / NB; l < a.L_out; l += LPI) {
                 const int pos = place(wrapi(l, a.L_out));
                 V v = X[pos * NB + rr];
+                if (grad_out && c == 1) {  // k2 y2 + k3 y3
+                    const T k2 = T(wrapi(l, a.L_out)), k3 = T(b0 + bb);
+                    const V y3 = X[pos * NB + rr + B];
+                    v.x = k2 * v.x + k3 * y3.x;
+                    v.y = k2 * v.y + k3 * y3.y;
+                }
                 if constexpr (BLUE) v = cmul(v, chirp_at<T>(chirp, pos, sg));
                 v.x *= scale;
                 v.y *= scale;
@@ -762,7 +807,7 @@ constexpr int iso_nt(int fi) {
 constexpr bool has_iso(int fi) { return fi < kNumGridLengths && palindromic(fi); }
 constexpr bool has_staged(int fi) { return has_iso(fi) && kFastSched[fi].nst == 2; }
 constexpr size_t pencil_lds(int n, int es, int d, bool blue = false) {
-    return (size_t)es * ((size_t)n * d * pencil_batch(n, es, d, blue) + tw_lds_entries(n, es));
+    return (size_t)es * ((size_t)n * (d == 1 ? 2 : d) * pencil_batch(n, es, d, blue) + tw_lds_entries(n, es));
 }
 constexpr size_t row_lds(int n, int es, int d) {
     return (size_t)es * ((size_t)n * d * fast_batch(n, es, d) + tw_lds_entries(n, es));
@@ -1863,11 +1908,11 @@ void row_iso_blue(const RowArgs *__restrict__ ra, const int *__restrict__ woff, 
 }
 
 // ---- launchers and the table of a part ----
-template <typename T, int FI, int D, bool BLUE>
+template <typename T, int FI, int D, bool BLUE, bool TWO = false>
 void launch_pencil_t(const PencilArgs *args, const int *woff, int np, int total, hipStream_t s, LaunchEv ev) {
-    constexpr int N = kFastSched[FI].n;
-    dispatch((pencil_fast<T, FI, D, BLUE>), dim3(total), dim3(pencil_nt(N, sizeof(Vt<T>), D, BLUE)),
-             pencil_lds(N, sizeof(Vt<T>), D, BLUE), Disp(s, ev), args, woff, np);
+    constexpr int N = kFastSched[FI].n, G = TWO ? 1 : D;
+    dispatch((pencil_fast<T, FI, D, BLUE, TWO>), dim3(total), dim3(pencil_nt(N, sizeof(Vt<T>), G, BLUE)),
+             pencil_lds(N, sizeof(Vt<T>), G, BLUE), Disp(s, ev), args, woff, np);
 }
 
 template <typename T, int FI, int D>
@@ -1913,6 +1958,11 @@ void fill_dim(FastKernels &k) {
     constexpr int n = kFastSched[FI].n, es = sizeof(Vt<T>), p = sizeof(T) == 8;
     if constexpr (fast_dim(FI, D)) {
         k.pencil[p][D - 2] = {launch_pencil_t<T, FI, D, false>, pencil_batch(n, es, D), pencil_lds(n, es, D)};
+        if constexpr (D == 3)
+            k.pencil2[p] = {launch_pencil_t<T, FI, D, false, true>, pencil_batch(n, es, 1), pencil_lds(n, es, 1)};
+        if constexpr (D == 3 && has_blue(FI, D))
+            k.blue_pencil2[p] = {launch_pencil_t<T, FI, D, true, true>, pencil_batch(n, es, 1, true),
+                                 pencil_lds(n, es, 1, true)};
         if constexpr (has_blue(FI, D)) {
             k.blue_pencil[p][D - 2] = {launch_pencil_t<T, FI, D, true>, pencil_batch(n, es, D, true),
                                        pencil_lds(n, es, D, true)};

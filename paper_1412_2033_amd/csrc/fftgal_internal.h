@@ -169,6 +169,10 @@ struct PencilArgs {
     int shift[3];
     int Nfull[3];
     int accumulate;
+    // 3D gradient fields between axis 1 and axis 2 (see pencil_fast): EXPAND and
+    // PROJECT passes of two components (ncomp = 2), and the axis-2 passes that
+    // make three of them and two of three (grad = 1)
+    int grad;
 };
 
 // Batched real transforms along the last (contiguous, half-spectrum) axis,
@@ -316,6 +320,8 @@ void fit_pencil_components(PencilArgs &a, bool fp64);
 void fit_row_batch(RowArgs &r, bool fp64);
 hipError_t launch_pencil(const PencilArgs &a, int nouter, bool fp64, hipStream_t s);
 hipError_t launch_row(const RowArgs &a, bool fp64, hipStream_t s);
+// Whether the 3D transforms of f have specialised passes (also for two components).
+bool fast_pencils(const FftDesc &f, bool fp64);
 int row_grid(const RowArgs &a);
 int pencil_grid_x(const PencilArgs &a);
 
@@ -385,12 +391,14 @@ struct FastKernels {
         size_t lds = 0;
     };
     Pencil pencil[2][2];
+    Pencil pencil2[2];  // 3D gradient fields: EXPAND and PROJECT of two components
     Row row[2][2];    // any material: RP row pairs
     Row iso[2][2];    // isotropic: RP transforms (row pair, component)
     Row pairs[2][2];  // isotropic: RP transforms of whole row pairs
     Row gram[2];      // FP64 energy Gram: RP row pairs
     // Bluestein transforms through this convolution length
     Pencil blue_pencil[2][2];
+    Pencil blue_pencil2[2];
     Row blue_row[2][2];  // isotropic: RP transforms, of whole row pairs or one
 };
 constexpr int kFastParts = 8;

@@ -1881,12 +1881,18 @@ const FastKernels &fast_kernels(int fi) {
 }
 
 // The table entry of a pass that configure_pencil / configure_row gave a
-// specialised kernel: pencils 1 (a length of kFastSched), 2 (Bluestein); rows
+// specialised kernel: pencils 1 (a length of kFastSched), 2 (Bluestein), 3 and 4
+// (the same for the two components of 3D gradient fields); rows
 // 1 (any material; energy Gram), 2 (isotropic, single transforms), 3
 // (isotropic, whole row pairs), 4 and 5 (Bluestein: whole row pairs, single).
 static const FastKernels::Pencil &fast_pencil(const PencilArgs &a, bool fp64) {
     const FastKernels &k = fast_kernels(fast_index(a.f.L));
-    return a.fast == 2 ? k.blue_pencil[fp64][a.d - 2] : k.pencil[fp64][a.d - 2];
+    switch (a.fast) {
+        case 1: return k.pencil[fp64][a.d - 2];
+        case 2: return k.blue_pencil[fp64][a.d - 2];
+        case 3: return k.pencil2[fp64];
+        default: return k.blue_pencil2[fp64];
+    }
 }
 static const FastKernels::Row &fast_row(const RowArgs &a, bool fp64) {
     const FastKernels &k = fast_kernels(fast_index(a.f.L));
@@ -1936,11 +1942,20 @@ static int fast_of(const FftDesc &f) {
     return fi;
 }
 
+bool fast_pencils(const FftDesc &f, bool fp64) {
+    const int fi = fast_of(f);
+    if (fi < 0) return false;
+    const FastKernels &k = fast_kernels(fi);
+    return f.blue ? k.blue_pencil[fp64][1].fn && k.blue_pencil2[fp64].fn
+                  : k.pencil[fp64][1].fn && k.pencil2[fp64].fn;
+}
+
 void configure_pencil(PencilArgs &a, bool fp64) {
     const int fi = fast_of(a.f);
-    if (fi >= 0 && a.nsol == 1 && a.ncomp == a.d && a.epi != EPI_WINDOW && (a.d == 2 || a.d == 3) &&
+    const bool two = a.d == 3 && a.ncomp == 2;
+    if (fi >= 0 && a.nsol == 1 && (a.ncomp == a.d || two) && a.epi != EPI_WINDOW && (a.d == 2 || a.d == 3) &&
         a.L_in <= a.f.n && a.L_out <= a.f.n) {
-        a.fast = a.f.blue ? 2 : 1;
+        a.fast = (a.f.blue ? 2 : 1) + (two ? 2 : 0);
         if (fast_pencil(a, fp64).fn) {
             a.B = fast_pencil(a, fp64).B;
             return;
