@@ -103,6 +103,10 @@ enum fftgal_precision {
  * (timing class FFTGAL_K_SOLO).  Solves of such plans in a batch run that way
  * too, side by side on a stream of the batch's own.  The flag keeps these
  * plans on the per-pass kernels instead (one launch per pass and iteration).
+ * Likewise 3D Ga plans with isotropic materials and equal double grids of at
+ * most 63 points along axes 2 and 3 transform each plane x1 in one pass (timed
+ * as FFTGAL_K_ROW) between the axis-1 passes, and the flag keeps them on the
+ * axis-2 and row passes.
  * Both forms compute the same iterations; their results agree to rounding.
  * It changes no workspace size. */
 #define FFTGAL_SEPARATE_PASSES 0x800

@@ -733,7 +733,8 @@ bool two_components(const Plan *pl, int kind, bool fp64) {
 // -> d spatial components per solution on the M-grid, stored as half-spectrum
 // rows along the last axis (T1 in 2D, T2 in 3D).
 int inverse_passes(Plan *pl, bool fp64, int kind, const void *state, long st_ss, int nsol,
-                   bool update_p, const CgStatus *st, void **rows_out, int cls_expand, int cls_inv, int shift = 0) {
+                   bool update_p, const CgStatus *st, void **rows_out, int cls_expand, int cls_inv, int shift = 0,
+                   bool plane = false) {
     const Dims &D = pl->D;
     const int d = D.d;
     const size_t es = fp64 ? 16 : 8;
@@ -778,7 +779,7 @@ int inverse_passes(Plan *pl, bool fp64, int kind, const void *state, long st_ss,
         int rc = run_pencil(pl, a, 1, fp64, cls_expand);
         if (rc) return rc;
     }
-    if (d == 2) {
+    if (d == 2 || plane) {
         *rows_out = pl->T1s();
         return FFTGAL_OK;
     }
@@ -812,12 +813,12 @@ int inverse_passes(Plan *pl, bool fp64, int kind, const void *state, long st_ss,
 // plus partial sums of (dot, q) (or (q, q) when dot == nullptr).
 int forward_passes(Plan *pl, bool fp64, int kind, void *rows, void *q, const void *dot, double scale,
                    const CgStatus *st, double *partial, int *nparts, int cls_fwd, int cls_proj, int shift = 0,
-                   bool accumulate = false) {
+                   bool accumulate = false, bool plane = false) {
     const Dims &D = pl->D;
     const int d = D.d;
     const bool two = two_components(pl, kind, fp64);
     void *src = rows;
-    if (d == 3) {
+    if (d == 3 && !plane) {
         PencilArgs b = base_pencil(pl, pl->fM[1], fp64);
         b.pro = PRO_PLAIN;
         b.epi = EPI_PLAIN;
@@ -915,6 +916,21 @@ RowArgs base_row(Plan *pl, bool fp64, int mode, void *rows, int kind, int shift 
             if (i == j ? (c0[k] != c0[0] || c1[k] != c1[0]) : (c0[k] != 0.0 || c1[k] != 0.0)) r.iso = 0;
         }
     return r;
+}
+
+// The operator's passes between the axis-1 passes as one plane pass (plane_iso)
+// on T1: 3D grids of the double size with equal axes 2 and 3, isotropic
+// materials, three components.
+bool plane_pass(Plan *pl, int kind, bool fp64, RowArgs &r) {
+    const Dims &D = pl->D;
+    if (D.d != 3 || !pl->solo || D.nshift != 1 || !r.iso || D.M[1] != D.M[2] || two_components(pl, kind, fp64) ||
+        !plane_fits(pl->fM[2], D.N[1], D.Nh, fp64))
+        return false;
+    r.data = pl->T1s();
+    r.L2 = D.N[1];
+    r.nrows = D.M[0];
+    r.cs = (long)D.M[0] * D.N[1] * D.Nh;
+    return true;
 }
 
 // ---- material setup --------------------------------------------------------
@@ -1241,10 +1257,12 @@ int capture_iteration(Plan *pl, int kind, int alpha, bool fp64, IterCfg *cfg) {
         int rc = FFTGAL_OK;
         for (int s = 0; s < D.nshift && !rc; ++s) {
             pl->islot = grouped ? s : 0;
+            RowArgs r = base_row(pl, fp64, ROW_OPER, nullptr, kind, s);
+            const bool plane = plane_pass(pl, kind, fp64, r);
             rc = inverse_passes(pl, fp64, kind, s == 0 ? nullptr : pl->ws + pl->so(pl->Lo.p), 0, 1, s == 0, st, &rows,
-                                FFTGAL_K_EXPAND, FFTGAL_K_PENCIL_INV, s);
+                                FFTGAL_K_EXPAND, FFTGAL_K_PENCIL_INV, s, plane);
             if (!rc) {
-                RowArgs r = base_row(pl, fp64, ROW_OPER, rows, kind, s);
+                r.data = rows;
                 r.status = st;
                 rc = run_row(pl, r, fp64, FFTGAL_K_ROW);
             }
@@ -1252,7 +1270,7 @@ int capture_iteration(Plan *pl, int kind, int alpha, bool fp64, IterCfg *cfg) {
                 char *q = pl->ws + pl->so(pl->Lo.q) + (grouped ? (size_t)s * pl->vec_bytes() : 0);
                 double *part = pl->at<double>(pl->so(pl->Lo.part_a)) + (grouped ? (size_t)s * npq_shift : 0);
                 rc = forward_passes(pl, fp64, kind, rows, q, pl->ws + pl->so(pl->Lo.p), 1.0 / ((double)D.nshift * D.Mtot),
-                                    st, part, &npq, FFTGAL_K_PENCIL_FWD, FFTGAL_K_PROJECT, s, !grouped && s > 0);
+                                    st, part, &npq, FFTGAL_K_PENCIL_FWD, FFTGAL_K_PROJECT, s, !grouped && s > 0, plane);
                 if (s == 0) npq_shift = npq;
             }
         }
@@ -2775,7 +2793,7 @@ void group_passes(const std::vector<const std::vector<PassRec> *> &lists, size_t
         const int n = r.type == 0 ? r.pa.f.n : r.ra.f.n;
         const int d = r.type == 0 ? r.pa.d : r.ra.d;
         const int fm = r.type == 0 ? r.pa.fast : r.ra.fast;
-        by[std::make_tuple(r.type, n, d, (int)r.fp64 * 4 + fm)].push_back(&r);
+        by[std::make_tuple(r.type, n, d, (int)r.fp64 * 8 + fm)].push_back(&r);
     }
     for (auto &kv : by) {
         const auto &ms = kv.second;

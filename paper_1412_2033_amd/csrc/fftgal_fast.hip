@@ -1762,6 +1762,186 @@ void row_iso_pairs(const RowArgs *__restrict__ ra, const int *__restrict__ woff,
         store(std::integral_constant<int, (N + 1) / 2>{});
 }
 
+// Axis 2, rows and back to axis 2 of an isotropic material on small 3D grids
+// with equal axes 2 and 3.  A work-group owns one plane x1: the inverse
+// transforms along axis 2 of its three half-spectrum fields, the row transforms
+// and the material as in row_iso_pairs, and the forward transforms along axis 2,
+// all in LDS, so that the plane is read and written once (in place).  On these
+// grids each pass takes 6 to 9 us whatever its work (launch, argument and first
+// load latency), so one pass in place of three is what counts.
+//
+// Taken up to 63 points per axis; us per iteration, all six solves at once /
+// one solve: 9^3 FP64 22 / 19 -> 18 / 16, 35^3 40 / 35 -> 31 / 27, 45^3 46 / 36
+// -> 39 / 31, 63^3 69 / 37 -> 60 / 34, FP32 48 / 29 -> 39 / 26.  From 75 points
+// (137 KB of LDS in FP64) one plane per CU runs at a time and the three passes
+// are as fast or faster: 75^3 FP64 131 / 43 -> 137 / 46, 75^3 FP32 89 / 36 ->
+// 85 / 39, 105^3 FP32 142 / 45 -> 141 / 43.
+// 512 threads within 128 registers put two work-groups on a CU; at 45 points,
+// FP64, 640 and 1024 threads took 44 us (one work-group per CU), 384 took 40.
+constexpr int plane_nt(int n) { return n <= 25 ? 256 : 512; }
+constexpr size_t plane_lds(int n, int es) {
+    return (size_t)es * ((size_t)n * 3 * ((n + 1) / 2) + tw_lds_entries(n, es));
+}
+constexpr bool has_plane(int n) { return seven_smooth(n) && n <= 63; }
+
+template <typename T, int FI>
+__global__ __launch_bounds__(plane_nt(kFastSched[FI].n), 4)
+void plane_iso(const RowArgs *__restrict__ ra, const int *__restrict__ woff, int np) {
+    using V = Vt<T>;
+    constexpr int N = kFastSched[FI].n;
+    constexpr int S = kFastSched[FI].nst;
+    constexpr int R = pairs_rl(FI);
+    constexpr int TQ = N / R;
+    constexpr int NT = plane_nt(N);
+    constexpr int H = (N + 1) / 2;         // frequencies along axis 2, row pairs
+    constexpr int NHC = staged_nhc(N);     // frequencies along axis 3
+    constexpr int NB = 3 * NHC;            // axis-2 transforms, LDS layout [pos][component][k3]
+    constexpr int TB = 3 * H;              // row pair transforms, LDS layout [component][pair][pos]
+    constexpr int OFFL = sched_off(FI, S - 1);
+    int lb;
+    const RowArgs &a = ra[find_problem(woff, np, &lb)];
+    if (a.status != nullptr && a.status->done) return;
+    extern __shared__ __align__(16) unsigned char smem_raw[];  // 16-byte complex doubles
+    V *X = reinterpret_cast<V *>(smem_raw);
+    const int nh = a.Nh_row, L2 = a.L2;
+    auto *data = gbl(reinterpret_cast<V *>(a.data) + (long)lb * L2 * nh);
+    const auto *gsrc = gbl(reinterpret_cast<const T *>(a.g) + (long)lb * N * N);
+    const V zero = mk<T>(T(0), T(0));
+    constexpr int PI = (3 * H * NHC + NT - 1) / NT;
+    {
+        T vx[PI], vy[PI];
+#pragma unroll
+        for (int t = 0; t < PI; ++t) {
+            const int idx = threadIdx.x + t * NT;
+            const int k = idx % NHC, l = idx / NHC % H, c = idx / (NHC * H);
+            const bool ok = c < 3 && l < L2 && k < nh;
+            const V v = gld(data + (ok ? c * a.cs + l * nh + k : 0L));
+            vx[t] = ok ? v.x : T(0);
+            vy[t] = ok ? v.y : T(0);
+        }
+        const int khi = (L2 + 1) / 2;
+        for (int idx = threadIdx.x; idx < (N - L2) * NB; idx += NT) X[khi * NB + idx] = zero;
+#pragma unroll
+        for (int t = 0; t < PI; ++t) {
+            const int idx = threadIdx.x + t * NT;
+            const int k = idx % NHC, l = idx / NHC % H, c = idx / (NHC * H);
+            if (c < 3 && l < L2) X[posmod(wrapi(l, L2), N) * NB + c * NHC + k] = mk<T>(vx[t], vy[t]);
+        }
+    }
+    const V *tw = twiddles_to_lds<T, N, NT>(X + N * TB, reinterpret_cast<const V *>(a.tw) + a.f.twoff[0]);
+    __syncthreads();
+    fft_ip<T, FI, 0, 1, 0, NB, false, NT>(X, tw, T(1));
+    constexpr int PL = (TB * NHC + NT - 1) / NT;
+    {  // two rows of a pair as one complex row
+        V u1[PL], u2[PL];
+#pragma unroll
+        for (int t = 0; t < PL; ++t) {
+            const int idx = threadIdx.x + t * NT;
+            const int tr = idx / NHC, k = idx % NHC;
+            const int c = tr / H, x2 = 2 * (tr % H);
+            u1[t] = u2[t] = zero;
+            if (idx < TB * NHC) {
+                u1[t] = X[x2 * NB + c * NHC + k];
+                if (x2 + 1 < N) u2[t] = X[(x2 + 1) * NB + c * NHC + k];
+            }
+        }
+        __syncthreads();
+        const int nz = N - 2 * nh + 1;  // zero band nh .. N - nh of every row
+        for (int idx = threadIdx.x; idx < TB * nz; idx += NT) {
+            const int tr = idx / nz;
+            X[tr * N + nh + (idx - tr * nz)] = zero;
+        }
+#pragma unroll
+        for (int t = 0; t < PL; ++t) {
+            const int idx = threadIdx.x + t * NT;
+            const int tr = idx / NHC, k = idx % NHC;
+            if (idx >= TB * NHC || k >= nh) continue;
+            V *xr = X + tr * N;
+            if (k == 0) {
+                xr[0] = mk<T>(u1[t].x, u2[t].x);
+            } else {
+                xr[k] = mk<T>(u1[t].x - u2[t].y, u1[t].y + u2[t].x);
+                xr[N - k] = mk<T>(u1[t].x + u2[t].y, u2[t].x - u1[t].y);
+            }
+        }
+    }
+    __syncthreads();
+    fft_mid<T, FI, 0, S - 1, TB, NT>(X, tw, T(1));
+    {
+        const T a0 = T(a.A0[0]);
+        const T da = T(a.D[0]);
+        for (int idx = threadIdx.x; idx < TQ * TB; idx += NT) {
+            const int tr = idx / TQ, i = idx % TQ;
+            const int x2 = 2 * (tr % H);
+            V *xr = X + tr * N + i;
+            const auto *gp = gsrc + x2 * N + i;
+            const auto *gq = x2 + 1 < N ? gp + N : gp;  // a missing second row repeats the first
+            T g1[R], g2[R];
+#pragma unroll
+            for (int q = 0; q < R; ++q) {
+                g1[q] = gp[q * TQ];
+                g2[q] = gq[q * TQ];
+            }
+            V u[R];
+#pragma unroll
+            for (int q = 0; q < R; ++q) u[q] = xr[q * TQ];
+#pragma unroll
+            for (int q = 1; q < R; ++q) {
+                V w = tw[OFFL + (q - 1) * TQ + i];
+                w.y = -w.y;
+                u[q] = cmul(u[q], w);
+            }
+            dftn<T, R>(u, T(1));
+#pragma unroll
+            for (int q = 0; q < R; ++q) {
+                u[q].x *= a0 + g1[q] * da;
+                u[q].y *= a0 + g2[q] * da;
+            }
+            dftn<T, R>(u, T(-1));
+#pragma unroll
+            for (int q = 1; q < R; ++q) u[q] = cmul(u[q], tw[OFFL + (q - 1) * TQ + i]);
+#pragma unroll
+            for (int q = 0; q < R; ++q) xr[q * TQ] = u[q];
+        }
+    }
+    __syncthreads();
+    fft_tr<T, FI, S - 2, TB, NT>(X, tw, T(-1));
+    {  // the half spectra of both rows of a pair
+        const T half = T(a.scale) * T(0.5);
+        V w[PL], wm[PL];
+#pragma unroll
+        for (int t = 0; t < PL; ++t) {
+            const int idx = threadIdx.x + t * NT;
+            const int tr = idx / NHC, k = idx % NHC;
+            w[t] = wm[t] = zero;
+            if (idx < TB * NHC) {
+                w[t] = X[tr * N + k];
+                wm[t] = X[tr * N + (k == 0 ? 0 : N - k)];
+            }
+        }
+        __syncthreads();
+#pragma unroll
+        for (int t = 0; t < PL; ++t) {
+            const int idx = threadIdx.x + t * NT;
+            const int tr = idx / NHC, k = idx % NHC;
+            const int c = tr / H, x2 = 2 * (tr % H);
+            if (idx >= TB * NHC) continue;
+            V *x = X + x2 * NB + c * NHC + k;
+            x[0] = mk<T>((w[t].x + wm[t].x) * half, (w[t].y - wm[t].y) * half);
+            if (x2 + 1 < N) x[NB] = mk<T>((w[t].y + wm[t].y) * half, (wm[t].x - w[t].x) * half);
+        }
+    }
+    __syncthreads();
+    fft_ip<T, FI, 0, 1, 0, NB, false, NT>(X, tw, T(-1));
+#pragma unroll
+    for (int t = 0; t < PI; ++t) {
+        const int idx = threadIdx.x + t * NT;
+        const int k = idx % NHC, l = idx / NHC % H, c = idx / (NHC * H);
+        if (c < 3 && l < L2 && k < nh)
+            gst(data + (c * a.cs + l * nh + k), X[posmod(wrapi(l, L2), N) * NB + c * NHC + k]);
+    }
+}
+
 // Row pass of an isotropic material with Bluestein transforms (rows of any
 // length n = a.f.n <= (N + 1) / 2): as row_iso_pairs, with each transform a
 // convolution of length N.  Between the inverse and the forward transform the
@@ -1947,6 +2127,12 @@ void launch_pairs_t(const RowArgs *args, const int *woff, int np, int total, hip
              pairs_lds(FI, sizeof(Vt<T>), D), Disp(s, ev), args, woff, np);
 }
 
+template <typename T, int FI>
+void launch_plane_t(const RowArgs *args, const int *woff, int np, int total, hipStream_t s, LaunchEv ev) {
+    constexpr int N = kFastSched[FI].n;
+    dispatch((plane_iso<T, FI>), dim3(total), dim3(plane_nt(N)), plane_lds(N, sizeof(Vt<T>)), Disp(s, ev), args, woff, np);
+}
+
 template <int FI, int D>
 void launch_gram_t(const RowArgs *args, const int *woff, int np, int total, hipStream_t s, LaunchEv ev) {
     dispatch((row_gram_fast<double, FI, D>), dim3(total), dim3(kThreads), gram_lds(kFastSched[FI].n, D), Disp(s, ev),
@@ -1975,6 +2161,8 @@ void fill_dim(FastKernels &k) {
         else if constexpr (has_pairs(FI))
             (pairs_one(n, es, D) ? k.iso : k.pairs)[p][D - 2] = {launch_pairs_t<T, FI, D>, pairs_tb(n, es, D),
                                                                  (n + 1) / 2, pairs_lds(FI, es, D)};
+        if constexpr (D == 3 && has_plane(n))
+            k.plane[p] = {launch_plane_t<T, FI>, 1, staged_nhc(n), plane_lds(n, es)};
         if constexpr (has_iso(FI)) k.iso[p][D - 2] = {launch_iso_t<T, FI>, iso_tb(FI), (n + 1) / 2, iso_lds<T>(FI)};
     }
 }

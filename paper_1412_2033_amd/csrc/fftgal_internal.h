@@ -207,6 +207,7 @@ struct RowArgs {
     // generic kernel: the components' rows form one batch of transforms (LDS
     // for two buffers of every component) instead of one batch per component
     int zbatch;
+    int L2;           // > 0: nrows planes x1 of L2 axis-2 frequencies (plane_iso); nrows rows otherwise
     double E[3];      // load for ROW_RHS
     void *real_out;   // ROW_C2R output rows (length n)
     const void *real_in;  // ROW_R2C input rows (length n)
@@ -395,6 +396,7 @@ struct FastKernels {
     Row row[2][2];    // any material: RP row pairs
     Row iso[2][2];    // isotropic: RP transforms (row pair, component)
     Row pairs[2][2];  // isotropic: RP transforms of whole row pairs
+    Row plane[2];     // isotropic, 3D: whole planes, axis 2 and rows
     Row gram[2];      // FP64 energy Gram: RP row pairs
     // Bluestein transforms through this convolution length
     Pencil blue_pencil[2][2];
@@ -406,6 +408,8 @@ template <int PART> void fill_fast(FastKernels *table);  // entries fi with fi %
 const FastKernels &fast_kernels(int fi);
 hipError_t launch_pencil_multi(const PencilArgs &proto, const PencilArgs *args, const int *woff, int np,
                                int total, bool fp64, hipStream_t s, LaunchEv ev = LaunchEv{});
+// Whether plane_iso takes planes of L2 x nh frequencies on an f.n x f.n grid.
+bool plane_fits(const FftDesc &f, int L2, int nh, bool fp64);
 hipError_t launch_row_multi(const RowArgs &proto, const RowArgs *args, const int *woff, int np, int total,
                             bool fp64, hipStream_t s, LaunchEv ev = LaunchEv{});
 hipError_t launch_cg_check_multi(const CgItem *items, int np, hipStream_t s, LaunchEv ev = LaunchEv{});

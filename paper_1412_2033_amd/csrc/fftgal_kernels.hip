@@ -1884,7 +1884,8 @@ const FastKernels &fast_kernels(int fi) {
 // specialised kernel: pencils 1 (a length of kFastSched), 2 (Bluestein), 3 and 4
 // (the same for the two components of 3D gradient fields); rows
 // 1 (any material; energy Gram), 2 (isotropic, single transforms), 3
-// (isotropic, whole row pairs), 4 and 5 (Bluestein: whole row pairs, single).
+// (isotropic, whole row pairs), 4 and 5 (Bluestein: whole row pairs, single), 6
+// (isotropic, planes).
 static const FastKernels::Pencil &fast_pencil(const PencilArgs &a, bool fp64) {
     const FastKernels &k = fast_kernels(fast_index(a.f.L));
     switch (a.fast) {
@@ -1901,6 +1902,7 @@ static const FastKernels::Row &fast_row(const RowArgs &a, bool fp64) {
         case 1: return k.row[fp64][a.d - 2];
         case 2: return k.iso[fp64][a.d - 2];
         case 3: return k.pairs[fp64][a.d - 2];
+        case 6: return k.plane[fp64];
         default: return k.blue_row[fp64][a.d - 2];
     }
 }
@@ -1926,6 +1928,7 @@ size_t row_lds_bytes(const RowArgs &a, bool fp64) {
 int pencil_grid_x(const PencilArgs &a) { return a.B > 0 ? (a.nb + a.B - 1) / a.B : 0; }
 int row_grid(const RowArgs &a) {
     if (a.RP < 1) return 0;
+    if (a.fast == 6) return a.nrows;
     if (a.mode == ROW_GRAM && a.gpack && !a.fast) return (a.nrows + a.RP - 1) / a.RP;
     const int pairs = (a.nrows + 1) / 2;
     if (a.fast == 3 || a.fast == 4) return (pairs + a.RP / a.d - 1) / (a.RP / a.d);
@@ -1980,7 +1983,19 @@ void fit_pencil_components(PencilArgs &a, bool fp64) {
     if (a.twl < 1 || pencil_lds_bytes(a, fp64) > kGenericLds) a.twl = 0;
 }
 
+bool plane_fits(const FftDesc &f, int L2, int nh, bool fp64) {
+    const int fi = fast_of(f);
+    if (fi < 0 || f.blue) return false;
+    const FastKernels::Row &e = fast_kernels(fi).plane[fp64];
+    return e.fn && nh <= e.nh_max && 2 * L2 <= f.n + 1;
+}
+
 void configure_row(RowArgs &r, bool fp64) {
+    if (r.L2 > 0) {  // plane_fits
+        r.fast = 6;
+        r.RP = 1;
+        return;
+    }
     const int fi = fast_of(r.f);
     if (fi >= 0 && (r.d == 2 || r.d == 3)) {
         const FastKernels &k = fast_kernels(fi);
