@@ -61,8 +61,9 @@ __device__ __forceinline__ void stage(const Vt<T> *X, Vt<T> *Y, int n, int p, in
 }
 
 // The stages of a transform of length f.L in LDS, ping-ponging between A and
-// Bf; returns the buffer holding the result.
-template <typename T, bool ROWL>
+// Bf; returns the buffer holding the result.  P13: lengths with the factors 11 or
+// 13 too; lengths that have them do not use radix 25.
+template <typename T, bool ROWL, bool P13>
 __device__ __forceinline__ Vt<T> *fft_stages(Vt<T> *A, Vt<T> *Bf, const FftDesc &f, int nb, const Vt<T> *tw, T sg,
                                               int tb = 0) {
     Vt<T> *X = A;
@@ -76,10 +77,16 @@ __device__ __forceinline__ Vt<T> *fft_stages(Vt<T> *A, Vt<T> *Bf, const FftDesc 
             case 5: stage<T, 5, ROWL>(X, Y, f.L, p, nb, t, sg); break;
             case 7: stage<T, 7, ROWL>(X, Y, f.L, p, nb, t, sg); break;
             case 9: stage<T, 9, ROWL>(X, Y, f.L, p, nb, t, sg); break;
-            case 11: stage<T, 11, ROWL>(X, Y, f.L, p, nb, t, sg); break;
-            case 13: stage<T, 13, ROWL>(X, Y, f.L, p, nb, t, sg); break;
             case 15: stage<T, 15, ROWL>(X, Y, f.L, p, nb, t, sg); break;
-            default: stage<T, 25, ROWL>(X, Y, f.L, p, nb, t, sg); break;
+            default:
+                if constexpr (P13) {
+                    if (r == 11)
+                        stage<T, 11, ROWL>(X, Y, f.L, p, nb, t, sg);
+                    else
+                        stage<T, 13, ROWL>(X, Y, f.L, p, nb, t, sg);
+                } else {
+                    stage<T, 25, ROWL>(X, Y, f.L, p, nb, t, sg);
+                }
         }
         __syncthreads();
         Vt<T> *tmp = X;
@@ -94,10 +101,10 @@ __device__ __forceinline__ Vt<T> *fft_stages(Vt<T> *A, Vt<T> *Bf, const FftDesc 
 // buffers of f.L positions; ROWL: element (pos, b) at b L + pos, else
 // pos nb + b); returns the buffer holding the result.  Must be called by
 // every thread of the work-group.
-template <typename T, bool ROWL>
+template <typename T, bool ROWL, bool P13>
 __device__ __forceinline__ Vt<T> *fft_lds(Vt<T> *A, Vt<T> *Bf, const FftDesc &f, int nb, const Vt<T> *tw, T sg,
                                            int tb = 0) {
-    if (!f.blue) return fft_stages<T, ROWL>(A, Bf, f, nb, tw, sg, tb);
+    if (P13 || !f.blue) return fft_stages<T, ROWL, P13>(A, Bf, f, nb, tw, sg, tb);
     // Bluestein: u_j = x_j c_j zero-padded to L, H (.) DFT^- u, DFT^+, times c_k
     const int n = f.n, L = f.L;
     const Vt<T> *chirp = tw + (f.choff - tb);
@@ -114,7 +121,7 @@ __device__ __forceinline__ Vt<T> *fft_lds(Vt<T> *A, Vt<T> *Bf, const FftDesc &f,
         v = pos < n ? cmul(v, chirp_of(pos)) : mk<T>(T(0), T(0));
     }
     __syncthreads();
-    Vt<T> *X = fft_stages<T, ROWL>(A, Bf, f, nb, tw, T(-1), tb);
+    Vt<T> *X = fft_stages<T, ROWL, false>(A, Bf, f, nb, tw, T(-1), tb);
     for (int idx = threadIdx.x; idx < L * nb; idx += blockDim.x) {
         const int b = idx / L, k = idx - b * L;
         // H for the sign sg: H_k (sg = +1) or conj(H_{-k}) (sg = -1)
@@ -124,7 +131,7 @@ __device__ __forceinline__ Vt<T> *fft_lds(Vt<T> *A, Vt<T> *Bf, const FftDesc &f,
         v = cmul(v, h);
     }
     __syncthreads();
-    Vt<T> *Y = fft_stages<T, ROWL>(X, X == A ? Bf : A, f, nb, tw, T(1), tb);
+    Vt<T> *Y = fft_stages<T, ROWL, false>(X, X == A ? Bf : A, f, nb, tw, T(1), tb);
     for (int idx = threadIdx.x; idx < n * nb; idx += blockDim.x) {
         const int b = idx / n, pos = idx - b * n;
         Vt<T> &v = at(Y, pos, b);
@@ -148,7 +155,7 @@ __device__ __forceinline__ T pick3(const T *t, int al) {
 // one batch of cb * B sequences (layout: position * (cn B) + j B + b for
 // component al0 + j of the chunk), so that a small grid runs one chain of
 // stages and barriers per work-group instead of one per component.
-template <typename T>
+template <typename T, bool P13>
 __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2))) void pencil_kernel(PencilArgs a) {
     using V = Vt<T>;
     if (a.status != nullptr && a.status->done) return;
@@ -255,7 +262,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2))) v
                     }
                 }
                 __syncthreads();
-                V *res = fft_lds<T, false>(bufA, bufB, a.f, nbt, tw, sg, tb);
+                V *res = fft_lds<T, false, P13>(bufA, bufB, a.f, nbt, tw, sg, tb);
                 for (int idx = threadIdx.x; idx < a.L_out * nbt; idx += blockDim.x) {
                     const int bt = idx % nbt;
                     const int l = idx / nbt;
@@ -297,7 +304,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2))) v
             bufA[posmod(wrapi(l, a.L_in), n) * nbt + bt] = v;
         }
         __syncthreads();
-        V *res = fft_lds<T, false>(bufA, bufB, a.f, nbt, tw, sg, tb);
+        V *res = fft_lds<T, false, P13>(bufA, bufB, a.f, nbt, tw, sg, tb);
         if (a.epi == EPI_PROJECT) {
             // q_a += -i t_a(k)_alpha yhat_alpha(k) on Z_N, alpha in ascending order
             for (int idx = threadIdx.x; idx < a.L_out * B; idx += blockDim.x) {
@@ -547,7 +554,7 @@ __host__ __device__ inline int row_zbufs(const RowArgs &a) {
     return a.ncomp;
 }
 
-template <typename T, int DIM>
+template <typename T, int DIM, bool P13>
 __global__ __launch_bounds__(kThreads) void row_kernel(RowArgs a) {
     using V = Vt<T>;
     if (a.status != nullptr && a.status->done) return;
@@ -575,7 +582,7 @@ __global__ __launch_bounds__(kThreads) void row_kernel(RowArgs a) {
 
     auto zbuf = [&](int c) { return Z + (size_t)c * RP * ln; };
     auto fft_into = [&](int c, T sg) {
-        V *res = fft_lds<T, true>(zbuf(c), S, a.f, RP, tw, sg);
+        V *res = fft_lds<T, true, P13>(zbuf(c), S, a.f, RP, tw, sg);
         if (res != zbuf(c)) {
             for (int idx = threadIdx.x; idx < RP * ln; idx += blockDim.x) zbuf(c)[idx] = res[idx];
             __syncthreads();
@@ -681,7 +688,7 @@ __global__ __launch_bounds__(kThreads) void row_kernel(RowArgs a) {
             }
         }
         __syncthreads();
-        const V *res = fft_lds<T, true>(Z, S, a.f, nall, tw, T(1));
+        const V *res = fft_lds<T, true, P13>(Z, S, a.f, nall, tw, T(1));
         if (res != Z) {
             for (int idx = threadIdx.x; idx < nall * ln; idx += blockDim.x) Z[idx] = res[idx];
             __syncthreads();
@@ -859,7 +866,7 @@ __global__ __launch_bounds__(kThreads) void row_kernel(RowArgs a) {
     // ---- forward transforms and Hermitian split ----
     const T half = T(a.scale) * T(0.5);
     if (zb) {
-        const V *res = fft_lds<T, true>(Z, S, a.f, nzc * RP, tw, T(-1));
+        const V *res = fft_lds<T, true, P13>(Z, S, a.f, nzc * RP, tw, T(-1));
         for (int idx = threadIdx.x; idx < nzc * RP * nh; idx += blockDim.x) {
             const int cj = idx / nh;
             const int kx = idx - cj * nh;
@@ -2033,15 +2040,25 @@ void fit_row_batch(RowArgs &r, bool fp64) {
     if (row_lds_bytes(r, fp64) > kGenericLds) r.zbatch = 0;
 }
 
+// Whether the generic kernels take f in their form with radices 11 and 13.  In
+// one kernel with all eight radices the row passes kept their arguments in
+// scratch memory (620 bytes, one wave per SIMD against three): the energies of
+// 3D GaNi fields of order 225 on 525^3 took 141 ms instead of 40.
+static bool has_13(const FftDesc &f) {
+    for (int st = 0; st < f.nst; ++st)
+        if (f.radix[st] == 11 || f.radix[st] == 13) return true;
+    return false;
+}
+
 hipError_t launch_pencil(const PencilArgs &a, int nouter, bool fp64, hipStream_t s) {
     if (a.B < 1 || nouter < 1 || a.fast) return hipErrorInvalidValue;
     dim3 grid(pencil_grid_x(a), nouter);
     const size_t lds = pencil_lds_bytes(a, fp64);
-    if (fp64) {
-        hipLaunchKernelGGL(pencil_kernel<double>, grid, dim3(kThreads), lds, s, a);
-    } else {
-        hipLaunchKernelGGL(pencil_kernel<float>, grid, dim3(kThreads), lds, s, a);
-    }
+    auto go = [&](auto kernel) { hipLaunchKernelGGL(kernel, grid, dim3(kThreads), lds, s, a); };
+    if (has_13(a.f))
+        fp64 ? go(pencil_kernel<double, true>) : go(pencil_kernel<float, true>);
+    else
+        fp64 ? go(pencil_kernel<double, false>) : go(pencil_kernel<float, false>);
     return hipGetLastError();
 }
 
@@ -2049,16 +2066,17 @@ hipError_t launch_row(const RowArgs &a, bool fp64, hipStream_t s) {
     if (a.RP < 1 || a.fast) return hipErrorInvalidValue;
     const size_t lds = row_lds_bytes(a, fp64);
     if (a.d != 2 && a.d != 3) return hipErrorInvalidValue;
-    if (fp64) {
+    auto go = [&](auto kernel) { hipLaunchKernelGGL(kernel, dim3(row_grid(a)), dim3(kThreads), lds, s, a); };
+    if (has_13(a.f)) {
         if (a.d == 3)
-            hipLaunchKernelGGL((row_kernel<double, 3>), dim3(row_grid(a)), dim3(kThreads), lds, s, a);
+            fp64 ? go(row_kernel<double, 3, true>) : go(row_kernel<float, 3, true>);
         else
-            hipLaunchKernelGGL((row_kernel<double, 2>), dim3(row_grid(a)), dim3(kThreads), lds, s, a);
+            fp64 ? go(row_kernel<double, 2, true>) : go(row_kernel<float, 2, true>);
     } else {
         if (a.d == 3)
-            hipLaunchKernelGGL((row_kernel<float, 3>), dim3(row_grid(a)), dim3(kThreads), lds, s, a);
+            fp64 ? go(row_kernel<double, 3, false>) : go(row_kernel<float, 3, false>);
         else
-            hipLaunchKernelGGL((row_kernel<float, 2>), dim3(row_grid(a)), dim3(kThreads), lds, s, a);
+            fp64 ? go(row_kernel<double, 2, false>) : go(row_kernel<float, 2, false>);
     }
     return hipGetLastError();
 }
@@ -2076,6 +2094,9 @@ constexpr size_t kSoloLds = 160 * 1024 - 1024;
 // Threads of the run-time-length form: few on small grids, then whatever the
 // registers of the in-place stages (solo_per) and of the CG vectors
 // (solo_cpt) need; 0 if the grid does not fit.
+// A serial chain of stages and barriers bounds the kernel, so threads without
+// work only cost barriers.  2D order 11 (21 x 21), FP64: 29 us per iteration in five
+// launches of single passes -> 4.4 us here.
 static int solo_threads(const SoloArgs &a, bool fp64) {
     const long pts = (long)a.M0 * a.M1;
     for (int nt = pts <= 1500 ? 256 : pts <= 4000 ? 512 : 1024; nt <= 1024; nt *= 2) {
