@@ -68,7 +68,8 @@ def algorithmic_bytes(cls, d, N, M, es, gs, nc):
     Nh = (N[-1] + 1) // 2
     Ns = (N[0] * N[1] if d == 3 else N[0]) * Nh
     if d == 3:
-        t1 = d * M[0] * N[1] * Nh
+        # primal (nc = 1) fields of large grids have two components between axis 1 and axis 2
+        t1 = (2 if nc == 1 and M[0] * M[1] * M[2] >= 343000 else d) * M[0] * N[1] * Nh
         t2 = d * M[0] * M[1] * Nh
     else:
         t1 = t2 = d * M[0] * Nh

@@ -382,11 +382,13 @@ int fftgal_bounds_of(struct fftgal_plan *plan, struct fftgal_plan *src, double *
  * inverse DFT of size N), and every operator application runs the transform
  * passes once per shift with the phases S(s), S*(s) of the lemma, summing the
  * projected results.  Every N_a must be odd; 3,5,7-smooth lengths from 9 to
- * 2025 (3D: to 405, and 729 and 2025) run the specialised kernels, other smooth
+ * 2025 (3D: to 405, and 729 and 2025) and the lengths to 385 with factors 11
+ * and 13 run the specialised kernels, other smooth
  * lengths the generic ones, and the other lengths (the primes 41, 113, 1013
  * among them) Bluestein's chirp convolution of the smooth length L >= 2 N_a - 1
- * in the generic kernels.  Solves, bounds, history and the bound tolerance work as for fftgal_plan; warm starts, a-posteriori
- * bounds and batches are not available (EINVAL).  The workspace holds 2^d
+ * (in specialised kernels when L has them).  Solves, bounds, history and the
+ * bound tolerance work as for fftgal_plan; warm starts, a-posteriori bounds and
+ * batches are not available (EINVAL).  The workspace holds 2^d
  * material fields of |N| values and transform intermediates of the N-grid:
  * fftgal_workspace_bytes_reduced (P as in fftgal_workspace_bytes_p).  With the
  * default layout and specialised transform lengths the shifts of each operator

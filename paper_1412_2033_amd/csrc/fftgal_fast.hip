@@ -244,6 +244,10 @@ constexpr int pencil_nt(int n, int es, int d, bool blue = false) {
                : kThreads;
 }
 
+// Bound by memory on large grids (3D, order 113: 4.3 to 4.9 TB/s), on small ones
+// by the latency of its loads and stages.  Against the kernel of run-time
+// lengths, FP64: 175^3 65 -> 19 us a launch, BLUE 99^3 (through 225) 102 -> 27 us.
+//
 // BLUE: Bluestein transforms of the length a.f.n through the convolution
 // length N; the inputs are multiplied by the chirp on their way into LDS, the
 // outputs on their way out.
@@ -1572,7 +1576,9 @@ __global__ __launch_bounds__(kThreads) void row_gram_fast(const RowArgs *__restr
 // between the two transforms needs an exchange, whatever the radices.  Rows
 // whose D transforms would take more than 16 KB run one transform per
 // work-group (pair-major, material values read at the multiply), so that
-// several work-groups share a CU.
+// several work-groups share a CU.  It is bound by memory on large grids and by
+// its LDS stages on small ones: 175^3 FP64 55 us a launch (2.6 TB/s), against
+// 138 us in the kernel of run-time lengths.
 constexpr bool pairs_one(int n, int es, int d) { return d * n * es > 16 * 1024; }
 constexpr int pairs_pw(int n, int es, int d) {
     const int cap = 20 * 1024;
@@ -1580,7 +1586,8 @@ constexpr int pairs_pw(int n, int es, int d) {
     while (p > 1 && d * p * n * es > cap) --p;
     return p;
 }
-// 125 points keep the general row pass: the best-iterate guard of FP32 solves
+// 125 points keep the general row pass (3D, order 63, one iteration of
+// all six solves: 323 us FP32 and 375 FP64 with it, 325 and 372 with this one): the best-iterate guard of FP32 solves
 // at contrasts near 1e4 compares energies at the rounding level of the operator
 // (they cancel to 1e-3 of its terms), and its tests hold the outcome for the
 // rounding of that pass
@@ -1949,8 +1956,9 @@ void plane_iso(const RowArgs *__restrict__ ra, const int *__restrict__ woff, int
 // chirp of the one, the material and the chirp of the other multiply the n
 // points of the row (the rest is zero padding) and the first stage of the
 // forward convolution follows on the same points.
-// (one pair of 225 FP64 points, 64 threads: 46.6 us at order 99 against 50.6
-// for two pairs and 128 threads)
+// It is bound by its two convolutions' stages: one pair of 225 FP64 points, 64
+// threads, takes 46.6 us at order 99, two pairs and 128 threads 50.6, the kernel
+// of run-time lengths took 157.
 constexpr int blue_pw(int n, int es, int d) {
     int p = d == 3 ? 4 : 2;
     while (p > 1 && d * p * n * es > 18 * 1024) --p;

@@ -24,8 +24,8 @@ FP32_ITER = 1
 REDUCED_LEAN = 0x100  # reduced Ga laid out with one set of intermediates (shifts in turn)
 TENSOR = 0x200  # d(d+1)/2 material fields per side (matrix images, anisotropic multi-phase inclusions)
 CONCURRENT = 0x400  # per-solve buffers for all 2d solves: they may run at once
-SEPARATE_PASSES = 0x800  # small 2D grids: per-pass kernels instead of one work-group per solve
-FAST_GRID = 0x1000  # Ga plans: the double grid with specialised kernels if it holds at most 4x the points
+SEPARATE_PASSES = 0x800  # small grids: per-pass kernels instead of one work-group per 2D solve or 3D plane
+FAST_GRID = 0x1000  # Ga plans: the next of six double-grid lengths if the grid holds at most 4x the points
 PRECISIONS = {"fp64": FP64, "fp32": FP32_ITER, "fp32_iter": FP32_ITER}
 
 STATUS = {0: "OK", -1: "EINVAL", -2: "ENOMEM", -3: "EDEVICE", -4: "ENOTCONV", -5: "ESTATE", -6: "EBREAKDOWN"}

@@ -12,8 +12,8 @@ single solve already fills the GPU, keep one buffer set (a request's solves
 then run one after another), and so does every plan with concurrent=False.
 When a request's last solve retires, its bounds are evaluated (FP64
 quadrature) and its latency recorded.  Plans are made with FFTGAL_FAST_GRID
-by default: orders whose smallest double grid has no specialised kernels run
-on a slightly larger grid that has them, with the same bounds.
+by default: the next of a few fixed grid lengths, so that requests of
+near orders share launches, with the same bounds.
 
 All scheduling is host logic; every step of the computation runs in the HIP
 library.
