@@ -290,6 +290,14 @@ int fftgal_solve_dual(struct fftgal_plan *plan, int alpha, double rtol, int maxi
 int fftgal_solve_all(struct fftgal_plan *plan, double rtol, int maxit, fftgal_info *info);
 
 /*
+ * What the last finished solve of (kind 0 primal / 1 dual, alpha) returned: OK,
+ * ENOTCONV or EBREAKDOWN; with alpha = -1 the first non-OK of the d solves of
+ * the kind, as fftgal_solve_primal / fftgal_solve_dual return it.  ESTATE while
+ * there is no such solve, EINVAL for a kind or alpha out of range.
+ */
+int fftgal_outcome(struct fftgal_plan *plan, int kind, int alpha);
+
+/*
  * Guaranteed bounds from the d primal and d dual fields (Prop. struct_bounds):
  * upper = A_{H,N} and lower = B_{H,N}^{-1}, each d x d row-major on the host,
  * and gap = tr(upper - lower)/2 (eq. error).  The energy Gram matrices

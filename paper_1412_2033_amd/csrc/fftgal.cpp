@@ -444,6 +444,7 @@ struct fftgal_plan {
     // the layout when the image resolution exceeds what the layout provisions
     size_t vox_tw64 = 0, vox_tw32 = 0, vox_u = 0, vox_w = 0;
     fftgal_info last_info[2][3];
+    bool broke[2][3] = {{false, false, false}, {false, false, false}};  // the last solve ended in a CG breakdown
     int busy = 0;          // solves of this plan that are members of a batch
     size_t bws_off = 0, bws_len = 0;  // workspace of the internal batch (FFTGAL_CONCURRENT)
     std::vector<char> slot_used;                               // solve slots held by batch members
@@ -1580,6 +1581,17 @@ int start_solve(Plan *pl, int kind, int alpha, double rtol, int maxit) {
     return FFTGAL_OK;
 }
 
+// Code of a finished solve (and, when it is not OK, the plan's error message).
+int outcome(Plan *pl, int kind, int alpha) {
+    const fftgal_info &i = pl->last_info[kind][alpha];
+    if (pl->broke[kind][alpha]) return fail(pl, FFTGAL_EBREAKDOWN, "CG breakdown (non-SPD or non-finite material)");
+    if (i.stagnated)
+        return fail(pl, FFTGAL_ENOTCONV, "FP32 iterations stalled after %d iterations; the field of iteration %d "
+                    "(lowest exact energy) is kept", i.iters, i.iterate);
+    if (!i.converged) return fail(pl, FFTGAL_ENOTCONV, "CG did not converge in %d iterations", i.iters);
+    return FFTGAL_OK;
+}
+
 int finish_solve(Plan *pl, int kind, int alpha, const CgStatus &h, fftgal_info *info) {
     fftgal_info inf{};
     inf.iters = h.iter;
@@ -1589,14 +1601,10 @@ int finish_solve(Plan *pl, int kind, int alpha, const CgStatus &h, fftgal_info *
     inf.stagnated = h.stagnated;
     inf.iterate = h.ck_restore ? h.best_it : h.iter;
     pl->last_info[kind][alpha] = inf;
+    pl->broke[kind][alpha] = h.breakdown != 0;
     if (info) *info = inf;
     pl->solved[kind][alpha] = true;
-    if (h.breakdown) return fail(pl, FFTGAL_EBREAKDOWN, "CG breakdown (non-SPD or non-finite material)");
-    if (h.stagnated)
-        return fail(pl, FFTGAL_ENOTCONV, "FP32 iterations stalled after %d iterations; the field of iteration %d "
-                    "(lowest exact energy) is kept", h.iter, inf.iterate);
-    if (!h.converged) return fail(pl, FFTGAL_ENOTCONV, "CG did not converge in %d iterations", h.maxit);
-    return FFTGAL_OK;
+    return outcome(pl, kind, alpha);
 }
 
 // After an FP32 solve that stopped without converging (at maxit or on a stall
@@ -2630,6 +2638,7 @@ int fftgal_bounds_of(struct fftgal_plan *pl, struct fftgal_plan *src, double *up
             pl->warm[k][a] = false;
             pl->hist_valid[k][a] = false;
             pl->last_info[k][a] = src->last_info[k][a];
+            pl->broke[k][a] = src->broke[k][a];
         }
     return fftgal_bounds(pl, upper, lower, gap);
 }
@@ -3032,7 +3041,7 @@ int run_stages(Plan *pl, const std::vector<PassRec> &ps, int width, int cls) {
 // (may be NULL) receives the outcomes in the order of the jobs.
 int group_solve(Plan *pl, const std::vector<std::pair<int, int>> &jobs, double rtol, int maxit, fftgal_info *info) {
     const bool fp64 = pl->fp64_iter();
-    int worst = FFTGAL_OK;
+    int first = -1;  // the first job that is not OK
     for (size_t j0 = 0; j0 < jobs.size(); j0 += pl->at_once) {
         const size_t n = std::min(jobs.size() - j0, (size_t)pl->at_once);
         Batch b;
@@ -3111,10 +3120,10 @@ int group_solve(Plan *pl, const std::vector<std::pair<int, int>> &jobs, double r
             pl->slot = 0;
             if (rc) return rc;
             rc = finish_solve(pl, m.kind, m.alpha, h, info ? info + j0 + j : nullptr);
-            if (rc != FFTGAL_OK && worst == FFTGAL_OK) worst = rc;
+            if (rc != FFTGAL_OK && first < 0) first = (int)(j0 + j);
         }
     }
-    return worst;
+    return first < 0 ? FFTGAL_OK : outcome(pl, jobs[first].first, jobs[first].second);
 }
 
 }  // namespace
@@ -3279,7 +3288,7 @@ int fftgal_solve_all(struct fftgal_plan *pl, double rtol, int maxit, fftgal_info
         if (hard(r1)) return r1;
         const int r2 = solve_entry(pl, KIND_J, -1, rtol, maxit, info ? info + d : nullptr);
         if (hard(r2)) return r2;
-        return r1 != FFTGAL_OK ? r1 : r2;
+        return r1 != FFTGAL_OK ? fftgal_outcome(pl, KIND_E, -1) : r2;
     }
     std::vector<std::pair<int, int>> jobs;
     for (int k = 0; k < 2; ++k)
@@ -3288,6 +3297,19 @@ int fftgal_solve_all(struct fftgal_plan *pl, double rtol, int maxit, fftgal_info
     if (conc && worst == FFTGAL_EBREAKDOWN) return fail(pl, worst, "CG breakdown (non-SPD or non-finite material)");
     if (conc && worst == FFTGAL_ENOTCONV) return fail(pl, worst, "a solve did not converge (see info)");
     return worst;
+}
+
+int fftgal_outcome(struct fftgal_plan *pl, int kind, int alpha) {
+    if (!pl) return FFTGAL_EINVAL;
+    if (kind != KIND_E && kind != KIND_J) return fail(pl, FFTGAL_EINVAL, "kind must be 0 (primal) or 1 (dual)");
+    if (alpha < -1 || alpha >= pl->D.d) return fail(pl, FFTGAL_EINVAL, "alpha %d out of range", alpha);
+    for (int a = 0; a < pl->D.d; ++a)
+        if ((alpha < 0 || a == alpha) && !pl->solved[kind][a]) return fail(pl, FFTGAL_ESTATE, "no finished solve");
+    for (int a = 0; a < pl->D.d; ++a) {
+        if (alpha >= 0 && a != alpha) continue;
+        if (const int rc = outcome(pl, kind, a)) return rc;
+    }
+    return FFTGAL_OK;
 }
 
 }  // extern "C"

@@ -35,6 +35,7 @@ EXPORTS = ("fftgal_workspace_bytes", "fftgal_workspace_bytes_p", "fftgal_plan", 
            "fftgal_warm_start", "fftgal_history", "fftgal_set_timing_classes", "fftgal_set_bound_tol",
            "fftgal_workspace_bytes_gani", "fftgal_plan_gani", "fftgal_bounds_of", "fftgal_envelope_images",
            "fftgal_workspace_bytes_reduced", "fftgal_plan_reduced", "fftgal_plan_static", "fftgal_solve_all",
+           "fftgal_outcome",
            "fftgal_static_workspace_bytes",
            "fftgal_batch_workspace_bytes", "fftgal_batch_create", "fftgal_batch_add", "fftgal_batch_step",
            "fftgal_batch_poll", "fftgal_batch_destroy", "fftgal_batch_last_error")
@@ -104,6 +105,8 @@ def load_library(path=LIB_PATH):
     lib.fftgal_set_material.restype = ctypes.c_int
     lib.fftgal_solve_all.argtypes = [vp, ctypes.c_double, ctypes.c_int, ctypes.POINTER(Info)]
     lib.fftgal_solve_all.restype = ctypes.c_int
+    lib.fftgal_outcome.argtypes = [vp, ctypes.c_int, ctypes.c_int]
+    lib.fftgal_outcome.restype = ctypes.c_int
     for name in ("fftgal_solve_primal", "fftgal_solve_dual"):
         f = getattr(lib, name)
         f.argtypes = [vp, ctypes.c_int, ctypes.c_double, ctypes.c_int, ctypes.POINTER(Info)]
@@ -306,6 +309,14 @@ def fftgal_solve_all(plan, d, rtol=1e-10, maxit=20000):
     return out[:d], out[d:], code
 
 
+def fftgal_outcome(plan, kind, alpha=-1):
+    """0 or -4 (ENOTCONV), as the solves of `kind` (0 primal, 1 dual) returned; any other outcome is raised."""
+    code = load_library().fftgal_outcome(plan, int(kind), int(alpha))
+    if code not in (0, -4):
+        _check(code, plan)
+    return code
+
+
 def fftgal_bounds(plan, d):
     up = (ctypes.c_double * (d * d))()
     lo = (ctypes.c_double * (d * d))()
@@ -448,8 +459,8 @@ class Plan:
         ip, idl, code = fftgal_solve_all(self.handle, self.d, rtol, maxit)
         if self.concurrent:
             cp = cd = code
-        else:  # the outcome of each side: OK or ENOTCONV
-            cp, cd = (0 if all(i["converged"] for i in infos) else -4 for infos in (ip, idl))
+        else:  # the outcome of each side (a breakdown of either is raised)
+            cp, cd = fftgal_outcome(self.handle, 0), fftgal_outcome(self.handle, 1)
         up, lo, gap = self.bounds()
         return {"upper": up, "lower": lo, "gap": gap, "info_primal": ip, "info_dual": idl,
                 "status_primal": cp, "status_dual": cd}
