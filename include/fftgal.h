@@ -125,6 +125,13 @@ enum fftgal_precision {
  * EINVAL with GaNi and reduced plans, whose grids the scheme fixes. */
 #define FFTGAL_FAST_GRID 0x1000
 
+/* Flag or-ed into `precision` of fftgal_workspace_bytes* and the plan
+ * constructors: the plan runs the solves of one call one after another, and its
+ * workspace has no room for more (see fftgal_workspace_bytes).  For plans whose
+ * solves run as members of a batch, one at a time.  The results are bitwise the
+ * same.  EINVAL with FFTGAL_CONCURRENT; no effect on reduced plans. */
+#define FFTGAL_ONE_AT_A_TIME 0x2000
+
 enum fftgal_material_kind {
     FFTGAL_INCLUSIONS = 0, /* eq. inclcomp: matrix phase plus inclusions          */
     FFTGAL_VOXELS = 1      /* eq. gridcomp: piecewise-constant voxel image        */
@@ -200,8 +207,9 @@ typedef struct fftgal_info {
  * (odd, >= 1) and precision needs; 0 if the arguments are invalid.  Used for
  * admission by HBM footprint.  For grids that one solve leaves the GPU idle on
  * it holds up to 32 MiB with which the d or 2d solves of one call run at once;
- * a plan also takes a workspace without that room and then runs them one after
- * another, with bitwise the same results.  If voxel images with resolution P other than
+ * a plan also takes a workspace without that room (the size with
+ * FFTGAL_ONE_AT_A_TIME) and then runs them one after another, with bitwise the
+ * same results.  If voxel images with resolution P other than
  * the plan's M will be set, pass the largest P through fftgal_workspace_bytes_p.
  */
 size_t fftgal_workspace_bytes(int d, const int32_t *N, int precision);

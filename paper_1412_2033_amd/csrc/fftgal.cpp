@@ -2065,23 +2065,24 @@ int scalar_inclusions(Plan *pl, const fftgal_material *m, std::vector<InclDev> &
     return FFTGAL_OK;
 }
 
-// least: without the copies of the solves run at once (a plan takes either).
-size_t workspace_bytes(int d, const int32_t *N, int precision, const int32_t *P, int scheme, bool least = false) {
+size_t workspace_bytes(int d, const int32_t *N, int precision, const int32_t *P, int scheme) {
     Dims D;
     const bool lean = (precision & FFTGAL_REDUCED_LEAN) != 0;
     const bool tensor = (precision & FFTGAL_TENSOR) != 0;
     const bool conc = (precision & FFTGAL_CONCURRENT) != 0;
     const bool fastg = (precision & FFTGAL_FAST_GRID) != 0;
+    const bool one = (precision & FFTGAL_ONE_AT_A_TIME) != 0;
     precision &= ~(FFTGAL_REDUCED_LEAN | FFTGAL_TENSOR | FFTGAL_CONCURRENT | FFTGAL_SEPARATE_PASSES |
-                   FFTGAL_FAST_GRID);
+                   FFTGAL_FAST_GRID | FFTGAL_ONE_AT_A_TIME);
     if (precision != FFTGAL_FP64 && precision != FFTGAL_FP32_ITER) return 0;
     if (lean && scheme != kSchemeReduced) return 0;
     if (tensor && scheme != kSchemeGa) return 0;
     if (conc && scheme == kSchemeReduced) return 0;
     if (fastg && scheme != kSchemeGa) return 0;
+    if (conc && one) return 0;
     if (!make_dims(d, N, nullptr, &D, scheme, tensor, fastg)) return 0;
     Layout Lo = make_layout(D, precision, !lean, conc ? 2 * d : 1);
-    if (!least) plan_at_once(D, &Lo);
+    if (!one) plan_at_once(D, &Lo);
     const size_t base = Lo.total + (conc ? bws_bytes(d) : 0);
     if (P == nullptr) return base + Lo.once_bytes;
     Dims DP;
@@ -2110,12 +2111,15 @@ int make_plan(struct fftgal_plan **out, int d, const int32_t *N, int precision, 
     const bool conc = (precision & FFTGAL_CONCURRENT) != 0;
     const bool sep = (precision & FFTGAL_SEPARATE_PASSES) != 0;
     const bool fastg = (precision & FFTGAL_FAST_GRID) != 0;
+    const bool one = (precision & FFTGAL_ONE_AT_A_TIME) != 0;
     precision &= ~(FFTGAL_REDUCED_LEAN | FFTGAL_TENSOR | FFTGAL_CONCURRENT | FFTGAL_SEPARATE_PASSES |
-                   FFTGAL_FAST_GRID);
+                   FFTGAL_FAST_GRID | FFTGAL_ONE_AT_A_TIME);
     if (precision != FFTGAL_FP64 && precision != FFTGAL_FP32_ITER)
         return fail(nullptr, FFTGAL_EINVAL, "unknown precision %d", precision);
     if (fastg && scheme != kSchemeGa)
         return fail(nullptr, FFTGAL_EINVAL, "FFTGAL_FAST_GRID applies to Ga plans only");
+    if (conc && one)
+        return fail(nullptr, FFTGAL_EINVAL, "FFTGAL_ONE_AT_A_TIME excludes FFTGAL_CONCURRENT");
     if (lean && scheme != kSchemeReduced)
         return fail(nullptr, FFTGAL_EINVAL, "FFTGAL_REDUCED_LEAN applies to reduced plans only");
     if (tensor && scheme != kSchemeGa)
@@ -2131,7 +2135,7 @@ int make_plan(struct fftgal_plan **out, int d, const int32_t *N, int precision, 
     const size_t bws = conc ? bws_bytes(d) : 0;  // the internal batch of the solves run at once
     // a workspace without room for the copies of the solves run at once is
     // taken too: the solves then run one after another
-    plan_at_once(D, &Lo);
+    if (!one) plan_at_once(D, &Lo);
     if (bytes < Lo.total + Lo.once_bytes) {
         Lo.at_once = 1;
         Lo.once_bytes = 0;
@@ -2223,7 +2227,8 @@ int fftgal_plan_static(struct fftgal_plan **out, int d, const int32_t *N, int pr
     *out = nullptr;
     size_t need = fftgal_workspace_bytes(d, N, precision);
     if (need == 0) return fail(nullptr, FFTGAL_EINVAL, "d must be 2 or 3, every N odd and >= 1, precision known");
-    if (need > kStaticBytes) need = workspace_bytes(d, N, precision, nullptr, kSchemeGa, true);
+    if (need > kStaticBytes && !(precision & FFTGAL_CONCURRENT))
+        need = fftgal_workspace_bytes(d, N, precision | FFTGAL_ONE_AT_A_TIME);
     if (need > kStaticBytes)
         return fail(nullptr, FFTGAL_ENOMEM, "the plan needs %zu bytes; the static workspace holds %zu", need,
                     kStaticBytes);

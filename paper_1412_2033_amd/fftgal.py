@@ -26,6 +26,7 @@ TENSOR = 0x200  # d(d+1)/2 material fields per side (matrix images, anisotropic 
 CONCURRENT = 0x400  # per-solve buffers for all 2d solves: they may run at once
 SEPARATE_PASSES = 0x800  # small grids: per-pass kernels instead of one work-group per 2D solve or 3D plane
 FAST_GRID = 0x1000  # Ga plans: the next of six double-grid lengths if the grid holds at most 4x the points
+ONE_AT_A_TIME = 0x2000  # no room for the solves of one call to run at once: one after another
 PRECISIONS = {"fp64": FP64, "fp32": FP32_ITER, "fp32_iter": FP32_ITER}
 
 STATUS = {0: "OK", -1: "EINVAL", -2: "ENOMEM", -3: "EDEVICE", -4: "ENOTCONV", -5: "ESTATE", -6: "EBREAKDOWN"}
@@ -379,7 +380,7 @@ class Plan:
     """A plan plus the torch device workspace it runs in."""
 
     def __init__(self, d, N, precision="fp64", device="cuda", stream=None, P=None, scheme="ga", lean=False,
-                 tensor=False, concurrent=False, separate_passes=False, fast_grid=False):
+                 tensor=False, concurrent=False, separate_passes=False, fast_grid=False, at_once=True):
         import torch
         if not torch.cuda.is_available():
             raise RuntimeError("fftgal needs a HIP device")
@@ -389,7 +390,7 @@ class Plan:
         self.scheme = scheme
         flags = self.precision | (REDUCED_LEAN if lean else 0) | (TENSOR if tensor else 0) | \
             (CONCURRENT if concurrent else 0) | (SEPARATE_PASSES if separate_passes else 0) | \
-            (FAST_GRID if fast_grid else 0)
+            (FAST_GRID if fast_grid else 0) | (0 if at_once or concurrent else ONE_AT_A_TIME)
         self.concurrent = bool(concurrent)
         self.nbytes = fftgal_workspace_bytes(self.d, self.N, flags, P, scheme)
         if self.nbytes == 0:

@@ -60,8 +60,9 @@ class Server:
         return bool(self.concurrent)
 
     def flags_for(self, d, N):
-        return fftgal.PRECISIONS[self.precision] | (fftgal.CONCURRENT if self.concurrent_for(d, N) else 0) | \
-            (fftgal.FAST_GRID if self.fast_grid else 0)
+        # a plan of one buffer set solves as a batch member only: no room for solves at once
+        return fftgal.PRECISIONS[self.precision] | (fftgal.FAST_GRID if self.fast_grid else 0) | \
+            (fftgal.CONCURRENT if self.concurrent_for(d, N) else fftgal.ONE_AT_A_TIME)
 
     def _plan(self, d, N):
         key = (d, N)
@@ -84,7 +85,7 @@ class Server:
         self.peak_bytes = max(self.peak_bytes, self.used_bytes)
         self.plans_created += 1
         return fftgal.Plan(d, N, self.precision, device=self.device, stream=self.batch.stream,
-                           concurrent=self.concurrent_for(d, N), fast_grid=self.fast_grid)
+                           concurrent=self.concurrent_for(d, N), fast_grid=self.fast_grid, at_once=False)
 
     def run(self, requests, realtime=True):
         """Serve `requests` (dicts with id, arrival_s, N, micro); returns per-request records."""
