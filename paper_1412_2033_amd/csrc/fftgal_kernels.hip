@@ -1680,9 +1680,12 @@ __global__ __launch_bounds__(kThreads) void ckpt_decide_kernel(CgStatus *st, con
                                                                int final) {
     const bool skip = final ? (st->converged || st->breakdown) : st->done;
     if (skip) {
+        // a stalled solve keeps its restore mark (the copy is then repeated, with
+        // the same result): solves that run together go on with their periodic
+        // checkpoints until the last of them is done
         if (threadIdx.x == 0) {
             st->ck_copy = 0;
-            st->ck_restore = 0;
+            if (final) st->ck_restore = 0;
         }
         return;
     }
