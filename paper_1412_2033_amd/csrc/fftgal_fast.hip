@@ -161,10 +161,10 @@ template <typename T> __device__ __forceinline__ Vt<T> chirp_at(const Vt<T> *chi
 // row pairs per work-group of the specialised anisotropic row pass so that
 // one batch of all d components stays within 24 KB of LDS (the passes are
 // latency-bound: smaller work-groups put more of them on a CU)
-constexpr bool small_tile(int n, int es, int d);
+constexpr bool small_tile(int n, int d);
 constexpr int fast_batch(int n, int es, int d) {
     const int cap = 24 * 1024;
-    int b = !small_tile(n, es, d) || (n == 125 && d == 3) ? 16 : d == 2 ? 2 : 4;
+    int b = !small_tile(n, d) ? 16 : d == 2 ? 2 : 4;
     while (b > 1 && d * b * n * es > cap) b /= 2;
     return b;
 }
@@ -184,30 +184,46 @@ constexpr int fast_batch(int n, int es, int d) {
 // radix-9 butterflies busy in one round, against two rounds for 2 pencils and
 // 256 threads): a batch of 16 such solves 7 % faster.
 // Small grids take small tiles, so that their few pencils spread over the CUs:
-// in 2D transforms below 300 points one pencil (n / 4 pencils make a pass), in
-// 3D up to 63 points two, and the 3D FP32 transforms of 125 points four (of
-// the eight that fit).  Per iteration of all 2d solves: 2D 189 x 135 FP64 33.3
-// -> 29.3 us, 2D 315^2 FP32 30.3 -> 27.2, 3D 45^3 FP32 36.2 -> 29.5, 3D 125^3
-// FP32 269 -> 255; at 405^2 one pencil cost 5 %, at 75^3 two cost 6 %.
-constexpr bool small_tile(int n, int es, int d) {
-    return d == 2 ? n < 330 : n <= 63 || (n == 125 && es < 16);
+// in 2D transforms below 330 points one pencil (n / 4 pencils make a pass), in
+// 3D up to 63 points two and up to 135 points four.  Per iteration of all 2d
+// solves: 2D 189 x 135 FP64 33.3 -> 29.3 us, 2D 315^2 FP32 30.3 -> 27.2, 3D 45^3
+// FP32 36.2 -> 29.5; at 405^2 one pencil cost 5 %, at 75^3 two cost 6 %.  Four
+// passes of a dual 3D solve, FP32, with the pencils that 24 KB hold (eight, at
+// 135 points four) and with four: 75^3 25.2 -> 21.5 us, 105^3 31.2 -> 27.7, 125^3
+// 38.3 -> 34.8, 135^3 38.7; FP64 (four, at 135 points two) 135^3 57.1 -> 46.0.
+// From 147 points on four were no better in FP32 and 1 % worse at 189^3 FP64.
+constexpr bool small_tile(int n, int d) { return d == 2 ? n < 330 : n <= 63; }
+constexpr int kFourPencils = 135;  // longest 3D transform that takes four pencils
+// Two components of 3D gradient fields.  Schedules of two stages of radix 9 or
+// 15 (81, 135, 225 points) take nine pencils and 512 threads: a stage's 18 n / r
+// butterflies fill one round of the threads, and two FP64 tiles of 225 points
+// fit a CU.  The others take two pencils up to 63 points, four up to 135, then
+// what 20 KB hold.  Expand and project together, in us, FP64 / FP32, with the
+// pencils 20 KB hold and now: 75^3 13.8 / 15.4 -> 11.9 / 10.6, 81^3 11.5 / 12.9
+// -> 11.9 / 10.5, 105^3 14.8 / 14.0 -> 14.9 / 12.4, 135^3 18.9 / 18.8 -> 17.9 /
+// 16.1; 225^3 47.0 / 27.5 (four pencils) -> 45.0 / 24.5.  Nine pencils lose where
+// a stage takes more rounds or leaves lanes idle: 125^3 16.0 / 14.4 -> 17.4 / 16.3,
+// 147^3 FP64 20.5 -> 22.2, 243^3 58.7 / 36.2 -> 79.1 / 38.4.  At order 113 two
+// components in place of three took expand / project from 31.4 / 29.4 to 25.9 /
+// 23.5 us per launch, FP64.
+constexpr bool nine_pencils(int n) {
+    const int fi = fast_index(n);
+    if (kFastSched[fi].nst != 2) return false;
+    for (int i = 0; i < 2; ++i)
+        if (kFastSched[fi].r[i] != 9 && kFastSched[fi].r[i] != 15) return false;
+    return true;
 }
-// Two components of 225 points: 9 FP64 (13 FP32) pencils and 512 threads, 716
-// (496) tiles for the 113 x 57 pencils of an axis-1 pass; expand / project per
-// launch 31.4 / 29.4 -> 25.9 / 23.5 us (FP32 17.7 / 16.4 -> 15.5 / 13.8)
-// against three components; 7, 8, 10 and 12 FP64 pencils took 28.5, 29.5, 31.8
-// and 36.3 us, 8, 9, 10 and 16 FP32 ones 17.3, 15.6, 20.9 and 16.6.
 constexpr int two_batch(int n, int es, bool blue) {
-    if (!blue && n == 225) return es >= 16 ? 9 : 13;
-    if (!blue && small_tile(n, es, 3)) return es >= 16 || n < 125 ? 2 : 4;
+    if (!blue && nine_pencils(n)) return 9;
+    if (!blue && n <= kFourPencils) return small_tile(n, 3) ? 2 : 4;
     const int cap = blue && n > 105 ? 36 * 1024 : 20 * 1024;
     int b = blue ? 8 : 16;
     while (b > 1 && 2 * b * n * es > cap) b /= 2;
     return b;
 }
-constexpr int two_nt(int n, int es, bool blue) {
-    if (!blue && n == 225) return 512;
-    return !blue && small_tile(n, es, 3) && n <= 63 ? 128 : kThreads;
+constexpr int two_nt(int n, bool blue) {
+    if (!blue && nine_pencils(n)) return 512;
+    return !blue && small_tile(n, 3) ? 128 : kThreads;
 }
 // Bluestein tiles: up to 8 pencils within 24 KB for the short lengths (their
 // grids are small), 48 KB for the others, whose two transforms per pencil need
@@ -223,7 +239,8 @@ constexpr int pencil_batch(int n, int es, int d, bool blue = false) {
     }
     if (d == 3 && n == 225) return es >= 16 ? 7 : 9;
     if (es < 16 && d == 2 && n == 729) return 3;
-    if (small_tile(n, es, d)) return d == 2 ? 1 : es >= 16 || n < 125 ? 2 : 4;
+    if (small_tile(n, d)) return d == 2 ? 1 : 2;
+    if (d == 3 && n <= kFourPencils) return 4;
     const int cap = (es >= 16 && d == 3 && n > 225) ? 48 * 1024 : 24 * 1024;
     int b = 16;
     while (b > 1 && d * b * n * es > cap) b /= 2;
@@ -236,9 +253,9 @@ constexpr int pencil_batch(int n, int es, int d, bool blue = false) {
 // 15 points per stage), so that every stage of the transform takes one round
 // of the threads; else 256
 constexpr int pencil_nt(int n, int es, int d, bool blue = false) {
-    if (d == 1) return two_nt(n, es, blue);
+    if (d == 1) return two_nt(n, blue);
     if (blue) return n >= 1125 ? 512 : kThreads;
-    if (small_tile(n, es, d)) return n == 125 && d == 3 ? kThreads : 128;
+    if (small_tile(n, d)) return 128;
     return ((es >= 16 && d == 2 && n >= 2025) || (es < 16 && d == 2 && n == 729) || (d == 3 && n == 225))
                ? 512
                : kThreads;
