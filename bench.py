@@ -217,7 +217,7 @@ def main():
     ap.add_argument("--fast-grid", type=int, default=1,
                     help="FFTGAL_FAST_GRID against the default grid at 3D N = 81 and 2D N = 201 (0: skip)")
     ap.add_argument("--generic", type=int, default=1,
-                    help="plans on lengths without specialised kernels (3D 45^3, GaNi 41^3 and 201^2; 0: skip)")
+                    help="small grids and Bluestein orders (3D 45^3, GaNi 41^3 and 201^2; 0: skip)")
     ap.add_argument("--envelope", type=int, default=1,
                     help="upper-upper / lower-lower bounds section on an anisotropic cube inclusion (0: skip)")
     ap.add_argument("--copy-calibration", type=int, default=0, metavar="BYTES",
@@ -579,8 +579,8 @@ def reduced_bench(fftgal, micro_dev, d, P, Nr, rtol, dev, variants=("reduced", "
 
 def fast_grid_bench(fftgal, micro_dev, d, P, dev, N3=81, N2=201):
     """FFTGAL_FAST_GRID against the default grid: the benchmark image at 3D
-    order N3 (default double grid 175^3, generic kernels; fast 225^3) and the
-    2D disc at order N2 (405^2 against 729^2), FP64."""
+    order N3 (default double grid 175^3; with the flag 225^3) and the 2D disc at
+    order N2 (405^2 against 729^2), FP64."""
     import numpy as np
     import synth
     import torch
@@ -615,11 +615,11 @@ def fast_grid_bench(fftgal, micro_dev, d, P, dev, N3=81, N2=201):
 
 
 def generic_bench(fftgal, dev):
-    """Plans on lengths without specialised kernels (the generic transform
-    kernels): the 3D double grid 45^3 (order 21, radices 9 5), 3D GaNi of order
-    41 (Bluestein, L = 81) and 2D GaNi of order 201 (Bluestein, L = 405 = 9 9 5),
-    FP64 and FP32 iterations; time to bounds (set_material, 2d solves, bounds;
-    best of two runs after a warm-up) and that time per CG iteration."""
+    """Plans on lengths other than those of the main workloads: the 3D double grid
+    45^3 (order 21, plane passes), 3D GaNi of order 41 (Bluestein, L = 81) and 2D
+    GaNi of order 201 (Bluestein, L = 405), FP64 and FP32 iterations; time to
+    bounds (set_material, 2d solves, bounds; best of two runs after a warm-up) and
+    that time per CG iteration."""
     import synth
     import torch
     print("bench: generic lengths", file=sys.stderr, flush=True)

@@ -119,8 +119,9 @@ enum fftgal_precision {
  * holds at most four times the points of the default grid or at most 2^21
  * points (else the default grid).  The double-grid
  * quadrature is exact for every M >= 2N - 1 (Lemma integ_eval_VM, eq. MBA_GA),
- * so the bounds are those of the default grid up to rounding.  The kernels of
- * these lengths are the most tuned ones; the workspace grows with the grid.
+ * so the bounds are those of the default grid up to rounding.  Orders that are
+ * near each other share a grid length this way; the larger grid itself takes
+ * more time and workspace.
  * fftgal_grid_size reports the grid taken.
  * EINVAL with GaNi and reduced plans, whose grids the scheme fixes. */
 #define FFTGAL_FAST_GRID 0x1000
@@ -398,10 +399,9 @@ int fftgal_bounds_of(struct fftgal_plan *plan, struct fftgal_plan *src, double *
  * inverse DFT of size N), and every operator application runs the transform
  * passes once per shift with the phases S(s), S*(s) of the lemma, summing the
  * projected results.  Every N_a must be odd; 3,5,7-smooth lengths from 9 to
- * 2025 (3D: to 405, and 729 and 2025) and the lengths to 385 with factors 11
- * and 13 run the specialised kernels, other smooth
- * lengths the generic ones, and the other lengths (the primes 41, 113, 1013
- * among them) Bluestein's chirp convolution of the smooth length L >= 2 N_a - 1
+ * 2025 (3D: to 405, and 729 and 2025) and 20 lengths to 385 with a factor 11
+ * or 13 run the specialised kernels, other smooth lengths the generic ones, and
+ * the other lengths (the primes 41, 113, 1013 among them) Bluestein's chirp convolution of the smooth length L >= 2 N_a - 1
  * (in specialised kernels when L has them).  Solves, bounds, history and the
  * bound tolerance work as for fftgal_plan; warm starts, a-posteriori bounds and
  * batches are not available (EINVAL).  The workspace holds 2^d
@@ -451,7 +451,9 @@ int fftgal_grid_size(const struct fftgal_plan *plan, int axis);
  * bracketed by two event records on the plan's stream.  fftgal_read_timing()
  * waits for the stream, writes the summed milliseconds and the launch counts
  * per class (arrays of FFTGAL_K_COUNT entries; either may be NULL) since the
- * previous read, and resets them.
+ * previous read, and resets them.  While a class is timed, plans without
+ * FFTGAL_CONCURRENT run the solves of one call one after another, also where they
+ * would run at once: the times of small grids are those of solves alone.
  */
 enum fftgal_kernel_class {
     FFTGAL_K_EXPAND = 0,      /* CG state -> d components, inverse DFT along axis 1 */

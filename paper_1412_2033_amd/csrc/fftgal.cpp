@@ -1697,8 +1697,8 @@ int run_solve_solo(Plan *pl, int kind, int alpha, int maxit, fftgal_info *info) 
 
 // Iterations to enqueue next, from the residual reduction since the previous
 // read of the status (at the first read: since the start): an iteration
-// enqueued past convergence costs its seven no-op launches, one too few a read
-// of the status.
+// enqueued past convergence costs its no-op launches (five in 2D and with plane
+// passes, seven in 3D), one too few a read of the status.
 struct ChunkRate {
     int it = -1;  // iterations at the previous read (-1: none yet)
     double rr = 0.0;
@@ -3041,8 +3041,9 @@ int run_stages(Plan *pl, const std::vector<PassRec> &ps, int width, int cls) {
 // the launches and waits of one solve (FP64, to bounds: 2D 95 x 67, four
 // solves, 9.7 -> 3.5 ms; 3D order 21, six, 6.9 -> 1.5 ms; 2D order 41, four
 // work-groups side by side, 4.6 -> 1.24 ms; 2D order 1013, two at a time, 43.3
-// -> 36.8 ms).  Every solve keeps its own reductions: its result equals bitwise that of the solve alone.  Returns the
-// first non-OK outcome after all solves ran, or a hard error at once; `info`
+// -> 36.8 ms).  Every solve keeps its own reductions: its result equals bitwise
+// that of the solve alone.  Returns the first non-OK outcome, with its message,
+// after all solves ran, or a hard error at once; `info`
 // (may be NULL) receives the outcomes in the order of the jobs.
 int group_solve(Plan *pl, const std::vector<std::pair<int, int>> &jobs, double rtol, int maxit, fftgal_info *info) {
     const bool fp64 = pl->fp64_iter();

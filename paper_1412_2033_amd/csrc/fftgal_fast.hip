@@ -1594,7 +1594,7 @@ __global__ __launch_bounds__(kThreads) void row_gram_fast(const RowArgs *__restr
 // whose D transforms would take more than 16 KB run one transform per
 // work-group (pair-major, material values read at the multiply), so that
 // several work-groups share a CU.  It is bound by memory on large grids and by
-// its LDS stages on small ones: 175^3 FP64 55 us a launch (2.6 TB/s), against
+// its LDS stages on small ones: 175^3 FP64 55 us a launch (163 MB, 3.0 TB/s), against
 // 138 us in the kernel of run-time lengths.
 constexpr bool pairs_one(int n, int es, int d) { return d * n * es > 16 * 1024; }
 constexpr int pairs_pw(int n, int es, int d) {
@@ -1603,11 +1603,12 @@ constexpr int pairs_pw(int n, int es, int d) {
     while (p > 1 && d * p * n * es > cap) --p;
     return p;
 }
-// 125 points keep the general row pass (3D, order 63, one iteration of
-// all six solves: 323 us FP32 and 375 FP64 with it, 325 and 372 with this one): the best-iterate guard of FP32 solves
-// at contrasts near 1e4 compares energies at the rounding level of the operator
-// (they cancel to 1e-3 of its terms), and its tests hold the outcome for the
-// rounding of that pass
+// The first six lengths keep the kernels above.  Theirs -> this one, us: 2025
+// points FP64 258 -> 269 and 729 points 43.2 -> 45.6 per iteration of four solves
+// at once (2D); 125 points, 3D order 63, the row pass 30.5 -> 29.6 (FP32 17.5 ->
+// 15.5), but six solves at once 375 -> 372 (FP32 323 -> 325).  245 points would
+// gain: 2D 21.1 -> 20.0 per iteration of four solves, the row pass of 3D order
+// 123 155 -> 145 (FP32 71.8 -> 69.9).
 constexpr bool has_pairs(int fi) { return fi >= kNumGridLengths; }
 constexpr int pairs_tb(int n, int es, int d) { return pairs_one(n, es, d) ? 1 : d * pairs_pw(n, es, d); }
 constexpr int pairs_rl(int fi) { return kFastSched[fi].r[kFastSched[fi].nst - 1]; }
@@ -1797,11 +1798,11 @@ void row_iso_pairs(const RowArgs *__restrict__ ra, const int *__restrict__ woff,
 // Taken up to 63 points per axis; us per iteration, all six solves at once /
 // one solve: 9^3 FP64 22 / 19 -> 18 / 16, 35^3 40 / 35 -> 31 / 27, 45^3 46 / 36
 // -> 39 / 31, 63^3 69 / 37 -> 60 / 34, FP32 48 / 29 -> 39 / 26.  From 75 points
-// (137 KB of LDS in FP64) one plane per CU runs at a time and the three passes
-// are as fast or faster: 75^3 FP64 131 / 43 -> 137 / 46, 75^3 FP32 89 / 36 ->
-// 85 / 39, 105^3 FP32 142 / 45 -> 141 / 43.
-// 512 threads within 128 registers put two work-groups on a CU; at 45 points,
-// FP64, 640 and 1024 threads took 44 us (one work-group per CU), 384 took 40.
+// the three passes are as fast or faster: 75^3 FP64 131 / 43 -> 137 / 46, 75^3
+// FP32 89 / 36 -> 85 / 39, 105^3 FP32 142 / 45 -> 141 / 43.
+// 512 threads within 128 registers let two work-groups share a CU where the LDS
+// does (FP64: up to 49 points, 60 KB; 63 points take 98 KB, one per CU); at 45
+// points, FP64, 640 and 1024 threads took 44 us (one per CU), 384 took 40.
 constexpr int plane_nt(int n) { return n <= 25 ? 256 : 512; }
 constexpr size_t plane_lds(int n, int es) {
     return (size_t)es * ((size_t)n * 3 * ((n + 1) / 2) + tw_lds_entries(n, es));

@@ -36,12 +36,12 @@ struct FftDesc {
 // Transform lengths with compile-time specialised kernels, and their radix
 // schedules (composite radices are done in registers): every odd 3,5,7-smooth
 // length from 9 to 2025, the lengths a double grid takes, and, for the plans
-// whose transforms have the length of the order itself (GaNi, reduced Ga), the
-// odd lengths up to 385 with prime factors up to 13, which would otherwise run
-// Bluestein's convolution of twice the length (3D GaNi of order 99 with its
-// bounds, FP64: 121 -> 67 ms).  The host builds the twiddle tables of these lengths
-// with the same schedule, and the generic kernels run it too (radices 3, 5, 7,
-// 9, 11, 13, 15, 25).  The schedules of the first six read the same forwards and
+// whose transforms have the length of the order itself (GaNi, reduced Ga), 20
+// odd lengths up to 385 with a factor 11 or 13 (those listed below; 275, 351 and
+// 363 are not among them), which would otherwise run Bluestein's convolution of
+// twice the length (3D GaNi of order 99 with its bounds, FP64: 121 -> 67 ms).
+// The host builds the twiddle tables of these lengths with the same schedule,
+// and the generic kernels run it too (radices 3, 5, 7, 9, 11, 13, 15, 25).  The schedules of the first six read the same forwards and
 // backwards where the length allows: then the last stage of an inverse
 // transform leaves each thread holding exactly the points that the first stage
 // of a forward transform consumes.  The others get that from running the

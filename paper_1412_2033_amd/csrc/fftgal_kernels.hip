@@ -1329,7 +1329,7 @@ constexpr size_t solo_lds_bytes_t(int m0, int m1) {
     return sizeof(Vt<T>) * ((size_t)m0 * m1 + m0 + m1 + (m0 + 1) / 2);
 }
 
-// fixed-order sum over the 1024 threads (shuffle tree per wave, then the
+// fixed-order sum over the NT threads (shuffle tree per wave, then the
 // waves in turn by thread 0), broadcast to every thread
 template <int NT>
 __device__ __forceinline__ double solo_sum(double v, double *red) {
