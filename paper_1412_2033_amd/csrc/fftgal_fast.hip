@@ -1594,7 +1594,7 @@ __global__ __launch_bounds__(kThreads) void row_gram_fast(const RowArgs *__restr
 // whose D transforms would take more than 16 KB run one transform per
 // work-group (pair-major, material values read at the multiply), so that
 // several work-groups share a CU.  It is bound by memory on large grids and by
-// its LDS stages on small ones: 175^3 FP64 55 us a launch (163 MB, 3.0 TB/s), against
+// its LDS stages on small ones: 175^3 FP64 50 us a launch (164 MB, 3.3 TB/s), against
 // 138 us in the kernel of run-time lengths.
 constexpr bool pairs_one(int n, int es, int d) { return d * n * es > 16 * 1024; }
 constexpr int pairs_pw(int n, int es, int d) {
